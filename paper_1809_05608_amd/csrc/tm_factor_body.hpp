@@ -1,6 +1,9 @@
 // Fused Jacobian assembly + block-Thomas factor/solve of the linearised transport
 // step (eq. a62ae), one (species, ray) system per SL-lane group of a wavefront.
 //
+// These lane kernels serve the partial-pivoting re-run (both precisions) and the float32 solves that the
+// quad kernel does not take; FP64 solves with diagonal pivots run on matrix-core tiles (tm_factor_t.hip).
+//
 // Layout on the chip: lane k of a group owns row k of the current zone's dense N x N
 // block (N <= NT <= 32, SL = 16 or 32 lanes per system, 4 or 2 systems per wave64).
 // The sweep over radial zones is sequential inside the group; systems run in parallel.
@@ -582,14 +585,8 @@ __device__ __forceinline__ void factor_sweeps(const FactorArgs& A) {
 }
 
 
-// waves per SIMD the register allocation is held to: two for the FP64 kernels with diagonal pivots (forward and
-// transposed) up to 20 groups (they fit 256 VGPRs without scratch and run a third faster than at one), one
-// otherwise
-template <typename T, int NT, bool TRANS, bool PIVOT>
-constexpr int factor_waves_per_eu() { return (sizeof(T) == 8 && NT <= 20 && !PIVOT) ? 2 : 1; }
-
 template <typename T, int NT, bool TRANS, bool PIVOT, bool GEO>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 1 : factor_waves_per_eu<T, NT, TRANS, PIVOT>())))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1)))
 void k_factor(FactorArgs A) {
     factor_sweeps<T, NT, TRANS, PIVOT, true, GEO>(A);
 }
@@ -617,11 +614,11 @@ static void launch_t(const FactorArgs& a, hipStream_t st) {
 
 template <typename T, int NT, bool GEO>
 static void launch_tp(const FactorArgs& a, bool tr, bool pv, hipStream_t st) {
-    if (tr) {
-        if (pv) launch_t<T, NT, true, true, GEO>(a, st);
-        else launch_t<T, NT, true, false, GEO>(a, st);
-    } else {
-        if (pv) launch_t<T, NT, false, true, GEO>(a, st);
+    if (pv) {
+        if (tr) launch_t<T, NT, true, true, GEO>(a, st);
+        else launch_t<T, NT, false, true, GEO>(a, st);
+    } else if constexpr (std::is_same<T, float>::value) {           // FP64 with diagonal pivots: k_factor_tile
+        if (tr) launch_t<T, NT, true, false, GEO>(a, st);
         else launch_t<T, NT, false, false, GEO>(a, st);
     }
 }
