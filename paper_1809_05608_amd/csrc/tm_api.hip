@@ -67,7 +67,7 @@ struct tm_ctx {
     int* y_flags = nullptr;
     int* y_pending = nullptr;
     int* y_backtrack = nullptr;
-    int* y_redo = nullptr;       // rays of the tiled diagonal-pivot launch sent to partial pivoting
+    int* y_redo = nullptr;       // rays of the diagonal-pivot launch sent to partial pivoting
     // inputs with the lapse folded in (allocated on first use with a lapse)
     double* lp_ka = nullptr;
     double* lp_et = nullptr;
@@ -930,23 +930,23 @@ tm_status tm_ye_newton_step(tm_ctx* c, const tm_inputs* in, const tm_ye_inputs* 
     a.alpha = c->y_alpha;
     a.ws = static_cast<double*>(c->ws);
     a.growth_limit = c->growth_limit;
-    // Diagonal pivots on lane tiles, with the rays the growth guard sends back re-run with partial
-    // pivoting (TM_PIVOT=always: partial pivoting only; =never: a guard trip is an error).  The
-    // neutrinosphere options and the pair processes take the partial-pivoting kernel.
-    const bool tiled = c->pivot_policy != 1 && tmk::ye_tiled_applies(a);
+    // Diagonal pivots, with the rays the growth guard sends back re-run with partial pivoting
+    // (TM_PIVOT=always: partial pivoting only; =never: a guard trip is an error, and the problems with
+    // neutrinosphere options, pair processes or a lapse take partial pivoting).
+    const bool diagonal = c->pivot_policy == 0 || (c->pivot_policy == 2 && tmk::ye_plain(a));
     const int max_trials = 9;                              // alpha = 1, 1/2, ..., 1/256
     for (int it = 0; it < max_iter; ++it) {
         int nact = 0;
         TM_TRY(count_of(c->y_active, &nact));
         if (nact == 0) break;
-        if (tiled && c->pivot_policy == 2)
+        if (diagonal && c->pivot_policy == 2)
             TM_TRY(hip_check(c, tmk::launch_fill_i32(c->y_redo, R, 0, c->stream), "fill kernel"));
         for (long long r0 = 0; r0 < R; r0 += batch) {
             a.ray0 = r0;
             a.nray = std::min(batch, R - r0);
-            if (tiled) {
+            if (diagonal) {
                 a.redo = c->y_redo;
-                TM_TRY(hip_check(c, tmk::launch_ye_factor_tiled(a, c->stream), "coupled tiled factor kernel"));
+                TM_TRY(hip_check(c, tmk::launch_ye_factor_wave(a, c->stream), "coupled diagonal-pivot factor kernel"));
                 if (c->pivot_policy != 2)        // the marked rays of this batch, with partial pivoting
                     TM_TRY(hip_check(c, tmk::launch_ye_factor(a, c->stream), "coupled factor kernel"));
             } else {
@@ -954,7 +954,7 @@ tm_status tm_ye_newton_step(tm_ctx* c, const tm_inputs* in, const tm_ye_inputs* 
                 TM_TRY(hip_check(c, tmk::launch_ye_factor(a, c->stream), "coupled factor kernel"));
             }
         }
-        if (tiled && c->pivot_policy == 2) {
+        if (diagonal && c->pivot_policy == 2) {
             int nredo = 0;
             TM_TRY(count_of(c->y_redo, &nredo));
             if (nredo > 0) return set_err(c, TM_ERR_SINGULAR, "diagonal-pivot growth guard tripped in the coupled step");

@@ -66,14 +66,6 @@ __device__ __forceinline__ double at(const double* base, unsigned off) {
 
 namespace {
 
-// The lane id through an opaque instruction: what is derived from it is formed again where it is used
-// instead of being held in registers across the zone loop.
-__device__ __forceinline__ int opaque_lane() {
-    int ln;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-    return ln;
-}
-
 // Which system, half and zones a lane works on.  Everything but the lane is uniform over the wavefront.
 struct Place {
     TileLane L;
@@ -217,7 +209,25 @@ void k_factor_tile(FactorArgs A) {
 #pragma unroll
         for (int t = 0; t < T; ++t) S[s][t] = 0.0;
     }
-    TileGuard guard;
+    TileGuard guard(A.growth_limit);
+
+    // C and y of step n.  Stored in the middle of the next step, not at the end of their own: loads and stores
+    // complete in order, so the wait for the next zone's loads would otherwise include the stores just issued.
+    typedef double V2 __attribute__((ext_vector_type(2)));
+    auto store = [&](int n, int ln, const TileLane& L) {
+        double* q = ws + (size_t)n * step_doubles<T>();
+        V2* q2 = reinterpret_cast<V2*>(q) + ln;
+#pragma unroll
+        for (int j = 0; j < T * T / 2; ++j)
+            nt_store(q2 + 64 * j, V2{S[(2 * j) / T][(2 * j) % T], S[(2 * j + 1) / T][(2 * j + 1) % T]});
+        if constexpr (T & 1) nt_store(q + 64 * (T * T - 1) + ln, S[T - 1][T - 1]);
+        double y1 = 0.0, y2 = 0.0;
+        tile_row_to_owner<T>(y, L, y1, y2);
+        double* qy = q + 64 * T * T + L.g * NT;
+        if (4 * L.b < NT) nt_store(qy + 4 * L.b + L.a, y1);
+        if constexpr (T > 4)
+            if (16 + 4 * L.b < NT) nt_store(qy + 16 + 4 * L.b + L.a, y2);
+    };
 
     for (int n = 0; n <= m; ++n) {
         const int ln = opaque_lane();
@@ -286,7 +296,7 @@ void k_factor_tile(FactorArgs A) {
                 sm.ps[q] = make_double2(real ? psi : 0.0, sch);
                 sm.rb[q] = make_double2(g, bco);
                 sm.dg[q] = diag;
-                if (nes) sm.df[q] = P.own(j) + 1 < N ? exp_nonpos(w[5][ln] * rcp_cubic(Tz)) : 0.0;
+                if (nes) sm.df[q] = P.own(j) + 1 < N ? exp_nonpos(w[5][ln] * rcp_cubic(Tz), exp_coef()) : 0.0;
             }
             w[0][ln] = n_psi;                                            // the next zone becomes the current one
             w[1][ln] = n_sig;
@@ -294,6 +304,7 @@ void k_factor_tile(FactorArgs A) {
             __builtin_amdgcn_sched_barrier(0);
         }
         wave_sync();
+        if (n > 0) store(n - 1, ln, L);
         // ---- loads of the coming step
         const double ampc = idle ? 0.0 : amp;
         {
@@ -414,19 +425,6 @@ void k_factor_tile(FactorArgs A) {
 #pragma unroll
                 for (int t = 0; t < T; ++t) S[s][t] *= bco;
             }
-            double* q = ws + (size_t)n * step_doubles<T>();
-            double2* q2 = reinterpret_cast<double2*>(q) + ln;
-            typedef double V2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-            for (int j = 0; j < T * T / 2; ++j)
-                nt_store(reinterpret_cast<V2*>(q2 + 64 * j), V2{S[(2 * j) / T][(2 * j) % T], S[(2 * j + 1) / T][(2 * j + 1) % T]});
-            if constexpr (T & 1) nt_store(q + 64 * (T * T - 1) + ln, S[T - 1][T - 1]);
-            double y1 = 0.0, y2 = 0.0;
-            tile_row_to_owner<T>(y, L, y1, y2);
-            double* qy = q + 64 * T * T + L.g * NT;
-            if (4 * L.b < NT) nt_store(qy + 4 * L.b + L.a, y1);
-            if constexpr (T > 4)
-                if (16 + 4 * L.b < NT) nt_store(qy + 16 + 4 * L.b + L.a, y2);
         }
         r_t = r_l;
         r_l = r_b;
@@ -440,7 +438,7 @@ void k_factor_tile(FactorArgs A) {
     const TileLane& L = P.L;
     const bool live = (L.g >> 1) ? live1 : live0;
     const long long sys = first + (P.second(two) ? 1 : 0);
-    const unsigned long long bad = __ballot(guard.tripped(A.growth_limit));
+    const unsigned long long bad = guard.bad;
     const bool skip = (bad & ((L.g >> 1) ? 0xFF00FF00FF00FF00ull : 0x00FF00FF00FF00FFull)) != 0;
     const bool lead = (lane & 0x37) == 0;                                 // first lane of each system
     if (live && lead && skip) {

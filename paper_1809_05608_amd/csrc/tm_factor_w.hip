@@ -1,0 +1,637 @@
+// FP64 assembly + block elimination + solve with one wavefront per half ray: the Y_e-coupled blocks.
+//
+// A ray is eliminated from both ends at once by the two wavefronts of a workgroup (zones 0 .. m-1 upwards and
+// I-1 .. m+1 downwards, meeting in zone m = I/2).  The transpose of a zone's block is spread over the whole
+// wavefront: register S[q][C] of lane 16 a + j holds row 4q + a, column 16C + j.  Each register is a row group
+// of four rows by 16 columns, that is, the B operand of v_mfma_f64_4x4x4 with its four blocks taking four
+// column groups of the same matrix; the A operand is then a 4 x 4 tile repeated for every block.  Four row groups
+// are a result of v_mfma_f64_16x16x4, whose B operand is the same and whose A operand holds 16 rows at once.
+//
+// Rows and columns of a coupled block: psi of nu_e in 0 .. NT-1, of anti-nu_e in NT .. 2NT-1, Y_e at 2NT (NT =
+// N padded to a multiple of 4; padding is identity), in row groups of four: G = 2T + 1.  Per pivot group the
+// panel of four columns goes through LDS, every lane inverts the 4 x 4 pivot, and G products per 16 columns
+// update the block.  The block is inverted in place, y = Ahat^-1 g and the back substitution are weighted column
+// sums over the registers.
+//
+// One wavefront per half ray, because a 41 x 41 block in one wavefront's registers (33 of them) leaves two
+// wavefronts to a SIMD, and the chain of zones is half as long as from one end.  With few rays a step is the
+// latency of one wavefront: 11 dependent panels of an LDS round trip, a 4 x 4 inversion (about 75 vector
+// operations) and the products.  With many rays the factors' way through memory (13.4 kB a zone, written once and
+// read once) comes to half the time.  Per update, 540 zones x 20 groups, residual passes included, against one
+// ray per wavefront on 8 x 8 tiles of the vector unit from one end: 90 rays 14.2 -> 4.0 ms, 2048 rays 21.4 -> 16 ms,
+// 8192 rays 74 -> 55 ms.  Lapse, neutrinosphere options and pairs had partial pivoting
+// on the vector unit only; with pairs 90 rays 18 -> 5 ms.
+#include "tm_kernels.hpp"
+#include "tm_tile.hpp"
+
+namespace tmk {
+
+namespace {
+
+// Sum over the wavefront, in every lane: column sums on the matrix core, then rotations within 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const long long w = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)w, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(w >> 32), CTRL, 0xF, 0xF, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+    v = mfma4(1.0, v, 0.0);
+    v = dpp_add<0xB1>(v);              // quad [1,0,3,2]
+    v = dpp_add<0x4E>(v);              // quad [2,3,0,1]
+    v = dpp_add<0x124>(v);             // row_ror:4
+    return dpp_add<0x128>(v);          // row_ror:8
+}
+
+template <int T>
+struct CoupledShape {
+    static constexpr int NT = 4 * T, NC = 2 * NT, M = NC + 1;
+    static constexpr int G = 2 * T + 1, Q = 2 * T, CN = (G + 3) / 4;   // row groups, those of C, column registers
+    static constexpr int W = 16 * CN;                                  // columns held
+    // column stride of the panel (doubles): 4 past a multiple of 16, so that the 16 lanes that write it (four
+    // columns by four rows) hit different banks (a multiple of 16 costs twice the cycles)
+    static constexpr int PR = ((4 * G + 11) / 16) * 16 + 4;
+    static constexpr int FC = M / 16, REM = M % 16;                    // full column registers, columns past them
+};
+
+template <int T, bool EXT>
+struct CoupledLds {
+    using C = CoupledShape<T>;
+    double pan[4 * C::PR];             // pivot panel, column by column
+    double psi[C::W], sch[C::W], bco[C::W], g[C::W], dg[C::W];   // per row: see the assembly
+    double yrow[C::W], ycol[C::W];     // Y_e row and column of the block
+    double y[C::W];                    // y of the previous zone; x in the back substitution
+    double pe[EXT ? C::W : 1], pm[EXT ? C::W : 1], bz[EXT ? C::NT : 1];   // pair terms
+};
+
+// What a lane owns: row i = lane of the block (species cell i < NC, Y_e at i = NC), and its cell's offset.
+template <int T>
+struct Owner {
+    int species, k;
+    bool real;
+    size_t cell;
+    __device__ __forceinline__ Owner(int lane, const Shape& sh, long long ray) {
+        constexpr int NT = 4 * T, NC = 8 * T;
+        species = lane < NT ? 0 : 1;
+        k = lane - species * NT;
+        real = lane < NC && k < sh.N;
+        cell = ((size_t)(real ? species : 0) * sh.R + ray) * sh.I * sh.N + (real ? k : 0);
+    }
+};
+
+}  // namespace
+
+// The wavefront's block: row groups in fours as 16 x 16 results, the last G % 4 on their own.
+template <int G, int CN>
+struct WaveBlock {
+    static constexpr int RF = G / 4, RM = G % 4;
+    Vec4 f[RF > 0 ? RF : 1][CN];
+    double r[RM > 0 ? RM : 1][CN];
+    __device__ __forceinline__ double get(int q, int C) const { return q < 4 * RF ? f[q / 4][C][q % 4] : r[q - 4 * RF][C]; }
+    __device__ __forceinline__ void set(int q, int C, double v) {
+        if (q < 4 * RF) f[q / 4][C][q % 4] = v;
+        else r[q - 4 * RF][C] = v;
+    }
+};
+
+// In-place inverse of the wavefront's block by block Gauss-Jordan with diagonal tile pivots.  The four columns
+// of the pivot's panel go to LDS (and are cleared: the update then leaves minus the panel times the pivot's
+// inverse there); every lane reads the pivot tile and its A operands back.  The column register of the coming
+// pivot is updated and published first; the rest of a pivot's update runs on the matrix cores under the
+// inversion of the next pivot's tile.
+template <int G, int CN, int PR>
+__device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane& L, int jc, double* pan, TileGuard& guard) {
+    constexpr int RF = G / 4, RM = G % 4;
+    struct Panel {                                                     // A operands of a pivot's panel
+        double f[RF > 0 ? RF : 1], r[RM > 0 ? RM : 1];
+    };
+    auto publish = [&](int p) {
+        if (L.g == (p & 3)) {
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                pan[L.b * PR + 4 * q + L.a] = S.get(q, p >> 2);
+                S.set(q, p >> 2, 0.0);
+            }
+        }
+        wave_sync();
+    };
+    auto update = [&](int C, const Panel& l, double u, int p) {
+#pragma unroll
+        for (int R = 0; R < RF; ++R) S.f[R][C] = mfma16_neg(l.f[R], u, S.f[R][C]);
+#pragma unroll
+        for (int x = 0; x < RM; ++x)
+            if (4 * RF + x != p) S.r[x][C] = mfma4_neg(l.r[x], u, S.r[x][C]);
+        S.set(p, C, u);
+    };
+    auto next_register = [&](int p) { return (p + 1 < G ? p + 1 : p) >> 2; };
+    publish(0);
+    Panel l_prev{};
+    double u_prev[CN] = {};
+#pragma unroll
+    for (int p = 0; p < G; ++p) {
+        const int C0 = p >> 2;
+        TileEntries e;                                                 // columns of the pivot: rows of its transpose
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double2* v = reinterpret_cast<const double2*>(pan + j * PR + 4 * p);
+            e.v[2 * j] = v[0];
+            e.v[2 * j + 1] = v[1];
+        }
+        Panel l;
+#pragma unroll
+        for (int R = 0; R < RF; ++R) l.f[R] = pan[L.a * PR + 16 * R + jc];
+#pragma unroll
+        for (int x = 0; x < RM; ++x) l.r[x] = pan[L.a * PR + 16 * RF + 4 * x + L.b];
+        wave_sync();
+        __builtin_amdgcn_sched_barrier(0);
+        int rest = 0;
+        if (p > 0) {                                                   // what is left of the previous update
+#pragma unroll
+            for (int C = 0; C < CN; ++C)
+                if (C != next_register(p - 1)) {
+                    update(C, l_prev, u_prev[C], p - 1);
+                    rest += RF + RM;
+                }
+        }
+        const double xa = tile_inverse(e, L, guard);                   // transpose of the inverse: its A operand
+#pragma unroll
+        for (int j = 0; j < rest; ++j) {                                // one product, then a few vector operations
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const double xn = mfma4(xa, L.id, 0.0);
+        double u[CN];
+#pragma unroll
+        for (int C = 0; C < CN; ++C) {
+            u[C] = mfma4(xa, S.get(p, C), 0.0);                         // zero in the panel's own columns
+            guard.see(u[C]);
+        }
+        guard.pin();
+        u[C0] = L.g == (p & 3) ? xn : u[C0];
+        if (C0 < RF) l.f[C0 < RF ? C0 : 0] = L.g == (p & 3) ? 0.0 : l.f[C0 < RF ? C0 : 0];   // the pivot rows stay
+        update(next_register(p), l, u[next_register(p)], p);
+        if (p + 1 < G) publish(p + 1);
+        l_prev = l;
+#pragma unroll
+        for (int C = 0; C < CN; ++C) u_prev[C] = u[C];
+    }
+#pragma unroll
+    for (int C = 0; C < CN; ++C)
+        if (C != next_register(G - 1)) update(C, l_prev, u_prev[C], G - 1);
+}
+
+// EXT: lapse, geometric limiter and boundary, and the pair processes compiled in.
+template <int T, bool EXT>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(EXT || T > 5 ? 1 : 2)))
+void k_ye_factor_wave(YeFactorArgs A) {
+    using X = CoupledShape<T>;
+    constexpr int NT = X::NT, NC = X::NC, M = X::M, G = X::G, Q = X::Q, CN = X::CN;
+    __shared__ CoupledLds<T, EXT> lds[2];
+    __shared__ double sP[NT * NT];                 // P[k][k'] at [k'][k]
+    __shared__ double sG[EXT ? NT * NT : 1];       // pair shape g[k][k'] W_k' / mean W at [k'][k]
+    __shared__ double s_eps[NT];
+    __shared__ double s_C[Q][CN][64];              // the outer half's last factor, for the meeting zone
+    __shared__ double s_y[X::W], s_x[X::W];        // the outer half's y; x of the meeting zone
+    __shared__ int s_bad[2];
+    const int lane = threadIdx.x & 63;
+    const bool half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // the half coming from the outer edge
+    const long long ray = A.ray0 + blockIdx.x;
+    if (A.active && A.active[ray] == 0) return;                            // both wavefronts
+    const Shape& sh = A.sh;
+    const int N = sh.N, I = sh.I, R = sh.R;
+    const bool diff = sh.terms & kDiffusion, emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
+    const bool pair = EXT && A.y.pair_amp != nullptr;
+    for (int j = threadIdx.x; j < NT * NT; j += 128) {
+        const int kp = j / NT, k = j % NT;
+        sP[j] = A.cs->P[k][kp];
+        if (EXT) sG[j] = (pair && k < N && kp < N) ? A.y.pair_g[(size_t)k * N + kp] * A.cs->W[kp] / A.cs->wbar : 0.0;
+    }
+    if (threadIdx.x < NT) s_eps[threadIdx.x] = threadIdx.x < N ? A.cs->eps[threadIdx.x] : 0.0;
+    __syncthreads();
+
+    CoupledLds<T, EXT>& sm = lds[half];
+    const double c = sh.c_dt;
+    const int m = I / 2, delay = half && (I & 1) == 0 ? 1 : 0;         // the outer half has one zone less
+    const int dir = half ? -1 : 1;
+    const double sgn = half ? -1.0 : 1.0;
+
+    const size_t zb = (size_t)ray * I, eb = (size_t)ray * (I + 1);
+    auto clampz = [&](int z) { return min(max(z, 0), I - 1); };
+    auto clampe = [&](int e) { return min(max(e, 0), I); };
+
+    double n_psi, n_ka, n_et, n_ks, z_rhs, z_dk, z_de, z_pe = 0.0;      // as loaded: next zone; this zone
+    auto load_next = [&](const Owner<T>& O, int z) {
+        const size_t ci = O.cell + (size_t)clampz(z) * N;
+        n_psi = A.psi[ci];
+        n_ka = A.f.kappa_a[ci];
+        n_et = A.f.eta[ci];
+        n_ks = A.f.kappa_s[ci];
+    };
+    double Tz = 1.0, amp0 = 0.0, amp1 = 0.0, Y = 0.0, Yn = 0.0, rho = 1.0, gY = 0.0, pamp = 0.0;
+    auto load_zone = [&](const Owner<T>& O, int zz) {
+        const int z = clampz(zz);
+        const size_t ci = O.cell + (size_t)z * N;
+        z_rhs = A.G[ci];
+        z_dk = z_de = 0.0;
+        if (emabs) {
+            z_dk = A.y.dka[ci];
+            z_de = A.y.deta[ci];
+        }
+        if (nes || pair) Tz = A.f.temp[zb + z];
+        if (nes) {
+            amp0 = A.f.nes_amp[zb + z];
+            amp1 = A.f.nes_amp[((size_t)R + ray) * I + z];
+        }
+        Y = A.ye[zb + z];
+        Yn = A.y.ye_n[zb + z];
+        rho = A.y.rho[zb + z];
+        gY = A.GY[zb + z];
+        if (pair) {
+            pamp = A.y.pair_amp[zb + z];
+            z_pe = A.y.pair_eta1[ci];
+        }
+    };
+    // area times dH/dpsi_I at the outer boundary
+    auto outer = [&](double rnu, double psi, double lam) -> double {
+        if (!diff || sh.outer_bc == 0) return 0.0;
+        const double r = A.f.r_edge[eb + I];
+        double area = r * r;
+        if (EXT && A.f.lapse) {
+            const double x = A.f.lapse_edge[eb + I];
+            area /= x * x;
+        }
+        if (EXT && sh.outer_bc == 2) {                                  // ghost zone of eq. a62af
+            const Ghost gh = outer_ghost(A.f.r_edge[eb + I - 1], r, rnu);
+            const EdgeFlux e = edge_flux(psi, gh.ratio * psi, lam, gh.D, sh.psi_floor, sh.limiter,
+                                         sh.limiter == 2 ? limb_factor(r, rnu) : -1.0);
+            return area * (e.dHu + gh.ratio * e.dHv);
+        }
+        return area;                                                   // free streaming: H = psi of the last zone
+    };
+    auto radius_nu = [&](const Owner<T>& O) {
+        return EXT && A.f.r_nu && O.real ? A.f.r_nu[(size_t)O.species * N + O.k] : 1.0;
+    };
+    const int z0 = half ? I - 1 : 0;
+    double psi, sig, lam, tc, to = 0.0;                                 // this zone; trailing edge
+    {
+        const Owner<T> O(lane, sh, ray);
+        load_next(O, z0);
+        psi = n_psi;
+        sig = n_ka + n_et;
+        lam = rcp_cubic(sig + n_ks);
+        tc = half ? outer(radius_nu(O), psi, lam) : 0.0;
+        load_next(O, z0 + dir);
+        load_zone(O, z0);
+    }
+    const int e0 = half ? I - 1 : 1;
+    double r_t = A.f.r_edge[clampe(e0 - dir) + eb], r_l = A.f.r_edge[clampe(e0) + eb],
+           r_b = A.f.r_edge[clampe(e0 + dir) + eb];
+
+    WaveBlock<G, CN> S;
+#pragma unroll
+    for (int q = 0; q < G; ++q)
+#pragma unroll
+        for (int C = 0; C < CN; ++C) S.set(q, C, 0.0);
+    if (lane < X::W) {
+        sm.y[lane] = 0.0;
+        sm.yrow[lane] = sm.ycol[lane] = sm.psi[lane] = sm.sch[lane] = sm.bco[lane] = sm.g[lane] = 0.0;
+        sm.dg[lane] = 1.0;
+    }
+    wave_sync();
+    TileGuard guard(A.growth_limit);
+    const size_t SZ = (size_t)M * M + 1;                               // slot of a zone (M is odd)
+    double* ws = A.ws + (size_t)blockIdx.x * I * SZ;
+    typedef double V2 __attribute__((ext_vector_type(2)));
+
+    // C and y of the zone that step n - 1 finished.  Stored in the middle of the next step, not at the end of
+    // their own: loads and stores complete in order, so the wait for the next zone's loads would otherwise
+    // include the stores just issued.
+    auto store = [&](int n, int ln) {
+        const int jc = ln & 15, a = ln >> 4;
+        double* slot = ws + (size_t)(half ? I - 1 - (n - 1 - delay) : n - 1) * SZ;
+#pragma unroll
+        for (int C = 0; C < X::FC; ++C)
+#pragma unroll
+            for (int q = 0; q < Q; q += 2)
+                nt_store(reinterpret_cast<V2*>(slot) + (C * T + q / 2) * 64 + ln, V2{S.get(q, C), S.get(q + 1, C)});
+        if (X::REM && jc < X::REM) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                nt_store(slot + 64 * Q * X::FC + 4 * X::REM * q + X::REM * a + jc, S.get(q, X::FC < CN ? X::FC : 0));
+        }
+        if (ln < M) nt_store(slot + (size_t)NC * M + ln, sm.y[ln]);
+    };
+
+    for (int n = delay; n <= m; ++n) {
+        const bool mid = n == m;
+        if (mid) {
+            if (half) {                                                // hand the last factor to the inner half
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+#pragma unroll
+                    for (int C = 0; C < CN; ++C) s_C[q][C][lane] = S.get(q, C);
+                if (lane < X::W) s_y[lane] = sm.y[lane];
+                if (n > delay) store(n, lane);
+                const bool bad = guard.bad != 0ull;
+                if (lane == 0) s_bad[1] = bad;
+            }
+            __syncthreads();
+            if (half) break;
+        }
+        // what derives from the lane id is formed again each step instead of being held across it
+        const int ln = opaque_lane(), jc = ln & 15;
+        const TileLane L(ln);
+        const Owner<T> O(ln, sh, ray);
+        const bool real = O.real;
+        const double rnu = radius_nu(O);
+        const double qs = O.species == 0 ? 1.0 : -1.0;                 // nu_e carries +1, anti-nu_e -1
+        const double Wk = real ? A.cs->W[O.k] : 0.0;
+        const int zc = half ? I - 1 - (n - delay) : n, zn = zc + dir;
+        const bool has_next = zn >= 0 && zn < I;
+        const ExpCoef coef = exp_coef();
+        // ---- owned rows: transport coefficients, Y_e terms, right-hand side
+        double alz = 1.0, iVc = rcp_cubic(sgn * shell_volume(r_t, r_l)), sA = sgn * r_l * r_l;
+        if (EXT && A.f.lapse) {
+            alz = A.f.lapse[zb + zc];
+            iVc *= alz * alz * alz;
+            const double x = A.f.lapse_edge[eb + clampe(half ? zc : zc + 1)];
+            sA /= x * x;
+        }
+        const double cV = c * iVc;
+        const double n_sig = n_ka + n_et, n_lam = rcp_cubic(n_sig + n_ks);
+        double ec = 0.0, eo = 0.0;
+        if (diff) {
+            if (has_next) {
+                const double Dl = fabs(0.5 * (r_l + r_b) - 0.5 * (r_t + r_l));
+                const double limb = (EXT && sh.limiter == 2) ? limb_factor(r_l, rnu) : -1.0;
+                const EdgeFlux e = edge_flux(half ? n_psi : psi, half ? psi : n_psi, sqrt(lam * n_lam), Dl, sh.psi_floor,
+                                             sh.limiter, limb);
+                ec = sA * (half ? e.dHv : e.dHu);
+                eo = sA * (half ? e.dHu : e.dHv);
+            } else if (!half) {
+                ec = outer(rnu, psi, lam);
+            }
+        }
+        const double dy = Y - Yn, dk = alz * z_dk, de = alz * z_de;
+        const double zt = kFourPiOverHc3 * kBaryonMassG / (rho * alz * alz * alz);
+        double diag = fma(cV, ec + tc, 1.0), yrow = 0.0, ycol = 0.0, ysum = 0.0;
+        if (emabs) {
+            diag += c * sig + c * dy * (dk + de);
+            ycol = c * (dk * psi - de * (1.0 - psi));
+            yrow = -qs * c * zt * Wk * (sig + dy * (dk + de));
+            ysum = real ? qs * Wk * (de * (1.0 - psi) - dk * psi) : 0.0;
+            ysum = wave_total(ysum);
+        }
+        if (ln <= NC) {
+            const double sch = real ? cV * to : 0.0, bco = real ? cV * eo : 0.0;
+            double g = real ? A.rhs_sign * z_rhs : (ln == NC ? A.rhs_sign * gY : 0.0);
+            g = fma(-sch, sm.y[ln], g);
+            if (mid) g = fma(-bco, s_y[ln], g);
+            sm.psi[ln] = real ? psi : 0.0;
+            sm.sch[ln] = sch;
+            sm.bco[ln] = bco;
+            sm.g[ln] = g;
+            sm.dg[ln] = real ? diag : (ln == NC && emabs ? fma(c * zt, ysum, 1.0) : 1.0);
+            sm.yrow[ln] = real ? yrow : 0.0;
+            sm.ycol[ln] = real ? ycol : 0.0;
+            if (EXT && pair) {
+                const double Rz = 0.5 * (A.f.r_edge[eb + zc] + A.f.r_edge[eb + zc + 1]);
+                sm.pe[ln] = real ? z_pe : 0.0;
+                sm.pm[ln] = real ? pair_limb_cosine(rnu / Rz) : 0.0;
+                if (ln < NT) sm.bz[ln] = real ? exp_nonpos(-s_eps[ln] * rcp_cubic(Tz), coef) : 0.0;
+            }
+        }
+        tc = -eo;                                                      // the next zone becomes the current one
+        to = -ec;
+        psi = n_psi;
+        sig = n_sig;
+        lam = n_lam;
+        wave_sync();
+        const double iT = rcp_cubic(Tz), a0 = amp0, a1 = amp1, pa = pamp;
+        if (n > delay) store(n, ln);
+        load_next(O, zn + dir);
+        load_zone(O, zn);
+        r_t = r_l;
+        r_l = r_b;
+        r_b = A.f.r_edge[eb + clampe((half ? zc : zc + 1) + 2 * dir)];
+        __builtin_amdgcn_sched_barrier(0);
+
+        // ---- the block: Schur term of the previous factor (both neighbours' in the meeting zone) ...
+#pragma unroll
+        for (int C = 0; C < CN; ++C) {
+            const double sc = -sm.sch[16 * C + jc], bc = sm.bco[16 * C + jc];
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                S.set(q, C, S.get(q, C) * sc);
+                if (mid && q < Q) S.set(q, C, fma(-s_C[q][C][ln], bc, S.get(q, C)));
+            }
+        }
+        // ... scattering and pair terms, per column k of the stored transpose and row k' = 4u + a ...
+#pragma unroll
+        for (int C = 0; C < CN; ++C) {
+            const bool has0 = 4 * C < T, has1 = 4 * C + 3 >= T && 4 * C < 2 * T;   // compile-time
+            const int cg = 4 * C + L.g;                                 // column group: species, tile
+            const int sc = cg < T ? 0 : 1, tt = cg - sc * T;
+            const bool in = cg < 2 * T;
+            const int k = in ? 4 * tt + L.b : 0;
+            const double m0 = cg < T ? 1.0 : 0.0, m1 = (cg >= T && in) ? 1.0 : 0.0;
+            double dgv = sm.dg[16 * C + jc];
+            const double pk = sm.psi[16 * C + jc];
+            if (nes && (has0 || has1)) {
+                const double camp = in ? c * (sc ? a1 : a0) : 0.0;
+                const double wk = -camp * pk, w1 = -camp - wk;          // weights of psi_k and 1 - psi_k
+                const double ek = s_eps[k];
+                double acc = 0.0;
+#pragma unroll
+                for (int u = 0; u < T; ++u) {
+                    const int kp = 4 * u + L.a;
+                    const double P = sP[kp * NT + k];
+                    const double PM = P * exp_nonpos(-fabs(s_eps[kp] - ek) * iT, coef);
+                    const double pv = sm.psi[(sc ? NT : 0) + kp];
+                    const bool up = kp > k;
+                    const double e = fma(up ? wk : w1, PM, (up ? w1 : wk) * P);
+                    if (has0) S.set(u, C, fma(m0, e, S.get(u, C)));
+                    if (has1) S.set(T + u, C, fma(m1, e, S.get(T + u, C)));
+                    const double pq = 1.0 - pv;
+                    acc = fma(up ? pv : pq, P, acc);
+                    acc = fma(up ? pq : pv, PM, acc);
+                }
+                dgv = fma(camp, mfma4(1.0, acc, 0.0), dgv);
+            }
+            if (EXT && pair && (has0 || has1)) {
+                const int self = in ? 16 * C + jc : 0;
+                const double bk = sm.bz[k], ek = sm.pe[self], mk = sm.pm[self];
+                const double w = in ? pa : 0.0;
+                double acc = 0.0;
+#pragma unroll
+                for (int u = 0; u < T; ++u) {
+                    const int kp = 4 * u + L.a, o = (sc ? 0 : NT) + kp;
+                    const double qa = w * sG[kp * NT + k];
+                    const double qp = qa * bk * sm.bz[kp];
+                    const double qx = qa * pair_chi(ek, sm.pe[o], mk, sm.pm[o]);
+                    const double pv = sm.psi[o];
+                    const double e = c * fma(1.0 - pk, qp, pk * qx);
+                    if (has0) S.set(T + u, C, fma(m0, e, S.get(T + u, C)));
+                    if (has1) S.set(u, C, fma(m1, e, S.get(u, C)));
+                    acc += fma(qp, 1.0 - pv, qx * pv);
+                }
+                dgv = fma(c, mfma4(1.0, acc, 0.0), dgv);
+            }
+            // ... the Y_e column and row, and the diagonal
+            if (emabs) {
+                const double isY = L.a == 0 ? 1.0 : 0.0;
+                S.set(2 * T, C, fma(isY, sm.ycol[16 * C + jc], S.get(2 * T, C)));
+            }
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (4 * C + x < G) {
+                    const double on = (L.g == x && L.a == L.b) ? 1.0 : 0.0;
+                    S.set(4 * C + x, C, fma(on, dgv, S.get(4 * C + x, C)));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (emabs) {
+            const double isY = (L.g == ((2 * T) & 3) && L.b == 0) ? 1.0 : 0.0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) S.set(q, (2 * T) >> 2, fma(isY, sm.yrow[4 * q + L.a], S.get(q, (2 * T) >> 2)));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+
+        // ---- Ahat^-1, y = Ahat^-1 g, C = Ahat^-1 diag(b)
+        wave_invert<G, CN, X::PR>(S, L, jc, sm.pan, guard);
+        double yc[CN];
+#pragma unroll
+        for (int C = 0; C < CN; ++C) yc[C] = 0.0;
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const double g = sm.g[4 * q + L.a];
+#pragma unroll
+            for (int C = 0; C < CN; ++C) yc[C] = fma(S.get(q, C), g, yc[C]);
+        }
+#pragma unroll
+        for (int C = 0; C < CN; ++C) yc[C] = mfma4(1.0, yc[C], 0.0);
+        if (L.a == 0) {
+#pragma unroll
+            for (int C = 0; C < CN; ++C) sm.y[16 * C + jc] = yc[C];
+        }
+        if (!mid) {
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const double b = q < Q ? sm.bco[4 * q + L.a] : 0.0;     // Y_e has no neighbours
+#pragma unroll
+                for (int C = 0; C < CN; ++C) S.set(q, C, S.get(q, C) * b);
+            }
+        }
+        wave_sync();
+    }
+    if (!half) {
+        const bool bad = guard.bad != 0ull;
+        if (lane == 0) s_bad[0] = bad;
+        if (lane < X::W) s_x[lane] = sm.y[lane];
+    }
+    __syncthreads();
+    // a ray whose growth guard tripped is left untouched and marked for the partial-pivoting re-run
+    const bool bad = s_bad[0] || s_bad[1];
+    if (A.redo && threadIdx.x == 0) A.redo[ray] = bad ? 1 : 0;
+    if (bad) return;
+
+    // ---- back substitution outwards from the meeting zone
+    const int lb = opaque_lane(), jc = lb & 15;                         // jc: column within a register
+    const TileLane L(lb);
+    const Owner<T> O(lb, sh, ray);
+    auto put = [&](int z, double d) {
+        if (O.real) {
+            const size_t ci = O.cell + (size_t)z * N;
+            A.psi_out[ci] += d;
+            A.dx[ci] = d;
+        } else if (lane == NC) {
+            A.ye_out[zb + z] += d;
+            A.dY[zb + z] = d;
+        }
+    };
+    if (lane < X::W) sm.y[lane] = s_x[lane];
+    if (!half) put(m, lane < X::W ? s_x[lane] : 0.0);
+    wave_sync();
+    double Cb[2][Q][CN], yb[2][CN];                                     // y in column form
+    auto fetch = [&](int n, double (&c_)[Q][CN], double (&y_)[CN]) {
+        const int z = half ? I - 1 - (n - delay) : n;
+        const double* slot = ws + (size_t)z * SZ;
+#pragma unroll
+        for (int C = 0; C < X::FC; ++C)
+#pragma unroll
+            for (int q = 0; q < Q; q += 2) {
+                const V2 v = nt_load(reinterpret_cast<const V2*>(slot) + (C * T + q / 2) * 64 + lane);
+                c_[q][C] = v.x;
+                c_[q + 1][C] = v.y;
+            }
+        if constexpr (X::REM > 0) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                c_[q][X::FC] = jc < X::REM ? nt_load(slot + 64 * Q * X::FC + 4 * X::REM * q + X::REM * L.a + jc) : 0.0;
+        }
+#pragma unroll
+        for (int C = 0; C < CN; ++C) y_[C] = 16 * C + jc < M ? nt_load(slot + (size_t)NC * M + 16 * C + jc) : 0.0;
+    };
+    auto step = [&](int n, const double (&c_)[Q][CN], const double (&y_)[CN]) {
+        double acc[CN];
+#pragma unroll
+        for (int C = 0; C < CN; ++C) acc[C] = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const double x = sm.y[4 * q + L.a];
+#pragma unroll
+            for (int C = 0; C < (X::REM ? X::FC + 1 : X::FC); ++C) acc[C] = fma(c_[q][C], x, acc[C]);
+        }
+#pragma unroll
+        for (int C = 0; C < CN; ++C) acc[C] = y_[C] - mfma4(1.0, acc[C], 0.0);
+        wave_sync();
+        if (L.a == 0) {
+#pragma unroll
+            for (int C = 0; C < CN; ++C) sm.y[16 * C + jc] = acc[C];
+        }
+        wave_sync();
+        const double x = lane < X::W ? sm.y[lane] : 0.0;                 // owner form
+        put(half ? I - 1 - (n - delay) : n, x);
+    };
+    int n = m - 1;
+    if (n >= delay) fetch(n, Cb[0], yb[0]);
+    for (; n >= delay; n -= 2) {
+        if (n - 1 >= delay) fetch(n - 1, Cb[1], yb[1]);
+        step(n, Cb[0], yb[0]);
+        if (n - 1 < delay) break;
+        if (n - 2 >= delay) fetch(n - 2, Cb[0], yb[0]);
+        step(n - 1, Cb[1], yb[1]);
+    }
+    if (threadIdx.x == 0) {
+        A.iters[ray] += 1;
+        A.pending[ray] = 1;                                            // trial psi + delta awaits the line search
+        A.alpha[ray] = 1.0;
+    }
+}
+
+template <int T>
+static void launch_wave_t(const YeFactorArgs& a, bool ext, hipStream_t st) {
+    const dim3 grid((unsigned)a.nray), block(128);
+    if (ext) hipLaunchKernelGGL((k_ye_factor_wave<T, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((k_ye_factor_wave<T, false>), grid, block, 0, st, a);
+}
+
+hipError_t launch_ye_factor_wave(const YeFactorArgs& a, hipStream_t st) {
+    if (!a.redo) return hipErrorInvalidValue;
+    const bool ext = a.sh.limiter == 2 || a.sh.outer_bc == 2 || a.y.pair_amp || a.f.lapse;
+    switch (padded_groups(a.sh.N)) {
+        case 4: launch_wave_t<1>(a, ext, st); break;
+        case 8: launch_wave_t<2>(a, ext, st); break;
+        case 12: launch_wave_t<3>(a, ext, st); break;
+        case 16: launch_wave_t<4>(a, ext, st); break;
+        case 20: launch_wave_t<5>(a, ext, st); break;
+        case 24: launch_wave_t<6>(a, ext, st); break;
+        case 28: launch_wave_t<7>(a, ext, st); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace tmk

@@ -24,6 +24,13 @@ __device__ __forceinline__ double mfma4_neg(double a, double b, double c) {
     return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 1);
 }
 
+// c - a b for one 16 x 16 matrix: A operand (row j, column a) and B operand (row a, column j) in lane 16 a + j,
+// result row 4 r + a, column j in element r.
+typedef double Vec4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Vec4 mfma16_neg(double a, double b, Vec4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
+}
+
 // 1/x from the hardware estimate (about 2^-22) and one cubic step: r + r (e + e^2), e = 1 - x r.
 __device__ __forceinline__ double rcp_cubic(double x) {
     const double r = __builtin_amdgcn_rcp(x);
@@ -38,10 +45,13 @@ __constant__ const double kExpCoef[16] = {
     1.4426950408889634, -0x1.62e42fee00000p-1, -0x1.a39ef35793c76p-33,          // 1/ln 2, ln 2 to 32 bits, the rest of ln 2
     1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0,
     1.0 / 5040.0, 1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0, 0.5, 1.0};
-__device__ __forceinline__ double exp_nonpos(double x) {
-    typedef const __attribute__((address_space(4))) double* cptr;
-    cptr c = (cptr)kExpCoef;
+typedef const __attribute__((address_space(4))) double* ExpCoef;
+__device__ __forceinline__ ExpCoef exp_coef() {
+    ExpCoef c = (ExpCoef)kExpCoef;
     asm volatile("" : "+s"(c));
+    return c;
+}
+__device__ __forceinline__ double exp_nonpos(double x, ExpCoef c) {
     x = x > -800.0 ? x : -800.0;                   // the result is 0 from -746 on
     const double n = __builtin_rint(x * c[0]);
     const double r = fma(n, c[2], fma(n, c[1], x));
@@ -65,6 +75,14 @@ __device__ __forceinline__ double dpp_quad(double v, int lane_of_quad) {
 
 constexpr int kPivStride = 18;                    // doubles per block in the pivot exchange (16-byte aligned)
 
+// The lane id through an opaque instruction: what is derived from it is formed again where it is used
+// instead of being held in registers across the zone loop.
+__device__ __forceinline__ int opaque_lane() {
+    int ln;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+    return ln;
+}
+
 // Lane constants of the tile layout.
 struct TileLane {
     int a, g, b;
@@ -79,25 +97,33 @@ struct TileLane {
     }
 };
 
-// Growth and zero-pivot record of an elimination: the largest multiplier magnitude (its upper word, which
-// orders magnitudes to about 2^-20) and whether some 2 x 2 pivot was zero or not finite.
+// Record of an elimination: whether some multiplier exceeded the growth limit or was NaN (a zero, infinite or
+// NaN determinant of a 2 x 2 pivot makes one).  One compare each, collected in a scalar mask.
 struct TileGuard {
-    uint32_t grow = 0;
-    bool zero = false;
-    __device__ __forceinline__ void see(double x) { grow = max(grow, abs_key_bits(x)); }
-    __device__ __forceinline__ bool tripped(double limit) const { return zero || grow > abs_key_bits(limit); }
+    double limit;
+    unsigned long long bad = 0;        // one bit per lane
+    __device__ __forceinline__ explicit TileGuard(double l) : limit(l) {}
+    __device__ __forceinline__ void see(double x) { bad |= __ballot(!(fabs(x) <= limit)); }
+    // keeps the record current: deferred by the compiler, it would hold every step's multipliers
+    __device__ __forceinline__ void pin() { asm volatile("" : "+s"(bad)); }
 };
 
-// Inverse of a tile (natural in, natural out).  The sixteen entries are gathered through LDS and every lane
-// solves for its own column with 2 x 2 block pivots (two reciprocals in sequence instead of four), then
-// keeps its row.  The pivots are diagonal: no exchange between the two halves of the tile.
-__device__ __forceinline__ double tile_inverse(double s, const TileLane& L, double* piv, TileGuard& G) {
-    double* q = piv + L.g * kPivStride;
-    q[4 * L.a + L.b] = s;
-    wave_sync();
-    const double2* v = reinterpret_cast<const double2*>(q);
-    const double2 r0 = v[0], r0b = v[1], r1 = v[2], r1b = v[3], r2 = v[4], r2b = v[5], r3 = v[6], r3b = v[7];
-    wave_sync();
+// The sixteen entries of a tile in row order, two per element.
+struct TileEntries {
+    double2 v[8];
+    __device__ __forceinline__ void read(const double* q) {
+        const double2* p = reinterpret_cast<const double2*>(q);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = p[j];
+    }
+};
+
+// Inverse of a tile in natural order from its entries: every lane solves for its own column with 2 x 2 block
+// pivots (two reciprocals in sequence instead of four) and keeps its row.  The pivots are diagonal: no
+// exchange between the two halves of the tile.
+__device__ __forceinline__ double tile_inverse(const TileEntries& e, const TileLane& L, TileGuard& G) {
+    const double2 r0 = e.v[0], r0b = e.v[1], r1 = e.v[2], r1b = e.v[3], r2 = e.v[4], r2b = e.v[5], r3 = e.v[6],
+                  r3b = e.v[7];
     const double d1 = fma(r0.x, r1.y, -(r0.y * r1.x));
     const double i1 = rcp_cubic(d1);
     const double e00 = r1.y * i1, e01 = -(r0.y * i1), e10 = -(r1.x * i1), e11 = r0.x * i1;
@@ -107,17 +133,14 @@ __device__ __forceinline__ double tile_inverse(double s, const TileLane& L, doub
     const double s10 = fma(-g10, r0b.x, fma(-g11, r1b.x, r3b.x)), s11 = fma(-g10, r0b.y, fma(-g11, r1b.y, r3b.y));
     const double d2 = fma(s00, s11, -(s01 * s10));
     const double i2 = rcp_cubic(d2);
-    // a zero, infinite or NaN determinant leaves a reciprocal that is not finite and non-zero
-    G.zero |= !(fabs(i1) > 0.0 && fabs(i1) < INFINITY && fabs(i2) > 0.0 && fabs(i2) < INFINITY);
-    // multipliers of this tile: those between the rows of the 2 x 2 pivots and those of the lower half
-    G.see(r0.y * e00);
-    G.see(r1.x * e00);
+    // multipliers of the lower 2 x 2 half (those between tiles are seen by the caller); a first determinant
+    // that is zero or not finite makes them NaN, a second one makes its reciprocal NaN
     G.see(g00);
     G.see(g01);
     G.see(g10);
     G.see(g11);
-    G.see(s01 * (s11 * i2));
-    G.see(s10 * (s11 * i2));
+    G.bad |= __ballot(!(i2 == i2));
+    G.pin();
     const double t0 = fma(-g00, L.u0, fma(-g01, L.u1, L.u2)), t1 = fma(-g10, L.u0, fma(-g11, L.u1, L.u3));
     const double x2 = fma(s11, t0, -(s01 * t1)) * i2, x3 = fma(s00, t1, -(s10 * t0)) * i2;
     const double w0 = fma(-r0b.x, x2, fma(-r0b.y, x3, L.u0)), w1 = fma(-r1b.x, x2, fma(-r1b.y, x3, L.u1));
@@ -128,37 +151,61 @@ __device__ __forceinline__ double tile_inverse(double s, const TileLane& L, doub
 
 // In-place inverse of a block of T x T tiles by block Gauss-Jordan with diagonal tile pivots.  For the
 // M-matrices of this method (off-diagonals <= 0, columns or rows dominant) no step subtracts like-signed
-// terms except on the diagonal, so entries far below the block's norm keep their relative accuracy.
+// terms except on the diagonal, so entries far below the block's norm keep their relative accuracy.  The coming
+// pivot's tile is updated first and gathered through LDS (transposed, so that its inverse comes out as an A
+// operand); the rest of a pivot's update runs on the matrix cores under the inversion of the next one.
 template <int T>
 __device__ __forceinline__ void tile_invert(double (&S)[T][T], const TileLane& L, double* piv, TileGuard& G) {
-#pragma unroll
-    for (int p = 0; p < T; ++p) {
-        double ct[T];
-#pragma unroll
-        for (int i = 0; i < T; ++i)
-            if (i != p) ct[i] = mfma4(S[i][p], L.id, 0.0);            // A operands of the pivot column
-        const double xn = tile_inverse(S[p][p], L, piv, G);
-        const double xa = mfma4(xn, L.id, 0.0);
-#pragma unroll
-        for (int jj = 1; jj < T; ++jj) {
-            const int j = (p + jj) % T;                                // the next pivot's column first
-            S[p][j] = mfma4(xa, S[p][j], 0.0);
-            G.see(S[p][j]);
-        }
+    double* q = piv + L.g * kPivStride;
+    double ct[T], xn = 0.0;
+    auto rest = [&](int p) {                                           // all of pivot p's update but the next pivot
 #pragma unroll
         for (int ii = 1; ii < T; ++ii) {
             const int i = (p + ii) % T;
 #pragma unroll
             for (int jj = 1; jj < T; ++jj) {
                 const int j = (p + jj) % T;
-                S[i][j] = mfma4_neg(ct[i], S[p][j], S[i][j]);
+                if (ii > 1 || jj > 1 || p == T - 1) S[i][j] = mfma4_neg(ct[i], S[p][j], S[i][j]);
             }
             S[i][p] = mfma4_neg(ct[i], xn, 0.0);
         }
         S[p][p] = xn;
-        asm volatile("" : "+v"(G.grow));      // keeps the record current: deferred, it would hold every step's multipliers
+    };
+    q[4 * L.b + L.a] = S[0][0];
+    wave_sync();
+#pragma unroll
+    for (int p = 0; p < T; ++p) {
+        TileEntries e;
+        e.read(q);
+        wave_sync();
         __builtin_amdgcn_sched_barrier(0);
+        if (p > 0) rest(p - 1);
+        const double xa = tile_inverse(e, L, G);
+        if (p > 0) {
+#pragma unroll
+            for (int j = 0; j < T * (T - 1) - 1; ++j) {                 // one product, then a few vector operations
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        xn = mfma4(xa, L.id, 0.0);
+#pragma unroll
+        for (int ii = 1; ii < T; ++ii) ct[(p + ii) % T] = mfma4(S[(p + ii) % T][p], L.id, 0.0);   // A operands of the column
+#pragma unroll
+        for (int jj = 1; jj < T; ++jj) {
+            const int j = (p + jj) % T;
+            S[p][j] = mfma4(xa, S[p][j], 0.0);
+            G.see(S[p][j]);
+        }
+        G.pin();
+        if (p + 1 < T) {
+            S[p + 1][p + 1] = mfma4_neg(ct[p + 1], S[p][p + 1], S[p + 1][p + 1]);
+            q[4 * L.b + L.a] = S[p + 1][p + 1];
+            wave_sync();
+        }
     }
+    rest(T - 1);
 }
 
 // Owner form of a row-form vector (element 4b + a, and 16 + 4b + a).

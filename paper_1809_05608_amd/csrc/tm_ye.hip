@@ -19,10 +19,8 @@
 //                     as a max over the wavefront, pivot row read from the pivot lane into scalar
 //                     registers) produces
 //                     C_i = Ahat_i^{-1} diag(bp_i) and y_i; the backward sweep x_i = y_i - C_i x_{i+1}
-//                     applies the Newton update.  The default instance (TILE) eliminates with diagonal
-//                     pivots instead, the block spread over 8 x 8 lane tiles, so each step moves 2 T
-//                     values per lane through LDS instead of M + 1 broadcasts; a ray that trips its growth
-//                     guard is left untouched and re-run by the partial-pivoting instance.
+//                     applies the Newton update.  It runs the rays that the diagonal-pivot elimination
+//                     (k_ye_factor_wave, tm_factor_w.hip) leaves untouched because its growth guard tripped.
 //   k_ye_backtrack    line-search move-back of rejected trials.
 //   k_ye_temperature  one thread per zone: energy-weighted collision sources of every species, the
 //                     matter energy change and the new temperature.
@@ -203,11 +201,6 @@ struct alignas(16) YeLds {
     double ys[2 * NT];         // species terms of dG_Y/dY_e
     double fix[MT][MT + 1];    // row-ownership fix-up after pivoting; the rows between zones
     int plane[MT];             // pivot lane of each elimination step
-    // tiled elimination: pivot row (entries, then g) and pivot column of each step, double-buffered
-    double urow[2][8 * ((MT + 8) / 8)];
-    double ucol[2][8 * ((MT + 8) / 8)];
-    double bpv[MT];            // B coefficient of every row
-    double pivs[MT];           // pivot of every step
 };
 
 template <int NT>
@@ -255,100 +248,9 @@ __device__ __forceinline__ void load_slot(const double* slot, int lane, bool ok,
 template <int NT>
 constexpr int ye_waves_per_eu() { return NT <= 20 ? 2 : 1; }
 
-// In-place Gauss-Jordan on [Ahat | diag(bp) | g] with diagonal pivots, the block and g spread over the
-// wavefront as 8 x 8 tiles of T x T entries (T = ceil((MT + 1) / 8), g being column MT): lane 8 a + b holds
-// rows T a .. T a + T - 1 and columns T b .. T b + T - 1.  Step cc needs, in each lane, the pivot row's
-// entries of its columns and the pivot column's entries of its rows: the lanes holding them put them in
-// LDS (T values per lane, double-buffered between steps) and every lane reads its 2 T values back,
-// instead of all M + 1 values of the pivot row.  Column cc becomes column cc of C = Ahat^-1 diag(bp) as
-// in the row-per-lane elimination; each row is divided by its pivot at the end.  Reads the rows and g
-// from L.fix, the B coefficients from L.bpv; writes C and y back to L.fix in natural order.  bad is set
-// for a multiplier above limit (growth guard) or a zero or non-finite pivot.
-template <int MT, typename Lds>
-__device__ __forceinline__ void tile_eliminate(Lds& L, int lane, double limit, bool& bad) {
-    constexpr int T = (MT + 8) / 8;
-    // the lane id through an opaque copy: the lane masks of the steps are then formed per zone instead of
-    // being hoisted out of the zone loop into scalar registers held across the row assembly
-    int lo = lane;
-    asm volatile("" : "+v"(lo));
-    const int ta = lo >> 3, tb = lo & 7;
-    // growth guard: at every step each lane checks one multiplier, entry T ta + (tb mod T) of the pivot
-    // column, so the eight lanes of a tile row cover its T rows and the wavefront covers the column
-    const int gs = T * ta + tb % T;
-    double t[T][T];
-    double gmax = 0.0;
-#pragma unroll
-    for (int tr = 0; tr < T; ++tr) {
-        const int r = T * ta + tr;
-#pragma unroll
-        for (int tc = 0; tc < T; ++tc) {
-            const int c = T * tb + tc;
-            const bool in = r < MT && c <= MT;
-            t[tr][tc] = in ? L.fix[in ? r : 0][in ? c : 0] : ((r == c && c != MT) ? 1.0 : 0.0);   // padding: identity
-        }
-    }
-#pragma unroll
-    for (int cc = 0; cc < MT; ++cc) {
-        const int ap = cc / T, rp = cc % T;            // tile row and column of the pivot: lane 9 ap, (rp, rp)
-        double* const ur = L.urow[cc & 1];
-        double* const uc = L.ucol[cc & 1];
-        if (ta == ap) {
-#pragma unroll
-            for (int tc = 0; tc < T; ++tc) ur[T * tb + tc] = t[rp][tc];
-        }
-        if (tb == ap) {                                // the pivot itself goes in as 0: its row's multiplier
-#pragma unroll
-            for (int tr = 0; tr < T; ++tr) uc[T * ta + tr] = (tr == rp && ta == ap) ? 0.0 : t[tr][rp];
-        }
-        wave_sync();
-        const double piv = ur[cc], bpiv = L.bpv[cc];
-        const double npinv = -drcp(piv);
-        if (lane == 0) L.pivs[cc] = piv;
-        double u[T], nf[T];                            // nf: minus the multipliers
-#pragma unroll
-        for (int tc = 0; tc < T; ++tc) u[tc] = ur[T * tb + tc];
-#pragma unroll
-        for (int tr = 0; tr < T; ++tr) nf[tr] = uc[T * ta + tr] * npinv;   // 0 for the pivot row itself
-        gmax = fmax(gmax, fabs(uc[gs] * npinv));
-#pragma unroll
-        for (int tr = 0; tr < T; ++tr)
-#pragma unroll
-            for (int tc = 0; tc < T; ++tc) t[tr][tc] = fma(nf[tr], u[tc], t[tr][tc]);
-        if (tb == ap) {                                // column cc: -f bp_cc, and bp_cc in the pivot row
-#pragma unroll
-            for (int tr = 0; tr < T; ++tr) t[tr][rp] = (tr == rp && ta == ap) ? bpiv : nf[tr] * bpiv;
-        }
-        // every entry is materialised at the end of its step: left alone, the compiler sinks each update to
-        // the entry's next use and holds every earlier step's multipliers and pivot-row values live
-#pragma unroll
-        for (int tr = 0; tr < T; ++tr)
-#pragma unroll
-            for (int tc = 0; tc < T; ++tc) asm volatile("" : "+v"(t[tr][tc]));
-        asm volatile("" : "+v"(gmax));
-    }
-    bad |= !(gmax <= limit);
-    wave_sync();                                       // pivs[] is read by other lanes
-#pragma unroll
-    for (int tr = 0; tr < T; ++tr) {
-        const int r = T * ta + tr;
-        if (r >= MT) continue;
-        const double pv = L.pivs[r];
-        bad |= !(fabs(pv) > 0.0) || !isfinite(pv);
-        const double ip = drcp(pv);
-#pragma unroll
-        for (int tc = 0; tc < T; ++tc) {
-            const int c = T * tb + tc;
-            if (c <= MT) L.fix[r][c] = t[tr][tc] * ip;
-        }
-    }
-    wave_sync();
-}
-
 // EXT: the geometric limiter and outer boundary, the pair processes and the lapse compiled in (instantiated
 // separately, at one wave per SIMD, and launched only for problems that ask for any of them).
-// TILE: the elimination with diagonal pivots on 8 x 8 lane tiles (below) instead of partial pivoting
-// with one row per lane.
-template <int NT, int WEU, bool EXT, bool TILE>
+template <int NT, int WEU, bool EXT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WEU))) void k_ye_factor(YeFactorArgs A) {
     constexpr int MT = 2 * NT + 1;              // rows of a coupled block (<= 57)
     constexpr int NC = 2 * NT;                  // columns of C that can be non-zero (Y_e has bp = 0)
@@ -365,7 +267,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WEU))) v
     if (rb >= A.nray) return;                                          // whole wave (no block barrier follows)
     const long long ray = A.ray0 + rb;
     if (A.active && A.active[ray] == 0) return;
-    if (!TILE && A.redo && A.redo[ray] == 0) return;                   // the re-run takes marked rays only
+    if (A.redo && A.redo[ray] == 0) return;                            // the re-run takes marked rays only
 
     YeLds<NT>& L = lds_all[wave];
     const Shape& sh = A.sh;
@@ -586,14 +488,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WEU))) v
         if (real) g = fma(-bm, ycar, A.rhs_sign * rhs[(size_t)i * N + kk]);
         else if (isY) g = A.rhs_sign * A.GY[zb + i];
         const double bcoef = bp;
-        if constexpr (TILE) {
-            if (is_row) {
-                frow[MT] = g;                          // y_{i-1} was consumed above
-                L.bpv[kr] = bcoef;
-            }
-            wave_sync();
-            tile_eliminate<MT>(L, lane, A.growth_limit, zp);
-        } else {
         // ---- (2) elimination in registers
         double a[MT];
 #pragma unroll
@@ -646,20 +540,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WEU))) v
             dst[MT] = g * ip;
         }
         wave_sync();
-        }
 
         psi_c = psi_n1;
         sig_c = sig_n1;
         lam_c = lam_n1;
         dHu_lo = dHu_hi;
         dHv_lo = dHv_hi;
-    }
-    if constexpr (TILE) {
-        // growth guard: a ray with a multiplier above the limit or a zero pivot is left untouched and
-        // marked for the partial-pivoting re-run
-        const bool bad = __ballot(zp) != 0ull;
-        if (lane == 0 && A.redo) A.redo[ray] = bad ? 1 : 0;
-        if (bad) return;
     }
     if (is_row) {                                      // C_{I-1}, y_{I-1}
         store_slot<NC, MT>(ws + (size_t)(I - 1) * SZ, lane, frow, frow[MT]);
@@ -877,27 +763,17 @@ hipError_t launch_ye_factor(const YeFactorArgs& a, hipStream_t st) {
     TM_YE_DISPATCH(padded_groups(a.sh.N),
                    constexpr int WPB = ye_waves_per_block<NT>();
                    const long long blocks = (a.nray + WPB - 1) / WPB;
-                   if (!ye_tiled_applies(a))
-                       hipLaunchKernelGGL((k_ye_factor<NT, 1, true, false>), dim3((unsigned)blocks), dim3(64 * WPB), 0,
+                   if (!ye_plain(a))
+                       hipLaunchKernelGGL((k_ye_factor<NT, 1, true>), dim3((unsigned)blocks), dim3(64 * WPB), 0,
                                           st, a);
                    else
-                       hipLaunchKernelGGL((k_ye_factor<NT, ye_waves_per_eu<NT>(), false, false>), dim3((unsigned)blocks),
+                       hipLaunchKernelGGL((k_ye_factor<NT, ye_waves_per_eu<NT>(), false>), dim3((unsigned)blocks),
                                           dim3(64 * WPB), 0, st, a))
     return hipGetLastError();
 }
 
-bool ye_tiled_applies(const YeFactorArgs& a) {
+bool ye_plain(const YeFactorArgs& a) {
     return !(a.sh.limiter == 2 || a.sh.outer_bc == 2 || a.y.pair_amp || a.f.lapse);
-}
-
-hipError_t launch_ye_factor_tiled(const YeFactorArgs& a, hipStream_t st) {
-    if (!ye_tiled_applies(a) || !a.redo) return hipErrorInvalidValue;
-    TM_YE_DISPATCH(padded_groups(a.sh.N),
-                   constexpr int WPB = ye_waves_per_block<NT>();
-                   const long long blocks = (a.nray + WPB - 1) / WPB;
-                   hipLaunchKernelGGL((k_ye_factor<NT, ye_waves_per_eu<NT>(), false, true>), dim3((unsigned)blocks),
-                                      dim3(64 * WPB), 0, st, a))
-    return hipGetLastError();
 }
 
 hipError_t launch_ye_backtrack(const Shape& sh, double* psi, double* ye, const double* dx, const double* dY,
