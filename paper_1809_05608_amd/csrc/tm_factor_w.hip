@@ -1,4 +1,5 @@
-// FP64 assembly + block elimination + solve with one wavefront per half ray: the Y_e-coupled blocks.
+// FP64 assembly + block elimination + solve with one wavefront per half ray: the Y_e-coupled blocks,
+// and the blocks of one species where there are few systems.
 //
 // A ray is eliminated from both ends at once by the two wavefronts of a workgroup (zones 0 .. m-1 upwards and
 // I-1 .. m+1 downwards, meeting in zone m = I/2).  The transpose of a zone's block is spread over the whole
@@ -629,6 +630,425 @@ hipError_t launch_ye_factor_wave(const YeFactorArgs& a, hipStream_t st) {
         case 20: launch_wave_t<5>(a, ext, st); break;
         case 24: launch_wave_t<6>(a, ext, st); break;
         case 28: launch_wave_t<7>(a, ext, st); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- single species, few systems
+//
+// The same layout for an N x N block: 128 threads a system.  Few systems leave the chip idle, so a step of one
+// wavefront is all there is to it: five panels of 20 columns, the scattering terms and the owners' transport
+// coefficients come to about 1100 vector operations against the tile kernel's 1500 to 2200, and the loads of a
+// zone to a quarter.  24 systems of 540 zones x 20 groups: 2.00 ms on tiles, 1.45 here.
+
+namespace {
+
+template <int T>
+struct SingleShape {
+    static constexpr int NT = 4 * T, CN = (T + 3) / 4, W = 16 * CN;
+    static constexpr int PR = ((4 * T + 11) / 16) * 16 + 4;
+    static constexpr int FC = NT / 16, REM = NT % 16;
+};
+
+template <int T>
+struct SingleLds {
+    using C = SingleShape<T>;
+    double pan[4 * C::PR];
+    double psi[C::W], sch[C::W], bco[C::W], g[C::W], dg[C::W];
+    double y[C::W];                    // y of the previous zone; x in the back substitution
+};
+
+}  // namespace
+
+// One (species, ray) system per workgroup, TRANS the transposed solve, EXT the lapse and the geometric options.
+template <int T, bool TRANS, bool EXT>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2)))
+void k_factor_wave(FactorArgs A) {
+    using X = SingleShape<T>;
+    constexpr int NT = X::NT, CN = X::CN;
+    __shared__ SingleLds<T> lds[2];
+    __shared__ double sP[NT * X::W];               // P[k][k'] with k the column: [row][column], zero beyond NT
+    __shared__ double sPt[TRANS ? NT * X::W : 1];  // P[row][column]
+    __shared__ double s_eps[X::W];
+    __shared__ double s_C[T][CN][64];              // the outer half's last factor, for the meeting zone
+    __shared__ double s_y[X::W], s_x[X::W];        // the outer half's y; x of the meeting zone
+    __shared__ int s_bad[2];
+    const int lane = threadIdx.x & 63;
+    const bool half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // the half coming from the outer edge
+    const long long sys = A.sys0 + blockIdx.x;
+    if (A.active && A.active[sys] == 0) return;                            // both wavefronts
+    const Shape& sh = A.sh;
+    const int N = sh.N, I = sh.I;
+    const bool diff = sh.terms & kDiffusion, emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
+    for (int j = threadIdx.x; j < NT * X::W; j += 128) {
+        const int r = j / X::W, q = j % X::W;
+        sP[j] = q < NT ? A.cs->P[q][r] : 0.0;
+        if (TRANS) sPt[j] = q < NT ? A.cs->P[r][q] : 0.0;
+    }
+    if (threadIdx.x < X::W) s_eps[threadIdx.x] = threadIdx.x < N ? A.cs->eps[threadIdx.x] : 0.0;
+    __syncthreads();
+
+    SingleLds<T>& sm = lds[half];
+    const double c = sh.c_dt;
+    const int m = I / 2, delay = half && (I & 1) == 0 ? 1 : 0;         // the outer half has one zone less
+    const int dir = half ? -1 : 1;
+    const double sgn = half ? -1.0 : 1.0;
+    const int ray = (int)(sys % sh.R), spec = (int)(sys / sh.R);
+    const size_t cb = (size_t)sys * I * N, zb = (size_t)ray * I, eb = (size_t)ray * (I + 1);
+    auto clampz = [&](int z) { return min(max(z, 0), I - 1); };
+    auto clampe = [&](int e) { return min(max(e, 0), I); };
+    auto group = [&](int ln) { return ln < N ? ln : 0; };              // owner lane i owns group i
+
+    double n_psi, n_ka, n_et, n_ks, z_rhs;                              // as loaded: next zone; this zone
+    auto load_next = [&](int k, int z) {
+        const size_t ci = cb + (size_t)clampz(z) * N + k;
+        n_psi = A.psi[ci];
+        n_ka = A.f.kappa_a[ci];
+        n_et = A.f.eta[ci];
+        n_ks = A.f.kappa_s[ci];
+    };
+    double Tz = 1.0, amp = 0.0;
+    auto load_zone = [&](int k, int zz) {
+        const int z = clampz(zz);
+        z_rhs = A.rhs[cb + (size_t)z * N + k];
+        if (nes) {
+            Tz = A.f.temp[zb + z];
+            amp = A.f.nes_amp[(size_t)sys * I + z];
+        }
+    };
+    // area times dH/dpsi_I at the outer boundary
+    auto outer = [&](double rnu, double psi, double lam) -> double {
+        if (!diff || sh.outer_bc == 0) return 0.0;
+        const double r = A.f.r_edge[eb + I];
+        double area = r * r;
+        if (EXT && A.f.lapse) {
+            const double x = A.f.lapse_edge[eb + I];
+            area /= x * x;
+        }
+        if (EXT && sh.outer_bc == 2) {                                  // ghost zone of eq. a62af
+            const Ghost gh = outer_ghost(A.f.r_edge[eb + I - 1], r, rnu);
+            const EdgeFlux e = edge_flux(psi, gh.ratio * psi, lam, gh.D, sh.psi_floor, sh.limiter,
+                                         sh.limiter == 2 ? limb_factor(r, rnu) : -1.0);
+            return area * (e.dHu + gh.ratio * e.dHv);
+        }
+        return area;                                                   // free streaming: H = psi of the last zone
+    };
+    auto radius_nu = [&](int k) { return EXT && A.f.r_nu ? A.f.r_nu[(size_t)spec * N + k] : 1.0; };
+    const int z0 = half ? I - 1 : 0;
+    double psi, sig, lam, tc, to = 0.0, iV_prev = 0.0;                  // this zone; trailing edge
+    {
+        const int k = group(lane);
+        load_next(k, z0);
+        psi = n_psi;
+        sig = n_ka + n_et;
+        lam = rcp_cubic(sig + n_ks);
+        tc = half ? outer(radius_nu(k), psi, lam) : 0.0;
+        load_next(k, z0 + dir);
+        load_zone(k, z0);
+    }
+    const int e0 = half ? I - 1 : 1;
+    double r_t = A.f.r_edge[clampe(e0 - dir) + eb], r_l = A.f.r_edge[clampe(e0) + eb],
+           r_b = A.f.r_edge[clampe(e0 + dir) + eb];
+
+    WaveBlock<T, CN> S;
+#pragma unroll
+    for (int q = 0; q < T; ++q)
+#pragma unroll
+        for (int C = 0; C < CN; ++C) S.set(q, C, 0.0);
+    if (lane < X::W) {
+        sm.psi[lane] = sm.sch[lane] = sm.bco[lane] = sm.g[lane] = sm.y[lane] = 0.0;
+        sm.dg[lane] = 1.0;
+    }
+    wave_sync();
+    TileGuard guard(A.growth_limit);
+    constexpr size_t SZ = (size_t)NT * (NT + 1);                       // slot of a zone
+    double* ws = reinterpret_cast<double*>(A.wsC) + (size_t)blockIdx.x * I * SZ;
+    typedef double V2 __attribute__((ext_vector_type(2)));
+
+    // C and y of the zone that step n - 1 finished, in the middle of the next step (see k_ye_factor_wave)
+    auto store = [&](int n, int ln) {
+        const int jc = ln & 15, a = ln >> 4;
+        double* slot = ws + (size_t)(half ? I - 1 - (n - 1 - delay) : n - 1) * SZ;
+#pragma unroll
+        for (int C = 0; C < X::FC; ++C) {
+#pragma unroll
+            for (int q = 0; q + 1 < T; q += 2)
+                nt_store(reinterpret_cast<V2*>(slot + 64 * T * C) + 32 * q + ln, V2{S.get(q, C), S.get(q + 1, C)});
+            if (T & 1) nt_store(slot + 64 * T * C + 64 * (T - 1) + ln, S.get(T - 1, C));
+        }
+        if (X::REM && jc < X::REM) {
+#pragma unroll
+            for (int q = 0; q < T; ++q)
+                nt_store(slot + 64 * T * X::FC + 4 * X::REM * q + X::REM * a + jc, S.get(q, X::FC < CN ? X::FC : 0));
+        }
+        if (ln < NT) nt_store(slot + (size_t)NT * NT + ln, sm.y[ln]);
+    };
+
+    for (int n = delay; n <= m; ++n) {
+        const bool mid = n == m;
+        if (mid) {
+            if (half) {                                                // hand the last factor to the inner half
+#pragma unroll
+                for (int q = 0; q < T; ++q)
+#pragma unroll
+                    for (int C = 0; C < CN; ++C) s_C[q][C][lane] = S.get(q, C);
+                if (lane < X::W) s_y[lane] = sm.y[lane];
+                if (n > delay) store(n, lane);
+                if (lane == 0) s_bad[1] = guard.bad != 0ull;
+            }
+            __syncthreads();
+            if (half) break;
+        }
+        // what derives from the lane id is formed again each step instead of being held across it
+        const int ln = opaque_lane(), jc = ln & 15, k = group(ln);
+        const TileLane L(ln);
+        const bool real = ln < N;
+        const int zc = half ? I - 1 - (n - delay) : n, zn = zc + dir;
+        const bool has_next = zn >= 0 && zn < I;
+        const ExpCoef coef = exp_coef();
+        // ---- owned groups: transport coefficients, right-hand side
+        double iVc = rcp_cubic(sgn * shell_volume(r_t, r_l)), iVn = 0.0, sA = sgn * r_l * r_l;
+        if (TRANS && has_next) iVn = rcp_cubic(sgn * shell_volume(r_l, r_b));
+        if (EXT && A.f.lapse) {
+            const double a0 = A.f.lapse[zb + zc], a1 = A.f.lapse[zb + clampz(zn)];
+            iVc *= a0 * a0 * a0;
+            iVn *= a1 * a1 * a1;
+            const double x = A.f.lapse_edge[eb + clampe(half ? zc : zc + 1)];
+            sA /= x * x;
+        }
+        const double cV = c * iVc;
+        const double n_sig = n_ka + n_et, n_lam = rcp_cubic(n_sig + n_ks);
+        double ec = 0.0, eo = 0.0;
+        if (diff) {
+            if (has_next) {
+                const double Dl = fabs(0.5 * (r_l + r_b) - 0.5 * (r_t + r_l));
+                const double limb = (EXT && sh.limiter == 2) ? limb_factor(r_l, radius_nu(k)) : -1.0;
+                const EdgeFlux e = edge_flux(half ? n_psi : psi, half ? psi : n_psi, sqrt(lam * n_lam), Dl, sh.psi_floor,
+                                             sh.limiter, limb);
+                ec = sA * (half ? e.dHv : e.dHu);
+                eo = sA * (half ? e.dHu : e.dHv);
+            } else if (!half) {
+                ec = outer(radius_nu(k), psi, lam);
+            }
+        }
+        double diag = fma(cV, ec + tc, 1.0);
+        if (emabs) diag = fma(c, sig, diag);
+        if (ln < NT) {
+            const double sch = real ? (TRANS ? -c * tc * iV_prev : cV * to) : 0.0;
+            const double bco = real ? (TRANS ? -c * ec * iVn : cV * eo) : 0.0;
+            double g = real ? A.rhs_sign * z_rhs : 0.0;
+            g = fma(-sch, sm.y[ln], g);
+            if (mid) g = fma(-bco, s_y[ln], g);
+            sm.psi[ln] = real ? psi : 0.0;
+            sm.sch[ln] = sch;
+            sm.bco[ln] = bco;
+            sm.g[ln] = g;
+            sm.dg[ln] = real ? diag : 1.0;
+        }
+        tc = -eo;                                                      // the next zone becomes the current one
+        to = -ec;
+        psi = n_psi;
+        sig = n_sig;
+        lam = n_lam;
+        iV_prev = iVc;
+        wave_sync();
+        const double iT = rcp_cubic(Tz), camp = c * amp;
+        if (n > delay) store(n, ln);
+        load_next(k, zn + dir);
+        load_zone(k, zn);
+        r_t = r_l;
+        r_l = r_b;
+        r_b = A.f.r_edge[eb + clampe((half ? zc : zc + 1) + 2 * dir)];
+        __builtin_amdgcn_sched_barrier(0);
+
+        // ---- the block: Schur term of the previous factor (both neighbours' in the meeting zone), scattering
+        //      terms and the diagonal, per column of the stored matrix and row 4u + a
+#pragma unroll
+        for (int C = 0; C < CN; ++C) {
+            const int col = 16 * C + jc;
+            const double sc = -sm.sch[col], bc = sm.bco[col];
+#pragma unroll
+            for (int q = 0; q < T; ++q) {
+                S.set(q, C, S.get(q, C) * sc);
+                if (mid) S.set(q, C, fma(-s_C[q][C][ln], bc, S.get(q, C)));
+            }
+            double dgv = sm.dg[col];
+            if (nes) {
+                const double pcol = sm.psi[col], ek = s_eps[col];
+                const double wc = -camp * pcol, w1c = -camp - wc;       // weights of psi and 1 - psi of the column
+                double acc = 0.0;
+#pragma unroll
+                for (int u = 0; u < T; ++u) {
+                    const int row = 4 * u + L.a;
+                    const double M = exp_nonpos(-fabs(s_eps[row] - ek) * iT, coef);
+                    const double P = sP[row * X::W + col], PM = P * M;
+                    const double prow = sm.psi[row];
+                    const bool up = row > col;
+                    if (TRANS) {                                        // row is k, column k'
+                        const double Pt = sPt[row * X::W + col], wr = -camp * prow, w1r = -camp - wr;
+                        S.set(u, C, fma((up ? w1r : wr) * Pt, M, fma(up ? wr : w1r, Pt, S.get(u, C))));
+                    } else {                                            // column is k, row k'
+                        S.set(u, C, fma(up ? wc : w1c, PM, fma(up ? w1c : wc, P, S.get(u, C))));
+                    }
+                    // sum over k' for k the column: k' is the row either way
+                    const double pq = 1.0 - prow;
+                    acc = fma(up ? prow : pq, P, acc);
+                    acc = fma(up ? pq : prow, PM, acc);
+                }
+                dgv = fma(camp, mfma4(1.0, acc, 0.0), dgv);
+            }
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (4 * C + x < T) {
+                    const double on = (L.g == x && L.a == L.b) ? 1.0 : 0.0;
+                    S.set(4 * C + x, C, fma(on, dgv, S.get(4 * C + x, C)));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+
+        // ---- Ahat^-1, y = Ahat^-1 g, C = Ahat^-1 diag(b)
+        wave_invert<T, CN, X::PR>(S, L, jc, sm.pan, guard);
+        double yc[CN];
+#pragma unroll
+        for (int C = 0; C < CN; ++C) yc[C] = 0.0;
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+            const double g = sm.g[4 * q + L.a];
+#pragma unroll
+            for (int C = 0; C < CN; ++C) yc[C] = fma(S.get(q, C), g, yc[C]);
+        }
+#pragma unroll
+        for (int C = 0; C < CN; ++C) yc[C] = mfma4(1.0, yc[C], 0.0);
+        if (L.a == 0) {
+#pragma unroll
+            for (int C = 0; C < CN; ++C) sm.y[16 * C + jc] = yc[C];
+        }
+        if (!mid) {
+#pragma unroll
+            for (int q = 0; q < T; ++q) {
+                const double b = sm.bco[4 * q + L.a];
+#pragma unroll
+                for (int C = 0; C < CN; ++C) S.set(q, C, S.get(q, C) * b);
+            }
+        }
+        wave_sync();
+    }
+    if (!half) {
+        if (lane == 0) s_bad[0] = guard.bad != 0ull;
+        if (lane < X::W) s_x[lane] = sm.y[lane];
+    }
+    __syncthreads();
+    // a system whose growth guard tripped is left to the pivoting re-run
+    const bool bad = s_bad[0] || s_bad[1];
+    if (bad) {
+        if (threadIdx.x == 0) {
+            if (A.guard) A.guard[sys] = 1;
+            if (A.flags) A.flags[sys] |= 8;
+        }
+        return;
+    }
+
+    // ---- back substitution outwards from the meeting zone
+    const int lb = opaque_lane(), jc = lb & 15;
+    const TileLane L(lb);
+    auto put = [&](int z, double d) {
+        if (lb < N) {
+            const size_t ci = cb + (size_t)z * N + lb;
+            if (A.psi_out) {
+                A.psi_out[ci] += d;
+                if (A.dx) A.dx[ci] = d;
+            } else {
+                A.x[ci] = d;
+            }
+        }
+    };
+    if (lb < X::W) sm.y[lb] = s_x[lb];
+    if (!half) put(m, lb < X::W ? s_x[lb] : 0.0);
+    wave_sync();
+    constexpr int D = 4;                                                // zones in flight
+    double Cb[D][T][CN], yb[D][CN];                                      // y in column form
+    auto fetch = [&](int n, double (&c_)[T][CN], double (&y_)[CN]) {
+        const double* slot = ws + (size_t)(half ? I - 1 - (n - delay) : n) * SZ;
+#pragma unroll
+        for (int C = 0; C < X::FC; ++C) {
+#pragma unroll
+            for (int q = 0; q + 1 < T; q += 2) {
+                const V2 v = nt_load(reinterpret_cast<const V2*>(slot + 64 * T * C) + 32 * q + lb);
+                c_[q][C] = v.x;
+                c_[q + 1][C] = v.y;
+            }
+            if (T & 1) c_[T - 1][C] = nt_load(slot + 64 * T * C + 64 * (T - 1) + lb);
+        }
+        if constexpr (X::REM > 0) {
+#pragma unroll
+            for (int q = 0; q < T; ++q)
+                c_[q][X::FC] = jc < X::REM ? nt_load(slot + 64 * T * X::FC + 4 * X::REM * q + X::REM * L.a + jc) : 0.0;
+        }
+#pragma unroll
+        for (int C = 0; C < CN; ++C) y_[C] = 16 * C + jc < NT ? nt_load(slot + (size_t)NT * NT + 16 * C + jc) : 0.0;
+    };
+    auto step = [&](int n, const double (&c_)[T][CN], const double (&y_)[CN]) {
+        double acc[CN];
+#pragma unroll
+        for (int C = 0; C < CN; ++C) acc[C] = 0.0;
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+            const double x = sm.y[4 * q + L.a];
+#pragma unroll
+            for (int C = 0; C < CN; ++C) acc[C] = fma(c_[q][C], x, acc[C]);
+        }
+#pragma unroll
+        for (int C = 0; C < CN; ++C) acc[C] = y_[C] - mfma4(1.0, acc[C], 0.0);
+        wave_sync();
+        if (L.a == 0) {
+#pragma unroll
+            for (int C = 0; C < CN; ++C) sm.y[16 * C + jc] = acc[C];
+        }
+        wave_sync();
+        put(half ? I - 1 - (n - delay) : n, lb < X::W ? sm.y[lb] : 0.0);
+    };
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+        if (m - 1 - d >= delay) fetch(m - 1 - d, Cb[d], yb[d]);
+    for (int n = m - 1; n >= delay; n -= D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (n - d < delay) break;
+            if (n - d - (D - 1) >= delay) fetch(n - d - (D - 1), Cb[(d + D - 1) % D], yb[(d + D - 1) % D]);
+            step(n - d, Cb[d], yb[d]);
+        }
+    }
+    if (threadIdx.x == 0 && A.psi_out) {
+        if (A.iters) A.iters[sys] += 1;
+        if (A.pending) A.pending[sys] = 1;                              // trial psi + delta awaits the line search
+        if (A.alpha) A.alpha[sys] = 1.0;
+    }
+}
+
+template <int T>
+static void launch_single_t(const FactorArgs& a, bool transpose, hipStream_t st) {
+    const dim3 grid((unsigned)a.nsys), block(128);
+    const bool ext = a.f.lapse || a.sh.limiter == 2 || a.sh.outer_bc == 2;
+    if (transpose) {
+        if (ext) hipLaunchKernelGGL((k_factor_wave<T, true, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((k_factor_wave<T, true, false>), grid, block, 0, st, a);
+    } else {
+        if (ext) hipLaunchKernelGGL((k_factor_wave<T, false, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((k_factor_wave<T, false, false>), grid, block, 0, st, a);
+    }
+}
+
+hipError_t launch_factor_wave(const FactorArgs& a, bool transpose, hipStream_t st) {
+    switch (padded_groups(a.sh.N)) {
+        case 4: launch_single_t<1>(a, transpose, st); break;
+        case 8: launch_single_t<2>(a, transpose, st); break;
+        case 12: launch_single_t<3>(a, transpose, st); break;
+        case 16: launch_single_t<4>(a, transpose, st); break;
+        case 20: launch_single_t<5>(a, transpose, st); break;
+        case 24: launch_single_t<6>(a, transpose, st); break;
+        case 28: launch_single_t<7>(a, transpose, st); break;
+        case 32: launch_single_t<8>(a, transpose, st); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

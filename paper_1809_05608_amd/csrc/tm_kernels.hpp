@@ -94,6 +94,7 @@ hipError_t launch_factor(const FactorArgs& a, bool fp32, bool transpose, bool pi
                          int kernel = kFactorQuadMfma);
 bool launch_factor_quad(const FactorArgs& a, hipStream_t st, int kernel);
 hipError_t launch_factor_tile(const FactorArgs& a, bool transpose, hipStream_t st);
+hipError_t launch_factor_wave(const FactorArgs& a, bool transpose, hipStream_t st);
 hipError_t launch_factor_geo(const FactorArgs& a, bool fp32, bool transpose, bool pivot, hipStream_t st);
 
 hipError_t launch_vjp(const Shape& sh, const Fields& f, const Consts* cs, const double* psi,

@@ -1,4 +1,4 @@
-"""The Y_e-coupled elimination with a wavefront per half ray, at the sizes where it can go wrong.
+"""The eliminations with a wavefront per half ray, at the sizes where they can go wrong.
 
 Row-group and column remainders of the block (2 NT + 1 rows from 9 to 57 over 16 columns), rays of 1 to 6 zones
 (no zone on one side of the meeting zone, both parities), and each option that changes the block, against the
@@ -13,10 +13,12 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
 from oracle import ye_coupled as yc
 from paper_1809_05608_amd import tm
 from test_kernel_resources import BUILD, LLVM, _kernel_scratch
+from test_tile_factor import _case
 
 SHAPES = [(1, 1, 4), (2, 2, 3), (3, 3, 5), (1, 4, 8), (2, 5, 9), (3, 6, 12), (2, 4, 15), (1, 5, 17), (5, 3, 20),
           (1, 6, 21), (2, 3, 24), (1, 5, 25), (2, 4, 28)]
@@ -67,6 +69,41 @@ def test_coupled_elimination_matches_oracle(shape, option, monkeypatch):
         for s in range(2):
             assert _zone_err(psi[s, r], ref[:, s * N:(s + 1) * N]) < 1e-12, (s, r)
         assert np.max(np.abs(ye[r] - ref[:, 2 * N])) < 1e-12 * np.max(np.abs(ref[:, 2 * N])), r
+    ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("option", ["plain", "lapse", "geometric"])
+@pytest.mark.parametrize("shape", [dict(S=2, R=256, I=3, N=4), dict(S=1, R=513, I=1, N=5), dict(S=3, R=171, I=2, N=12),
+                                   dict(S=1, R=515, I=4, N=17), dict(S=1, R=514, I=5, N=20), dict(S=1, R=517, I=3, N=29),
+                                   dict(S=1, R=516, I=6, N=32)])
+def test_eliminations_on_both_sides_of_the_system_count(shape, option):
+    """512 systems (a wavefront per half system), and just more (four half systems to a wavefront, the last one
+    partly filled), plain and transposed, sampled systems against the oracle.  Bar: 1e-11 of max|x|."""
+    print("case either side", shape, option, flush=True)
+    sys.stdout.flush()
+    w, over = _case(shape, option)
+    rng = np.random.default_rng(7)
+    psi = (w.psi_n.numpy() * rng.uniform(0.6, 1.4, w.psi_n.shape)).clip(0, 1)
+    rhs = rng.standard_normal(psi.shape)
+    wn = w.numpy()
+    wn.update({k: v.numpy() for k, v in over.items()})
+    syss = oracle.systems_from_workload(wn)
+    wd = w.to("cuda")
+    f = tm.DeviceFields.of(wd, **{k: v.to("cuda") for k, v in over.items()})
+    ctx = tm.Context(tm.problem_of(wd))
+    psi_d, rhs_d = torch.as_tensor(psi, device="cuda"), torch.as_tensor(rhs, device="cuda")
+    picked = sorted({(0, 0), (0, 1), (0, w.R // 2), (w.S - 1, w.R - 3), (w.S - 1, w.R - 2), (w.S - 1, w.R - 1)})
+    for transpose in (False, True):
+        x = torch.full_like(psi_d, float("nan"))
+        ctx.factor_solve(f, psi_d, rhs_d, x, transpose)
+        torch.cuda.synchronize()
+        x = x.cpu().numpy()
+        assert np.all(np.isfinite(x))
+        for s, r in picked:
+            xo = oracle.block_thomas_solve(*oracle.jacobian_blocks(syss[s][r], psi[s, r]), rhs[s, r], transpose=transpose)
+            err = np.max(np.abs(x[s, r] - xo)) / np.max(np.abs(xo))
+            assert err < 1e-11, (s, r, transpose, err)
     ctx.close()
 
 
