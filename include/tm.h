@@ -241,7 +241,9 @@ tm_status tm_factor_solve_noalloc(tm_ctx *ctx, const tm_inputs *in, const double
  * largest sum over a cell of the magnitudes of the terms of G (the level below which
  * G itself is rounding).  rtol = 0 runs exactly max_iter updates (unless G is exactly
  * zero).  In TM_PREC_MIXED each update is an FP32 solve of the FP64 residual, so the
- * iteration is iterative refinement to the same stopping rule.  `stats` (all pointers
+ * iteration is iterative refinement to the same stopping rule; with 4096 systems or fewer
+ * still iterating the update is solved in FP64, which is then the faster (never with
+ * TM_FACTOR_KERNEL set at tm_create).  `stats` (all pointers
  * device, may be NULL as a whole) receives the per-system results at the returned
  * psi.  Returns TM_OK, or the worst of TM_ERR_NONFINITE, TM_ERR_SINGULAR,
  * TM_ERR_NOT_CONVERGED over systems (per-system detail in stats.flags).           */

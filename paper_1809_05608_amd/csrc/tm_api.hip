@@ -29,6 +29,7 @@ struct tm_ctx {
     double* res = nullptr;      // [nsys]
     double* res0 = nullptr;     // [nsys]
     int* active = nullptr;      // [nsys]
+    int* list = nullptr;        // [nsys] the active systems
     int* iters = nullptr;       // [nsys]
     int* flags = nullptr;       // [nsys]
     int* count = nullptr;       // [1]
@@ -45,6 +46,7 @@ struct tm_ctx {
     // pivoting policy: 0 diagonal pivots with guarded fallback to partial pivoting (default),
     // 1 always partial pivoting, 2 diagonal pivots only (guard trips become failures)
     int pivot_policy = 0;
+    bool factor_forced = false;                 // TM_FACTOR_KERNEL is set: the float32 solve stays in float32
     int factor_kernel = tmk::kFactorQuadMfma;   // float32 diagonal-pivot solve: TM_FACTOR_KERNEL=window|bf16x3|bf16|mfma|valu|lane
     double growth_limit = 16.0;
     long long pivot_fallbacks = 0;   // systems re-factored with partial pivoting since creation
@@ -196,6 +198,7 @@ tm_status ensure_small(tm_ctx* c) {
     TM_TRY(hip_check(c, hipMalloc((void**)&c->res, ns * sizeof(double)), "hipMalloc res"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->res0, ns * sizeof(double)), "hipMalloc res0"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->active, ns * sizeof(int)), "hipMalloc active"));
+    TM_TRY(hip_check(c, hipMalloc((void**)&c->list, ns * sizeof(int)), "hipMalloc list"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->iters, ns * sizeof(int)), "hipMalloc iters"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->flags, ns * sizeof(int)), "hipMalloc flags"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->count, sizeof(int)), "hipMalloc count"));
@@ -233,7 +236,9 @@ tm_status factor_batch(tm_ctx* c, bool fp32, long long* batch) {
         TM_TRY(hip_check(c, hipMemGetInfo(&freeb, &totalb), "hipMemGetInfo"));
         long long b = ns;
         while (b > 1 && (double)(b + tmk::kWsPadSystems) * per > 0.7 * (double)freeb) b = (b + 1) / 2;
-        const size_t bytes = (size_t)(b + tmk::kWsPadSystems) * per;
+        size_t bytes = (size_t)(b + tmk::kWsPadSystems) * per;
+        if (fp32 && tmk::factor_in_fp64(shape_of(c->p), ns))        // Newton updates in FP64 take twice the bytes
+            bytes = std::max(bytes, std::min((size_t)(ns + 1) * 2 * per, (size_t)(0.7 * (double)freeb)));
         hipError_t e = hipMalloc(&c->ws, bytes);
         if (e != hipSuccess) {
             c->ws = nullptr;
@@ -325,9 +330,10 @@ tmk::YeFields ye_fields_of(const tm_ye_inputs& y) {
     return f;
 }
 
+// `listed`: the set entries of `active` are the first so many of c->list.
 tm_status run_factor(tm_ctx* c, const tm_inputs* in, const double* psi, const double* rhs, double rhs_sign,
                      double* x, double* psi_out, const int* active, bool fp32, bool transpose,
-                     double* dx = nullptr, const double* rhs_max = nullptr) {
+                     double* dx = nullptr, const double* rhs_max = nullptr, long long listed = -1) {
     long long batch = 0;
     TM_TRY(factor_batch(c, fp32, &batch));
     const int NT = tmk::padded_groups(c->p.n_groups);
@@ -357,10 +363,25 @@ tm_status run_factor(tm_ctx* c, const tm_inputs* in, const double* psi, const do
     if (!pivot_first)
         TM_TRY(hip_check(c, hipMemsetAsync(c->guard, 0, ns * sizeof(int), c->stream), "memset guard"));
     if (c->timing) TM_TRY(hip_check(c, hipEventRecord(c->kt[0], c->stream), "timing event"));
-    for (long long s0 = 0; s0 < ns; s0 += batch) {
-        a.sys0 = s0;
-        a.nsys = std::min(batch, ns - s0);
-        TM_TRY(hip_check(c, tmk::launch_factor(a, fp32, transpose, pivot_first, c->stream, c->factor_kernel), "factor kernel"));
+    {
+        // diagonal pivots in FP64, also for the float32 Newton updates of few systems; systems at rest then
+        // take neither slots nor wavefronts
+        const bool few = fp32 && psi_out && !pivot_first && !c->factor_forced &&
+                         tmk::factor_in_fp64(a.sh, listed >= 0 ? listed : ns);
+        const bool as32 = fp32 && !few;
+        tmk::FactorArgs d = a;
+        d.total = ns;
+        if (!as32 && !pivot_first && listed >= 0 && listed < ns && tmk::factor_takes_list(a.sh, listed)) {
+            d.list = c->list;
+            d.total = listed;
+        }
+        const long long step = few ? std::min(d.total, tmk::factor_fp64_slots(a.sh, c->ws_bytes)) : batch;
+        if (step < 1) return set_err(c, TM_ERR_WORKSPACE, "workspace smaller than one system's factors");
+        for (long long s0 = 0; s0 < d.total; s0 += step) {
+            d.sys0 = s0;
+            d.nsys = std::min(step, d.total - s0);
+            TM_TRY(hip_check(c, tmk::launch_factor(d, as32, transpose, pivot_first, c->stream, c->factor_kernel), "factor kernel"));
+        }
     }
     if (c->timing) {
         TM_TRY(hip_check(c, hipEventRecord(c->kt[1], c->stream), "timing event"));
@@ -378,6 +399,7 @@ tm_status run_factor(tm_ctx* c, const tm_inputs* in, const double* psi, const do
     c->pivot_fallbacks += nredo;
     if (c->pivot_policy == 2) return set_err(c, TM_ERR_SINGULAR, "diagonal-pivot growth guard tripped");
     a.active = c->redo;
+    a.total = ns;
     for (long long s0 = 0; s0 < ns; s0 += batch) {
         a.sys0 = s0;
         a.nsys = std::min(batch, ns - s0);
@@ -521,6 +543,7 @@ tm_status tm_create(const tm_problem* p, void* stream, tm_ctx** out) {
     }
     if (const char* e = std::getenv("TM_GROWTH_LIMIT")) c->growth_limit = std::atof(e);
     if (const char* e = std::getenv("TM_FACTOR_KERNEL")) {
+        c->factor_forced = true;
         if (!std::strcmp(e, "lane")) c->factor_kernel = tmk::kFactorLane;
         else if (!std::strcmp(e, "valu")) c->factor_kernel = tmk::kFactorQuadValu;
         else if (!std::strcmp(e, "mfma")) c->factor_kernel = tmk::kFactorQuadMfma;
@@ -544,6 +567,7 @@ tm_status tm_destroy(tm_ctx* c) {
         (void)hipFree(c->res);
         (void)hipFree(c->res0);
         (void)hipFree(c->active);
+        (void)hipFree(c->list);
         (void)hipFree(c->iters);
         (void)hipFree(c->flags);
         (void)hipFree(c->count);
@@ -690,6 +714,7 @@ tm_status tm_factor_solve_noalloc(tm_ctx* c, const tm_inputs* in, const double* 
     a.dx = nullptr;
     a.pending = nullptr;
     a.alpha = nullptr;
+    a.total = ns;
     a.wsC = base + pl.o_ws;
     a.wsY = base + pl.o_ws + (size_t)(pl.batch + tmk::kWsPadSystems) * c->p.n_zones * NT * NT * es;
     const bool pivot_first = c->pivot_policy == 1;
@@ -732,8 +757,9 @@ tm_status tm_newton_step(tm_ctx* c, const tm_inputs* in, const double* psi_n, do
     TM_TRY(hip_check(c, hipMemsetAsync(c->iters, 0, ns * sizeof(int), c->stream), "memset iters"));
     TM_TRY(hip_check(c, hipMemsetAsync(c->flags, 0, ns * sizeof(int), c->stream), "memset flags"));
 
-    auto count_of = [&](const int* flags_arr, int* out_n) -> tm_status {
-        TM_TRY(hip_check(c, tmk::launch_count_active(flags_arr, ns, c->count, c->stream), "count kernel"));
+    auto count_of = [&](const int* flags_arr, int* out_n, int* list = nullptr) -> tm_status {
+        if (list) TM_TRY(hip_check(c, tmk::launch_list_active(flags_arr, ns, list, c->count, c->stream), "list kernel"));
+        else TM_TRY(hip_check(c, tmk::launch_count_active(flags_arr, ns, c->count, c->stream), "count kernel"));
         TM_TRY(hip_check(c, hipMemcpyAsync(c->h_count, c->count, sizeof(int), hipMemcpyDeviceToHost, c->stream),
                          "copy count"));
         TM_TRY(hip_check(c, hipStreamSynchronize(c->stream), "stream sync"));
@@ -769,11 +795,11 @@ tm_status tm_newton_step(tm_ctx* c, const tm_inputs* in, const double* psi_n, do
     const int max_trials = 9;                              // alpha = 1, 1/2, ..., 1/256
     for (int it = 0; it < max_iter; ++it) {
         int nact = 0;
-        TM_TRY(count_of(c->active, &nact));
+        TM_TRY(count_of(c->active, &nact, c->list));
         if (nact == 0) break;
         // Newton update psi += delta for the active systems (delta kept for backtracking)
         // res holds max |G| of the residual in gbuf for every active system (scaling of the float32 solve)
-        TM_TRY(run_factor(c, in, psi, c->gbuf, -1.0, nullptr, psi, c->active, fp32, false, c->dbuf, c->res));
+        TM_TRY(run_factor(c, in, psi, c->gbuf, -1.0, nullptr, psi, c->active, fp32, false, c->dbuf, c->res, nact));
         // line search on max|G| with the FP64 residual; a rejected trial is moved back to half the step
         o.mode = tmk::kResTrial;
         for (int t = 0; t < max_trials; ++t) {

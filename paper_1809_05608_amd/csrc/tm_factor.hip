@@ -17,8 +17,30 @@ size_t factor_ws_bytes_per_system(int I, int N, bool fp32) {
 // it four half systems per wavefront (tm_factor_t.hip), whose matrix operations have no idle rows.  Measured,
 // 540 zones x 20 groups: 6 systems 1.28 against 1.90 ms, 24: 1.45 against 2.00, 512: 1.99 against 2.00, 1024:
 // 2.20 against 2.23, 2048: 4.6 against 2.6; 300 x 12: 1024 systems 0.65 against 0.63, 2048 1.10 against 0.76.
-// The count is the problem's, not the launch's: a batch takes the kernel that the whole would take.
+// The count is that of all batches: a batch takes the kernel that the whole would take.
 constexpr long long kWaveSystems = 512;
+
+// Up to this many systems a float32 launch leaves the chip waiting for one wavefront's chain of zones, 16 systems
+// from one end: the FP64 kernels with two or half a system per wavefront from both ends are faster up to about
+// twice as many, float32 the faster above for half the bytes of factors.  float32 against FP64, 540 zones x 20
+// groups: 720 systems 7.0 against 2.2 ms, 4096: 7.1 against 4.0, 8192: 8.1 against 7.7, 16384: 10.9 against 15.1;
+// 300 zones, 4096 systems: 8 groups 1.12 against 0.65, 12: 1.79 against 1.11, 16: 2.74 against 1.63, 24: 4.87
+// against 4.18, 32: 7.64 against 7.03.
+constexpr long long kFp64Systems = 4096;
+
+static bool near_cells(const Shape& sh) { return (long long)sh.S * sh.R * sh.I * sh.N < (1ll << 29); }
+
+bool factor_takes_list(const Shape& sh, long long systems) {
+    return systems <= kWaveSystems || near_cells(sh);       // the tile kernel reaches a pair's cells with 32-bit offsets
+}
+
+bool factor_in_fp64(const Shape& sh, long long systems) {
+    return systems <= kFp64Systems && (systems == (long long)sh.S * sh.R || factor_takes_list(sh, systems));
+}
+
+long long factor_fp64_slots(const Shape& sh, size_t bytes) {
+    return (long long)(bytes / factor_ws_bytes_per_system(sh.I, sh.N, false)) & ~1ll;     // whole pairs
+}
 
 hipError_t launch_factor(const FactorArgs& a, bool fp32, bool transpose, bool pivot, hipStream_t st, int kernel) {
     // the float32 forward solve with diagonal pivots (the mixed-precision Newton update) takes one
@@ -30,7 +52,7 @@ hipError_t launch_factor(const FactorArgs& a, bool fp32, bool transpose, bool pi
     // option (one row per lane: 8.2 ms against 2.1 at 720 systems, 122 against 57 at 65536).  The tile kernel
     // addresses the cells of two systems with 32-bit byte offsets.
     if (!fp32 && !pivot) {
-        const bool few = (long long)a.sh.S * a.sh.R <= kWaveSystems, far = (long long)a.sh.I * a.sh.N >= (1ll << 27);
+        const bool few = a.total <= kWaveSystems, far = (long long)a.sh.I * a.sh.N >= (1ll << 27);
         return few || far ? launch_factor_wave(a, transpose, st) : launch_factor_tile(a, transpose, st);
     }
     if (a.sh.limiter == 2 || a.sh.outer_bc == 2) return launch_factor_geo(a, fp32, transpose, pivot, st);

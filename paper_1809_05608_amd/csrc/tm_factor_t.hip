@@ -73,12 +73,12 @@ struct Place {
     int delay, dir, I, N;
     double sgn;
     unsigned off0;                     // byte offset of the system's cells from the wavefront's first system
-    __device__ __forceinline__ Place(int lane, bool two, int I_, int N_) : L(lane), I(I_), N(N_) {
+    __device__ __forceinline__ Place(int lane, bool two, unsigned gap, int I_, int N_) : L(lane), I(I_), N(N_) {
         half = L.g & 1;
         delay = half && (I & 1) == 0 ? 1 : 0;                   // the outer half has one zone less
         dir = half ? -1 : 1;
         sgn = half ? -1.0 : 1.0;
-        off0 = second(two) ? (unsigned)I * (unsigned)N * 8u : 0u;
+        off0 = second(two) ? gap * (unsigned)I * (unsigned)N * 8u : 0u;
     }
     __device__ __forceinline__ bool second(bool two) const { return two && (L.g >> 1); }
     __device__ __forceinline__ int zone_at(int n) const { return half ? I - 1 - (n - delay) : n; }
@@ -106,9 +106,11 @@ void k_factor_tile(FactorArgs A) {
     const int N = sh.N, I = sh.I;
     const long long pos0 = (long long)blockIdx.x * 2;
     const bool two = pos0 + 1 < A.nsys;                                 // an odd batch leaves the last wave one system
-    const long long first = A.sys0 + pos0;
+    const long long first = A.list ? A.list[A.sys0 + pos0] : A.sys0 + pos0;
+    const long long other = !two ? first : A.list ? A.list[A.sys0 + pos0 + 1] : first + 1;
+    const unsigned gap = (unsigned)(other - first);                     // in systems
     const bool live0 = A.active == nullptr || A.active[first] != 0;
-    const bool live1 = two && (A.active == nullptr || A.active[first + 1] != 0);
+    const bool live1 = two && (A.active == nullptr || A.active[other] != 0);
     if (!live0 && !live1) return;
     {
         const TileLane L(lane);
@@ -120,8 +122,8 @@ void k_factor_tile(FactorArgs A) {
     }
     wave_sync();
 
-    const int ray0 = (int)(first % sh.R), ray1 = two ? (int)((first + 1) % sh.R) : ray0;
-    const int spec0 = (int)(first / sh.R), spec1 = two ? (int)((first + 1) / sh.R) : spec0;
+    const int ray0 = (int)(first % sh.R), ray1 = (int)(other % sh.R);
+    const int spec0 = (int)(first / sh.R), spec1 = (int)(other / sh.R);
     const size_t base0 = (size_t)first * I * N;
     const double* const psi_b = A.psi + base0;
     const double* const ka_b = A.f.kappa_a + base0;
@@ -151,7 +153,7 @@ void k_factor_tile(FactorArgs A) {
         for (int j = 0; j < OWN; ++j) o[j].rhs = at(rhs_b, cz + P.own8(j));
         if (nes) {
             Tz = A.f.temp[(size_t)(P.second(two) ? ray1 : ray0) * I + P.clampz(z)];
-            amp = A.f.nes_amp[(size_t)(first + (P.second(two) ? 1 : 0)) * I + P.clampz(z)];
+            amp = A.f.nes_amp[(size_t)(P.second(two) ? other : first) * I + P.clampz(z)];
         }
     };
     auto radius = [&](const Place& P, int e) {
@@ -180,7 +182,7 @@ void k_factor_tile(FactorArgs A) {
     double r_t, r_l, r_b;                                               // edge radii: trailing, leading, next zone's far one
     double iV_prev = 0.0;
     {
-        const Place P(lane, two, I, N);
+        const Place P(lane, two, gap, I, N);
         const int z0 = P.zone_at(0);         // for the outer half the outer zone, or past it when it waits one step
         load_next(P, z0);
 #pragma unroll
@@ -231,7 +233,7 @@ void k_factor_tile(FactorArgs A) {
 
     for (int n = 0; n <= m; ++n) {
         const int ln = opaque_lane();
-        const Place P(ln, two, I, N);
+        const Place P(ln, two, gap, I, N);
         const TileLane& L = P.L;
         const bool half = P.half;
         const double sgn = P.sgn;
@@ -434,10 +436,10 @@ void k_factor_tile(FactorArgs A) {
     }
 
     // ---- growth guard and zero pivots of each system (both halves)
-    const Place P(opaque_lane(), two, I, N);
+    const Place P(opaque_lane(), two, gap, I, N);
     const TileLane& L = P.L;
     const bool live = (L.g >> 1) ? live1 : live0;
-    const long long sys = first + (P.second(two) ? 1 : 0);
+    const long long sys = P.second(two) ? other : first;
     const unsigned long long bad = guard.bad;
     const bool skip = (bad & ((L.g >> 1) ? 0xFF00FF00FF00FF00ull : 0x00FF00FF00FF00FFull)) != 0;
     const bool lead = (lane & 0x37) == 0;                                 // first lane of each system
@@ -451,8 +453,8 @@ void k_factor_tile(FactorArgs A) {
     double x[T];
 #pragma unroll
     for (int s = 0; s < T; ++s) {
-        const double other = __shfl_xor(y[s], 4);                          // read with every lane active
-        x[s] = P.half ? other : y[s];
+        const double met = __shfl_xor(y[s], 4);                            // read with every lane active
+        x[s] = P.half ? met : y[s];
     }
     double* const out_b = (A.psi_out ? A.psi_out : A.x) + base0;
     double* const dx_b = A.psi_out && A.dx ? A.dx + base0 : nullptr;

@@ -676,7 +676,7 @@ void k_factor_wave(FactorArgs A) {
     __shared__ int s_bad[2];
     const int lane = threadIdx.x & 63;
     const bool half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // the half coming from the outer edge
-    const long long sys = A.sys0 + blockIdx.x;
+    const long long sys = A.list ? A.list[A.sys0 + blockIdx.x] : A.sys0 + blockIdx.x;
     if (A.active && A.active[sys] == 0) return;                            // both wavefronts
     const Shape& sh = A.sh;
     const int N = sh.N, I = sh.I;

@@ -61,10 +61,13 @@ struct FactorArgs {
     double growth_limit;      // largest |multiplier| accepted with diagonal pivots
     void* wsC;                // [batch][I][NT][NT] factors (element type of the kernel)
     void* wsY;                // [batch][I][NT]
-    long long sys0;           // first system of the batch
-    long long nsys;           // systems in the batch
+    long long sys0;           // first system (position) of the batch
+    long long nsys;           // systems (positions) in the batch
     int skip_if_window = 0;   // quad kernel, exp2 NES form: do nothing when the energy grid admits the
                               // windowed form (launched beside the windowed kernel)
+    long long total;          // systems (positions) of all batches
+    const int* list = nullptr;  // FP64 diagonal-pivot kernels: the system at each position, in ascending order
+                              // (nullable: position = system); factor slots then follow the position
 };
 
 hipError_t launch_setup(const double* e_edge, const double* nes_g, int N, Consts* out, hipStream_t st);
@@ -90,6 +93,12 @@ enum FactorKernel : int {
     kFactorQuadBf16x3 = 4,
     kFactorQuadBf16 = 5
 };
+// Whether a Newton update of this many systems, for which float32 would do, is the faster in FP64
+bool factor_in_fp64(const Shape& sh, long long systems);
+// Whether the FP64 diagonal-pivot launch of this many systems takes them through a list
+bool factor_takes_list(const Shape& sh, long long systems);
+// FP64 slots of one system per launch that a workspace of so many bytes holds
+long long factor_fp64_slots(const Shape& sh, size_t bytes);
 hipError_t launch_factor(const FactorArgs& a, bool fp32, bool transpose, bool pivot, hipStream_t st,
                          int kernel = kFactorQuadMfma);
 bool launch_factor_quad(const FactorArgs& a, hipStream_t st, int kernel);
@@ -107,6 +116,8 @@ hipError_t launch_lum_seed(const Shape& sh, const double* r_edge, const double* 
 hipError_t launch_final_flags(long long n, const double* res, const double* tgt, double rtol, int* flags,
                               hipStream_t st);
 hipError_t launch_sys_absmax(const double* v, long long nsys, long long per_sys, double* out, hipStream_t st);
+// the indices of the set entries in ascending order, and their number
+hipError_t launch_list_active(const int* active, long long n, int* list, int* count, hipStream_t st);
 hipError_t launch_count_active(const int* active, long long n, int* count, hipStream_t st);
 
 // psi += (alpha/2 - alpha) dx and alpha /= 2 for systems with backtrack set (which is cleared)

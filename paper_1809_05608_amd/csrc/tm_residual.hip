@@ -792,6 +792,38 @@ __global__ __launch_bounds__(kBlock) void k_count(const int* __restrict__ active
     if (threadIdx.x == 0) *count = (int)s;
 }
 
+// One block: each wavefront counts its stretch, then writes the indices behind those of the stretches before it.
+__global__ __launch_bounds__(1024) void k_list(const int* __restrict__ active, long long n, int* __restrict__ list,
+                                               int* __restrict__ count) {
+    __shared__ int s_n[16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const long long len = ((n + 1023) / 1024) * 64, lo = wave * len, hi = min(n, lo + len);
+    int mine = 0;
+    for (long long j = lo + lane; j < hi; j += 64) mine += active[j] != 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+    if (lane == 0) s_n[wave] = mine;
+    __syncthreads();
+    int at = 0;
+    for (int w = 0; w < 16; ++w) {
+        if (w == wave) mine = at;
+        at += s_n[w];
+    }
+    for (long long j0 = lo; j0 < hi; j0 += 64) {
+        const long long j = j0 + lane;
+        const bool on = j < hi && active[j] != 0;
+        const unsigned long long m = __ballot(on);
+        if (on) list[mine + __popcll(m & ((1ull << lane) - 1))] = (int)j;
+        mine += __popcll(m);
+    }
+    if (threadIdx.x == 0) *count = at;
+}
+
+hipError_t launch_list_active(const int* active, long long n, int* list, int* count, hipStream_t st) {
+    hipLaunchKernelGGL(k_list, dim3(1), dim3(1024), 0, st, active, n, list, count);
+    return hipGetLastError();
+}
+
 hipError_t launch_count_active(const int* active, long long n, int* count, hipStream_t st) {
     hipLaunchKernelGGL(k_count, dim3(1), dim3(kBlock), 0, st, active, n, count);
     return hipGetLastError();
