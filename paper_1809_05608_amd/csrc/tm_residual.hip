@@ -1,13 +1,13 @@
 // FP64 kernels of libtm over cells: grid constants, residual with per-system norms and
 // conservation sums, debug Jacobian blocks, and the adjoint vector-Jacobian product.
 //
-// Mapping of the residual and VJP kernels: one 256-thread block per (species, ray) system,
-// one thread per cell (zone, group) of a chunk of zones; each edge flux is computed once
-// and shared through LDS, and the block reduces per-system quantities in a fixed order
-// (deterministic, no atomics).
+// Mapping of the residual and VJP kernels: one 256-thread block per (species, ray) system, a chunk
+// of zones at a time; each edge flux is computed once, and the block reduces per-system quantities
+// in a fixed order (deterministic, no atomics).
 #include <algorithm>
 
 #include "tm_kernels.hpp"
+#include "tm_tile.hpp"
 
 namespace tmk {
 
@@ -130,44 +130,135 @@ __device__ __forceinline__ double inv_mfp(const Fields& f, size_t c) {
 
 // ---------------------------------------------------------------- residual / statistics
 
-// Mapping: one block per system.  The 256 threads form RZ = 256/NT rows of NT groups (thread =
-// cell, so every global access is coalesced); row r of a chunk holds zone z0 - 1 + r, and the
-// interior rows z0 .. z0 + RZ - 3 are the chunk's output zones, the first and last rows being
-// halo.  Per chunk: every cell brings psi and its transport opacity (one reciprocal for lambda)
-// to LDS, together with the chunk's zone edges, temperatures and NES amplitudes (one value per
-// thread); every edge flux is computed once, by the cell below the edge, into LDS; then each
-// output cell assembles G from the two edge fluxes of its zone, emission/absorption and the
-// O(N) NES sums over its zone's LDS row.  The loads of the next chunk are issued before the
-// current chunk is processed, so the memory latency overlaps the arithmetic (the barriers wait
-// for LDS traffic only).  The NES shape matrix is staged once per block.  Besides max|G| the
-// kernel computes the rounding level of G (32 ulp of the largest per-cell sum of term
-// magnitudes plus |psi| |dG/dpsi|), below which the Newton stopping rule does not ask for
-// further progress.
-// LAPSE and GEO compile the lapse factors and the neutrinosphere options (limiter 2, outer boundary 2)
-// in; the plain instance leaves their registers out (127 instead of 131 VGPRs: four waves per SIMD
-// instead of three).
-template <int NT, bool LAPSE, bool GEO>
-__global__ __launch_bounds__(kBlock) void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs,
-                                                     const double* __restrict__ psi_n,
-                                                     const double* __restrict__ psi, double* __restrict__ G_out,
-                                                     double g_sign, ResidualOut out) {
-    constexpr int RZ = kBlock / NT;             // rows per chunk (zones incl. one halo on each side)
-    constexpr int ZB = RZ - 2;                  // output zones per chunk
-    constexpr int PS = NT + 1;                  // padded LDS row stride (conflict-free column reads)
-    static_assert(3 * RZ + 2 <= kBlock, "one zone value per thread");
-    __shared__ double s_P[NT * PS];
-    __shared__ double s_psi[RZ][PS];
-    __shared__ double2 s_pq[RZ][NT];            // psi and 1 - psi of the row (the NES sums read both at once)
-    __shared__ double s_lam[RZ][PS];
-    __shared__ double s_d[RZ][PS];
-    __shared__ double s_H[RZ][PS];              // flux at the upper edge of the row's zone
-    __shared__ double s_du[RZ][PS];             // its derivative with respect to the lower zone
-    __shared__ double s_dv[RZ][PS];             // ... and to the upper zone
-    __shared__ double s_z[3 * RZ + 2];          // edges z0-1 .. z0+RZ, then T and amp of the rows
+// Mapping: one block per system, its four wavefronts taking a quarter of the ray each, in chunks of 16 zones.
+// Lane 16 a + j holds groups a, 4 + a, 8 + a, ... of the chunk's zone j: the natural order of the 4 x 4 x 4
+// matrix products with the sixteen zones as columns.  The NES sums over k' are products of the constant shape
+// matrix with vectors per zone, so they go to the matrix cores, tile by tile (nes_sums); a neighbouring zone's
+// value is one lane away (two DPP moves); LDS holds only the constants.  Each edge flux is computed once, by the
+// zone below the edge; a chunk's last row serves as the upper neighbour only, and the flux below its first row
+// comes from the chunk before.
+// The sums over k' in Horner form, one cell per thread, took 38 steps of three LDS reads (32 bytes a lane) and were
+// bound by LDS; now vector issue (63% of the cycles) and memory share the time: 32768 systems of 540 zones x 20
+// groups 7.3 -> 4.6 ms (48 bytes a cell once: 3.9 ms at the 4.4 TB/s of a copy), with the geometric options 9.6 ->
+// 5.1, 16384 systems of 300 x 32 4.5 -> 2.7, of 300 x 12 1.0 -> 0.86, 720 of 540 x 20 0.26 -> 0.14.  Loading in the
+// layout of the sums instead (32-byte pieces, no way through LDS) took 6.1 ms, most of it in the address units; a
+// chunk's loads one chunk ahead, at two wavefronts a SIMD instead of three, 5.4.
+// Besides max|G| the kernel computes the rounding level of G (32 ulp of the largest per-cell sum of term
+// magnitudes plus |psi| |dG/dpsi|), below which the Newton stopping rule does not ask for further progress.
+
+// A value from the neighbouring zone's lane: j + 1 (row 15 gets its own), or j - 1 with `first` in row 0.
+__device__ __forceinline__ double zone_up(double v) {
+    const long long w = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp((int)w, (int)w, 0x101, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(w >> 32), (int)(w >> 32), 0x101, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double zone_down(double v, double first) {
+    const long long w = __double_as_longlong(v), f = __double_as_longlong(first);
+    const int lo = __builtin_amdgcn_update_dpp((int)f, (int)w, 0x111, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(f >> 32), (int)(w >> 32), 0x111, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// 1/sqrt(x) from the hardware estimate (about 2^-22) and one cubic step: y + y e (1/2 + 3/8 e), e = 1 - x y^2.
+__device__ __forceinline__ double rsqrt_newton(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y, e * fma(e, 0.375, 0.5), y);
+}
+
+// Element at a byte offset from a wave-uniform base (scalar base, 32-bit lane offset).
+template <typename D>
+__device__ __forceinline__ D& at(D* base, unsigned off) {
+    return *(D*)((uintptr_t)base + off);
+}
+
+template <int T>
+struct NesLds {
+    double P[T * T * 16];          // tile (t, s) as an A operand: P[4t + b][4s + a] at 4a + b
+    double near[T][6][4];          // P[k][k - n] (n = 1..3), then P[k][k + n], of row a of tile t
+};
+
+// The two NES sums of every group of 16 zones (without amp), eq. d8b with the detailed-balance factor
+// exp(-|eps_k - eps_k'|/T) as a product of neighbour factors d_j = exp(-(eps_{j+1} - eps_j)/T), all at most 1:
+//   sin_k  = sum_{k' > k} P psi_k'       + sum_{k' < k} P d_{k'} .. d_{k-1} psi_k'
+//   sout_k = sum_{k' < k} P (1 - psi_k') + sum_{k' > k} P d_k .. d_{k'-1} (1 - psi_k').
+// Between tiles of four groups the product splits into F_k (from the tile's first group to k), R_k (from k to the
+// next tile's first group) and the whole tiles between, R of their first groups, applied as the sum passes them.
+// Inside a tile the vector is shifted one group at a time, times d.
+template <int T>
+__device__ __forceinline__ void nes_sums(const NesLds<T>& sm, const double (&p)[T], const double (&d)[T], int a, int b,
+                                         int ab, double (&sin_)[T], double (&sout)[T]) {
+    const double to_up = a == b + 1 ? 1.0 : 0.0, to_dn = a + 1 == b ? 1.0 : 0.0;    // shift matrices, A operands
+    double F[T], R[T], W[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const double d0 = mfma4(a == 0 ? 1.0 : 0.0, d[t], 0.0), d1 = mfma4(a == 1 ? 1.0 : 0.0, d[t], 0.0);
+        const double d2 = mfma4(a == 2 ? 1.0 : 0.0, d[t], 0.0), d3 = mfma4(a == 3 ? 1.0 : 0.0, d[t], 0.0);
+        const double lo = d0 * d1, hi = d2 * d3;
+        W[t] = lo * hi;
+        const double f3 = lo * d2, r1 = d1 * hi;        // both arms of every choice are at hand: no branches
+        const double f01 = a == 0 ? 1.0 : d0, f23 = a == 2 ? lo : f3;
+        const double r01 = a == 0 ? W[t] : r1, r23 = a == 2 ? hi : d3;
+        F[t] = a < 2 ? f01 : f23;
+        R[t] = a < 2 ? r01 : r23;
+    }
+    double dn[T], up[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) sin_[t] = sout[t] = dn[t] = up[t] = 0.0;
+#pragma unroll
+    for (int s = 0; s < T; ++s) {                       // sources below: t > s
+        __builtin_amdgcn_sched_barrier(0);
+        const double q = R[s] * p[s], h = 1.0 - p[s];
+#pragma unroll
+        for (int t = s + 1; t < T; ++t) {
+            const double P = sm.P[(t * T + s) * 16 + ab];
+            dn[t] = mfma4(P, q, s > 0 ? dn[t] * W[s] : 0.0);
+            sout[t] = mfma4(P, h, sout[t]);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = T - 1; s >= 0; --s) {                  // sources above: t < s
+        __builtin_amdgcn_sched_barrier(0);
+        const double h = 1.0 - p[s], q = F[s] * h;
+#pragma unroll
+        for (int t = s - 1; t >= 0; --t) {
+            const double P = sm.P[(t * T + s) * 16 + ab];
+            up[t] = mfma4(P, q, s < T - 1 ? up[t] * W[s] : 0.0);
+            sin_[t] = mfma4(P, p[s], sin_[t]);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {                       // inside the tile
+        __builtin_amdgcn_sched_barrier(0);
+        const double P = sm.P[(t * T + t) * 16 + ab], h = 1.0 - p[t];
+        sin_[t] = mfma4(a > b ? P : 0.0, p[t], sin_[t]);
+        sout[t] = mfma4(a < b ? P : 0.0, h, sout[t]);
+        double x = F[t] * dn[t], u = p[t], y = R[t] * up[t], v = h;
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+            u = mfma4(to_dn, d[t] * u, 0.0);
+            x = fma(sm.near[t][n][a], u, x);
+            v = d[t] * mfma4(to_up, v, 0.0);
+            y = fma(sm.near[t][3 + n][a], v, y);
+        }
+        sin_[t] += x;
+        sout[t] += y;
+    }
+}
+
+// GEO compiles the neutrinosphere options (limiter 2, outer boundary 2) in.
+template <int T, bool GEO>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(T <= 3 ? 4 : T <= 6 ? 3 : 2)))
+void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double* __restrict__ psi_n,
+                const double* __restrict__ psi, double* __restrict__ G_out, double g_sign, ResidualOut out) {
+    constexpr int NT = 4 * T;
+    __shared__ NesLds<T> sm;
+    __shared__ double s_W[NT], s_We[NT], s_de[NT], s_rnu[GEO ? NT : 1];
+    constexpr int PS = NT + 1;                            // row stride: the 16 rows of a group in different banks
+    __shared__ double s_cell[kBlock / 64][4][16 * PS + 1];    // a chunk's psi, then psi_n, then G; kappa_a, eta, kappa_s
+    __shared__ double2 s_edge[kBlock / 64][T][4];         // flux and derivative at the edge above row 14
     __shared__ double red[kBlock / 64];
-    double* const s_re = s_z;
-    double* const s_T = s_z + RZ + 2;
-    double* const s_amp = s_z + 2 * RZ + 2;
     const long long sys = blockIdx.x;
     if (out.mode == kResTrial && out.pending[sys] == 0) return;         // no trial to evaluate
     if (out.mode == kResEval && out.pending && out.pending[sys % sh.R] == 0) return;
@@ -176,201 +267,192 @@ __global__ __launch_bounds__(kBlock) void k_residual(Shape sh, Fields f, const C
     const double* re = f.r_edge + (size_t)ray * (I + 1);
     const double c = sh.c_dt;
     const bool diff = sh.terms & kDiffusion, emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
-    const int t = threadIdx.x, zl = t / NT, k = t - zl * NT;
-    const bool tile = zl < RZ;
-    const bool lane_ok = tile && k < N;
-    const bool out_row = zl >= 1 && zl <= RZ - 2;
+    const bool geo = GEO && (sh.limiter == 2 || sh.outer_bc == 2);      // neutrinosphere radii in use
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-    if (nes)
-        for (int j = t; j < NT * NT; j += kBlock) s_P[(j / NT) * PS + (j % NT)] = cs->P[j / NT][j % NT];
+    if (nes) {
+        for (int x = threadIdx.x; x < T * T * 16; x += kBlock) {
+            const int tile = x / 16, ka = (x % 16) / 4, kb = x % 4;
+            sm.P[x] = cs->P[4 * (tile / T) + kb][4 * (tile % T) + ka];
+        }
+        for (int x = threadIdx.x; x < T * 24; x += kBlock) {
+            const int n = (x / 4) % 6, row = x % 4, k = 4 * (x / 24) + row;
+            const int col = n < 3 ? row - 1 - n : row + n - 2;           // within the tile
+            sm.near[x / 24][n][row] = col >= 0 && col < 4 ? cs->P[k][k - row + col] : 0.0;
+        }
+    }
+    if (threadIdx.x < NT) {
+        const int k = threadIdx.x;
+        s_W[k] = k < N ? cs->W[k] : 0.0;
+        s_We[k] = k < N ? cs->W[k] * cs->eps[k] : 0.0;
+        s_de[k] = k + 1 < N ? cs->de[k] : 0.0;
+        if (geo) s_rnu[k] = k < N ? f.r_nu[(size_t)(sys / sh.R) * N + k] : 0.0;
+    }
+    __syncthreads();
 
     double gmax = 0.0, gscale = 0.0;
     int bad = 0;
     double s_n = 0.0, s_nold = 0.0, s_e = 0.0, s_q = 0.0, s_nes = 0.0, s_b = 0.0;
-    const double Wk = lane_ok ? cs->W[k] : 0.0;
-    const double epsk = lane_ok ? cs->eps[k] : 0.0;
-    const bool geo = GEO && (sh.limiter == 2 || sh.outer_bc == 2);   // neutrinosphere radii in use
-    const double rnuk = (geo && lane_ok) ? f.r_nu[(size_t)(sys / sh.R) * N + k] : 0.0;
-    const double dek = (lane_ok && k + 1 < N) ? cs->de[k] : 0.0;
-    const size_t sys_cell0 = (size_t)sys * I * N;
+    const size_t cells = (size_t)sys * I * N;
+    const double* const zT = f.temp ? f.temp + (size_t)ray * I : re;
+    const double* const zA = f.nes_amp ? f.nes_amp + (size_t)sys * I : re;
 
-    // per-thread inputs of one chunk: the cell's fields and one zone value
-    struct In {
-        double p, ka, et, ks, pn, zv;
-    };
-    // Every load is issued unconditionally from a clamped, in-bounds address and the value selected
-    // afterwards: straight-line code lets the wait for a chunk's data count exactly the loads
-    // issued after it, instead of draining the memory pipe.
-    auto load = [&](int z0, In& v) {
-        const int i = z0 - 1 + zl;
-        const bool in_zone = lane_ok && i >= 0 && i < I;
-        const bool outc = in_zone && out_row;
-        const size_t cb = sys_cell0 + (in_zone ? (size_t)i * N + k : 0);
-        const double lp = psi[cb], lka = f.kappa_a[cb], let = f.eta[cb], lks = f.kappa_s[cb], lpn = psi_n[cb];
-        const bool opac = diff ? in_zone : (emabs && outc);
-        v.p = (diff ? in_zone : outc) ? lp : 0.0;
-        v.ka = opac ? lka : 0.0;
-        v.et = opac ? let : 0.0;
-        v.ks = (diff && in_zone) ? lks : 0.0;
-        v.pn = outc ? lpn : 0.0;
-        const double* src = re;
-        bool zok = false;
-        double zdef = 0.0;
-        if (t < RZ + 2) {
-            const int j = z0 - 1 + t;
-            zok = j >= 0 && j <= I;
-            src = re + (zok ? j : 0);
-        } else if (t < 2 * RZ + 2) {
-            const int j = z0 - 1 + (t - RZ - 2);
-            zok = nes && j >= 0 && j < I;
-            src = zok ? f.temp + (size_t)ray * I + j : re;
-            zdef = 1.0;
-        } else if (t < 3 * RZ + 2) {
-            const int j = z0 - 1 + (t - 2 * RZ - 2);
-            zok = nes && j >= 0 && j < I;
-            src = zok ? f.nes_amp + (size_t)sys * I + j : re;
+    // this wavefront's zones lo .. hi - 1; row 0 of its first chunk is the zone below them
+    const int per = (I + 3) / 4, lo = min(I, wave * per), hi = min(I, lo + per);
+    if ((threadIdx.x & 63) < 4 * T)                      // the edge below zone 0 has zero flux
+        s_edge[wave][(threadIdx.x & 63) >> 2][threadIdx.x & 3] = make_double2(0.0, 0.0);
+    const int zf = lo == hi ? hi : lo > 0 ? lo - 1 : 0;
+    const float iN = 1.0f / (float)N;
+    for (int z0 = zf; z0 < hi; z0 += 15) {
+        // what derives from the lane id, the constants in LDS among it, is fetched again for each chunk
+        const int lane = opaque_lane(), a = lane >> 4, j = lane & 15, b = lane & 3, ab = 4 * a + b;
+        const int i = z0 + j, ic = min(i, I - 1);
+        const bool out_row = j < 15 && i >= lo && i < hi;
+        // a chunk's cells are contiguous: loaded and stored in order, turned into zones by groups in LDS
+        const size_t chunk = cells + (size_t)z0 * N;
+        const int last = min(16, I - z0) * N - 1;
+        double nx[5][T];
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+            const unsigned o = 8u * (unsigned)min(64 * q + lane, last);
+            nx[0][q] = at(psi + chunk, o);
+            nx[1][q] = at(f.kappa_a + chunk, o);
+            nx[2][q] = at(f.eta + chunk, o);
+            nx[3][q] = at(f.kappa_s + chunk, o);
+            nx[4][q] = at(psi_n + chunk, o);
         }
-        const double lz = *src;
-        v.zv = zok ? lz : zdef;
-    };
-
-    In cur;
-    load(0, cur);
-    for (int z0 = 0; z0 < I; z0 += ZB) {
-        In nxt;
-        load(z0 + ZB, nxt);                                 // in flight while this chunk is processed
-        const int i = z0 - 1 + zl;                          // this row's zone (may be a halo or outside)
-        const bool in_zone = lane_ok && i >= 0 && i < I;
-        const double p = cur.p;
-        const double lam = (diff && in_zone) ? drcp(cur.ka + cur.et + cur.ks) : 0.0;
-        __syncthreads();                                    // previous chunk done with the LDS rows
-        if (tile) {
-            s_psi[zl][k] = p;
-            if (nes) s_pq[zl][k] = make_double2(p, 1.0 - p);
-            s_lam[zl][k] = lam;
+        auto slot = [&](int q) {                              // of cell 64 q + lane: row x / N, group x % N
+            const int x = 64 * q + lane, row = (int)(((float)x + 0.5f) * iN);
+            return row < 16 ? row * PS + x - row * N : 16 * PS;      // past the chunk: one spare element
+        };
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+            const int o = slot(q);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s_cell[wave][v][o] = nx[v][q];
         }
-        if (t < 3 * RZ + 2) s_z[t] = cur.zv;
-        __syncthreads();
-        if (tile) {
-            s_d[zl][k] = (nes && in_zone && out_row && k + 1 < N) ? exp(-dek * drcp(s_T[zl])) : 0.0;
-            // flux at the upper edge of this row's zone, computed once per edge
-            if (diff) {
-                double H = 0.0, du = 0.0, dv = 0.0;
-                if (in_zone && zl + 1 < RZ) {
-                    if (i + 1 < I) {
-                        const double rlo = s_re[zl], rhi = s_re[zl + 1], rp = s_re[zl + 2];
-                        const double D = 0.5 * (rhi + rp) - 0.5 * (rlo + rhi);
-                        const EdgeFlux e = edge_flux(p, s_psi[zl + 1][k], sqrt(lam * s_lam[zl + 1][k]), D,
-                                                     sh.psi_floor, sh.limiter,
-                                                     (GEO && sh.limiter == 2) ? limb_factor(rhi, rnuk) : -1.0);
-                        H = e.H;
-                        du = e.dHu;
-                        dv = e.dHv;
-                    } else if (sh.outer_bc == 1) {
-                        H = p;                              // free streaming, eq. a22 limit
-                        du = 1.0;
-                    } else if (GEO && sh.outer_bc == 2) {   // ghost zone of eq. a62af
-                        const double rlo = s_re[zl], rhi = s_re[zl + 1];
-                        const Ghost gh = outer_ghost(rlo, rhi, rnuk);
-                        const EdgeFlux e = edge_flux(p, gh.ratio * p, lam, gh.D, sh.psi_floor, sh.limiter,
-                                                     sh.limiter == 2 ? limb_factor(rhi, rnuk) : -1.0);
-                        H = e.H;
-                        du = e.dHu + gh.ratio * e.dHv;
-                    }
-                }
-                s_H[zl][k] = H;                             // the edge below zone 0 has zero flux
-                s_du[zl][k] = du;
-                s_dv[zl][k] = dv;
-            }
+        const double rlo = re[ic], rhi = re[ic + 1], rp = re[min(ic + 2, I)];
+        const double amp = nes ? zA[ic] : 0.0, Tz = nes ? zT[ic] : 1.0;
+        wave_sync();
+        double p[T];                                          // padding groups repeat the last one
+#pragma unroll
+        for (int t = 0; t < T; ++t) p[t] = s_cell[wave][0][j * PS + (t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1))];
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < T; ++q) s_cell[wave][0][slot(q)] = nx[4][q];
+        wave_sync();
+        double sin_[T], sout[T];
+        if (nes) {
+            const double iT = drcp(Tz);
+            const ExpCoef coef = exp_coef();
+            double d[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t) d[t] = exp_nonpos(-s_de[4 * t + a] * iT, coef);
+            nes_sums<T>(sm, p, d, a, b, ab, sin_, sout);
         }
-        __syncthreads();
-        const In now = cur;
-        cur = nxt;
-        if (!in_zone || !out_row) continue;
-
-        const size_t cb = sys_cell0 + (size_t)i * N + k;
-        const double pn = now.pn;
-        double G = p - pn;
-        double scale = fabs(p) + fabs(pn);
-        const double rlo = s_re[zl], rhi = s_re[zl + 1];
-        double V = shell_volume(rlo, rhi);
-        double A_lo = rlo * rlo, A_hi = rhi * rhi;
-        if (LAPSE && f.lapse) {                             // eq. a58 times a_i c dt: V / a^3 and A / a^2
-            const double a0 = f.lapse[(size_t)ray * I + i];
-            const double e0 = f.lapse_edge[(size_t)ray * (I + 1) + i], e1 = f.lapse_edge[(size_t)ray * (I + 1) + i + 1];
+        double V = shell_volume(rlo, rhi), A_lo = rlo * rlo, A_hi = rhi * rhi;
+        if (f.lapse) {                                      // eq. a58 times a_i c dt: V / a^3 and A / a^2
+            const double a0 = f.lapse[(size_t)ray * I + ic];
+            const double e0 = f.lapse_edge[(size_t)ray * (I + 1) + ic], e1 = f.lapse_edge[(size_t)ray * (I + 1) + ic + 1];
             V /= a0 * a0 * a0;
             A_lo /= e0 * e0;
             A_hi /= e1 * e1;
         }
-        double Hh = 0.0;
-        double jd = 1.0;                                    // |dG_ik/dpsi_ik| bound, for the rounding level
-        if (diff) {
-            const double Hlo = s_H[zl - 1][k], dlo = s_dv[zl - 1][k];
-            Hh = s_H[zl][k];
-            const double dhi = s_du[zl][k];
-            const double iV = drcp(V);
-            G += c * (A_hi * Hh - A_lo * Hlo) * iV;
-            scale += c * (fabs(A_hi * Hh) + fabs(A_lo * Hlo)) * iV;
-            jd += c * (A_hi * fabs(dhi) + A_lo * fabs(dlo)) * iV;
-        }
-        const double ka = now.ka, et = now.et;
-        if (emabs) {
-            G += c * (ka * p - et * (1.0 - p));
-            scale += c * (fabs(ka * p) + fabs(et * (1.0 - p)));
-            jd += c * (ka + et);
-        }
-        double S = 0.0;
-        if (nes) {
-            const double amp = s_amp[zl];
-            // The group index goes through an opaque copy: the lane masks of the two loops are then formed here
-            // (one compare per term) instead of being hoisted out of the zone loop as 38 live scalar masks.
-            int kz = k;
-            asm volatile("" : "+v"(kz));
-            // k' > k: the out kernel carries exp(-(eps_k' - eps_k)/T) = prod_{j=k}^{k'-1} d_j.  The weighted sum
-            // of those products is taken in Horner form from the last group down, one multiply-add and one
-            // multiply per term: h <- (h + P_kk' (1 - psi_k')) d_{k'-1}.
-            double hup = 0.0, sin_ = 0.0;
+        const double iV = drcp(V), D = 0.5 * (rhi + rp) - 0.5 * (rlo + rhi);
+        double w_n = 0.0, w_old = 0.0, w_e = 0.0, w_q = 0.0, w_nes = 0.0;    // the zone's sums over its groups
 #pragma unroll
-            for (int kp = NT - 1; kp >= 1; --kp) {
-                if (kp > kz) {                         // padding groups add exact zeros (P = 0 there)
-                    const double Pk = s_P[k * PS + kp];
-                    const double2 pq = s_pq[zl][kp];
-                    hup = fma(Pk, pq.y, hup) * s_d[zl][kp - 1];
-                    sin_ = fma(Pk, pq.x, sin_);
+        for (int t = 0; t < T; ++t) {
+            const int k = 4 * t + a;
+            const bool ok = t + 1 < T ? out_row : out_row && k < N;
+            __builtin_amdgcn_sched_barrier(0);
+            const int o = j * PS + 4 * t + a;
+            const double ka = s_cell[wave][1][o], et = s_cell[wave][2][o], ks = s_cell[wave][3][o], pn = s_cell[wave][0][o];
+            const double h = 1.0 - p[t], sig = ka + et;
+            double H = 0.0, du = 0.0, dv = 0.0, H_lo = 0.0, d_lo = 0.0;
+            if (diff) {
+                const double chi = sig + ks;
+                const double p_up = zone_up(p[t]), chi_up = zone_up(chi);
+                const double rnu = geo ? s_rnu[k] : 0.0;
+                if (i + 1 < I) {                            // mean free path at the edge: geometric mean
+                    const EdgeFlux e = edge_flux(p[t], p_up, rsqrt_newton(chi * chi_up), D, sh.psi_floor, sh.limiter,
+                                                 (GEO && sh.limiter == 2) ? limb_factor(rhi, rnu) : -1.0);
+                    H = e.H;
+                    du = e.dHu;
+                    dv = e.dHv;
+                } else if (sh.outer_bc == 1) {
+                    H = p[t];                               // free streaming, eq. a22 limit
+                    du = 1.0;
+                } else if (GEO && sh.outer_bc == 2) {       // ghost zone of eq. a62af
+                    const Ghost gh = outer_ghost(rlo, rhi, rnu);
+                    const EdgeFlux e = edge_flux(p[t], gh.ratio * p[t], drcp(chi), gh.D, sh.psi_floor, sh.limiter,
+                                                 sh.limiter == 2 ? limb_factor(rhi, rnu) : -1.0);
+                    H = e.H;
+                    du = e.dHu + gh.ratio * e.dHv;
                 }
+                const double2 below = s_edge[wave][t][a];
+                H_lo = zone_down(H, below.x);
+                d_lo = zone_down(dv, below.y);
+                wave_sync();
+                if (j == 14) s_edge[wave][t][a] = make_double2(H, dv);
             }
-            // k' < k: the in kernel carries exp(-(eps_k - eps_k')/T) = prod_{j=k'}^{k-1} d_j, in Horner form from
-            // group 0 up: h <- (h + P_kk' psi_k') d_k'
-            double hdn = 0.0, sout = hup;
+            if (!ok) continue;
+            // G = psi - psi_n + c dt (rest); size: the same sum of magnitudes; jd: |dG_ik/dpsi_ik| bound
+            double rest = 0.0, size = 0.0, jd = 0.0;
+            if (diff) {
+                const double up = A_hi * H, dn = A_lo * H_lo;
+                rest = (up - dn) * iV;
+                size = (fabs(up) + fabs(dn)) * iV;
+                jd = (A_hi * fabs(du) + A_lo * fabs(d_lo)) * iV;
+            }
+            double em = 0.0;
+            if (emabs) {
+                const double ab = ka * p[t], re_ = et * h;
+                em = ab - re_;
+                rest += em;
+                size += fabs(ab) + fabs(re_);
+                jd += sig;
+            }
+            double S = 0.0;
+            if (nes) {
+                const double in = h * sin_[t], ex = p[t] * sout[t];
+                S = in - ex;
+                rest = fma(-amp, S, rest);
+                size = fma(amp, fabs(in) + fabs(ex), size);
+                jd = fma(amp, fabs(sin_[t]) + fabs(sout[t]), jd);
+            }
+            const double G = fma(c, rest, p[t] - pn);
+            const double scale = fma(c, size, fabs(p[t]) + fabs(pn)) + fabs(p[t]) * fma(c, jd, 1.0);  // G per ulp of psi
+            bad |= !isfinite(G);
+            gmax = fmax(gmax, fabs(G));
+            gscale = fmax(gscale, scale);
+            s_cell[wave][0][o] = g_sign * G;
+            if (out.stats) {
+                const double Wk = s_W[k];
+                w_n = fma(Wk, p[t], w_n);
+                w_old = fma(Wk, pn, w_old);
+                w_e = fma(s_We[k], p[t], w_e);
+                w_q = fma(Wk, em, w_q);
+                w_nes = fma(Wk, S, w_nes);
+                if (i == I - 1 && diff) s_b = fma(Wk, H, s_b);
+            }
+        }
+        if (out.stats && out_row) {
+            s_n = fma(V, w_n, s_n);
+            s_nold = fma(V, w_old, s_nold);
+            s_e = fma(V, w_e, s_e);
+            s_q = fma(-c * V, w_q, s_q);
+            s_nes = fma(c * V * amp, w_nes, s_nes);
+        }
+        wave_sync();
+        if (G_out) {
+            const int x0 = (max(z0, lo) - z0) * N, x1 = (min(z0 + 15, hi) - z0) * N;      // the rows put out
 #pragma unroll
-            for (int kp = 0; kp < NT - 1; ++kp) {
-                if (kp < kz) {
-                    const double Pk = s_P[k * PS + kp];
-                    const double2 pq = s_pq[zl][kp];
-                    hdn = fma(Pk, pq.x, hdn) * s_d[zl][kp];
-                    sout = fma(Pk, pq.y, sout);
-                }
+            for (int q = 0; q < T; ++q) {
+                const int x = 64 * q + lane;
+                if (x >= x0 && x < x1) at(G_out + chunk, 8u * (unsigned)x) = s_cell[wave][0][slot(q)];
             }
-            sin_ += hdn;
-            S = amp * ((1.0 - p) * sin_ - p * sout);
-            G -= c * S;
-            scale += c * amp * (fabs(1.0 - p) * fabs(sin_) + fabs(p) * fabs(sout));
-            jd += c * amp * (fabs(sin_) + fabs(sout));
         }
-        scale += fabs(p) * jd;                              // G changes by jd * ulp(psi) per ulp of psi
-        bad |= !isfinite(G);
-        gmax = fmax(gmax, fabs(G));
-        gscale = fmax(gscale, scale);
-        if (G_out) G_out[cb] = g_sign * G;
-        if (out.stats) {
-            const double vw = V * Wk;
-            s_n = fma(vw, p, s_n);
-            s_nold = fma(vw, pn, s_nold);
-            s_e = fma(vw * epsk, p, s_e);
-            if (emabs) s_q = fma(c * vw, et * (1.0 - p) - ka * p, s_q);
-            if (nes) s_nes = fma(c * vw, S, s_nes);
-            if (i == I - 1 && diff) s_b = fma(Wk, Hh, s_b);
-        }
+        wave_sync();
     }
 
     const double res = block_max(gmax, red);
@@ -417,7 +499,7 @@ __global__ __launch_bounds__(kBlock) void k_residual(Shape sh, Fields f, const C
             }
         }
         if (out.stats) {
-            const double rout = re[I] * re[I] * (LAPSE ? lapse_edge_inv2(f, (size_t)ray * (I + 1) + I) : 1.0);
+            const double rout = re[I] * re[I] * lapse_edge_inv2(f, (size_t)ray * (I + 1) + I);
             const double b = c * rout * s_b;
             if (out.n_tot) out.n_tot[sys] = s_n;
             if (out.e_tot) out.e_tot[sys] = s_e;
@@ -889,16 +971,12 @@ hipError_t launch_residual(const Shape& sh, const Fields& f, const Consts* cs, c
     const long long nsys = (long long)sh.S * sh.R;
     if (sh.limiter == 2 || sh.outer_bc == 2) {
         TM_DISPATCH_NT(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_residual<NT, true, true>), dim3((unsigned)nsys), dim3(kBlock), 0, st, sh,
-                                          f, cs, psi_n, psi, G_out, g_sign, out));
-    } else if (f.lapse) {
-        TM_DISPATCH_NT(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_residual<NT, true, false>), dim3((unsigned)nsys), dim3(kBlock), 0, st, sh,
-                                          f, cs, psi_n, psi, G_out, g_sign, out));
+                       hipLaunchKernelGGL((k_residual<NT / 4, true>), dim3((unsigned)nsys), dim3(kBlock), 0, st, sh, f,
+                                          cs, psi_n, psi, G_out, g_sign, out));
     } else {
         TM_DISPATCH_NT(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_residual<NT, false, false>), dim3((unsigned)nsys), dim3(kBlock), 0, st, sh,
-                                          f, cs, psi_n, psi, G_out, g_sign, out));
+                       hipLaunchKernelGGL((k_residual<NT / 4, false>), dim3((unsigned)nsys), dim3(kBlock), 0, st, sh, f,
+                                          cs, psi_n, psi, G_out, g_sign, out));
     }
     return hipGetLastError();
 }

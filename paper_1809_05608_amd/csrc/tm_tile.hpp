@@ -52,7 +52,7 @@ __device__ __forceinline__ ExpCoef exp_coef() {
     return c;
 }
 __device__ __forceinline__ double exp_nonpos(double x, ExpCoef c) {
-    x = x > -800.0 ? x : -800.0;                   // the result is 0 from -746 on
+    x = x < -800.0 ? -800.0 : x;                   // the result is 0 from -746 on; NaN stays
     const double n = __builtin_rint(x * c[0]);
     const double r = fma(n, c[2], fma(n, c[1], x));
     double p = c[3];
