@@ -3,9 +3,13 @@
 // (eqs. a81a-a81d), and the remap after a change of the lapse (eqs. p1-p8).
 //
 // One thread per (species, ray, zone): its N groups are independent of every other zone.  A block of
-// 128 zones loads its psi rows into LDS with coalesced loads and stores the new psi the same way; each
-// thread reads its Eddington factors from HBM and keeps its net fluxes in registers (staging both rows
-// in LDS halves the blocks a CU holds, and the kernel needs the waves to hide its FP64 latency).  The target
+// 128 zones loads its Eddington factors and then its psi rows into the same LDS rows with coalesced loads and
+// stores the new psi the same way; a thread keeps its source edges, made from the factors, and its net
+// fluxes in registers (both rows in LDS at once would halve the blocks a CU holds, and the kernel needs the
+// waves to hide its FP64 latency).  Vector issue bounds it (77% of the cycles; 24 bytes a cell with Eddington
+// factors are half the time): 4096 rays x 4 species of 540 zones x 20 groups 2.13 -> 1.5 ms, from each thread
+// reading its own row of factors from memory, a division per element staged, a library square root and three
+// more reciprocals a group.  The target
 // grid is the shared e_edge (in the lapse mode everything is measured in units of the new local grid,
 // E/a^{n+1} times a^{n+1}; the remap is invariant under that common scale).  The source grid is the
 // target grid with every edge m multiplied by s_m:
@@ -32,6 +36,13 @@ namespace tmk {
 
 namespace {
 
+// sqrt(x) of a positive x from the hardware's 1/sqrt (about 2^-22) and one cubic step.
+__device__ __forceinline__ double sqrt_newton(double x) {
+    const double y = __builtin_amdgcn_rsq(x), s = x * y;
+    const double e = fma(-s, y, 1.0);
+    return fma(s, e * fma(e, 0.375, 0.5), s);
+}
+
 // per-zone description of the source grid and number factor
 struct EaZone {
     double c;       // N_k = c W_k psi_k
@@ -55,10 +66,24 @@ __global__ __launch_bounds__(kEaBlock) void k_energy_advect(EaArgs A) {
     const int nb = (int)min((long long)kEaBlock, A.nz - zs0);
     double* gP = A.psi + zs0 * N;
     const double* gH = A.edd ? A.edd + zs0 * N : nullptr;
-    for (int e = tid; e < nb * N; e += kEaBlock) {
-        const int r = e / N, k = e - r * N;
-        sP[r * LD + k] = gP[e];
-    }
+    // element e of the block's rows in LDS: row e / N, by a product (exact: e < 4096)
+    const float iN = 1.0f / (float)N;
+    auto slot = [&](int e) {
+        const int r = (int)(((float)e + 0.5f) * iN);
+        return r * LD + e - r * N;
+    };
+    auto stage = [&](const double* src) {
+        int e = tid;
+        for (; e + 3 * kEaBlock < nb * N; e += 4 * kEaBlock) {
+            const double v0 = src[e], v1 = src[e + kEaBlock], v2 = src[e + 2 * kEaBlock], v3 = src[e + 3 * kEaBlock];
+            sP[slot(e)] = v0;
+            sP[slot(e + kEaBlock)] = v1;
+            sP[slot(e + 2 * kEaBlock)] = v2;
+            sP[slot(e + 3 * kEaBlock)] = v3;
+        }
+        for (; e < nb * N; e += kEaBlock) sP[slot(e)] = src[e];
+    };
+    if (gH) stage(gH);
     __syncthreads();
     for (int k = tid; k < N; k += kEaBlock) {
         const double lo = sT[k], hi = sT[k + 1];
@@ -77,40 +102,42 @@ __global__ __launch_bounds__(kEaBlock) void k_energy_advect(EaArgs A) {
     }
     __syncthreads();
 
-    if (tid < nb) {
-        const long long zs = zs0 + tid;
-        const long long zi = zs % A.RI;                           // zone index r*I + i
-        EaZone z;
-        if (A.mode == kEaLapse) {
-            const double s = A.a_new[zi] / A.a_old[zi];
-            z.c = s * s * s;
-            z.s0 = s;
-            z.s1 = 0.0;
-        } else {
-            const double ao = A.a_old ? A.a_old[zi] : 1.0, an = A.a_new ? A.a_new[zi] : 1.0;
-            const double ro = A.rho_old ? A.rho_old[zi] : 1.0, rn = A.rho_new ? A.rho_new[zi] : 1.0;
-            const double dR = A.dlnR ? A.dlnR[zi] : 0.0, db = A.dlnb ? A.dlnb[zi] : 0.0;
-            z.c = (rn * an * an * an) / (ro * ao * ao * ao);
-            z.s0 = 1.0 + ((an / ao - 1.0) - dR);
-            z.s1 = db - dR;
-        }
-        double* rowP = sP + tid * LD;
-        const double* rowH = gH ? gH + tid * N : nullptr;
-        double Dn[NT];
-
-        // source edges S_m = s_m T_m (eq. a79 at edge m; the Eddington factor of an edge is the mean of
-        // its two groups, the end groups' own at the two ends)
-        double Sv[NT + 1];
+    const long long zs = zs0 + min(tid, nb - 1);
+    const long long zi = zs % A.RI;                               // zone index r*I + i
+    EaZone z;
+    if (A.mode == kEaLapse) {
+        const double s = A.a_new[zi] / A.a_old[zi];
+        z.c = s * s * s;
+        z.s0 = s;
+        z.s1 = 0.0;
+    } else {
+        const double ao = A.a_old ? A.a_old[zi] : 1.0, an = A.a_new ? A.a_new[zi] : 1.0;
+        const double ro = A.rho_old ? A.rho_old[zi] : 1.0, rn = A.rho_new ? A.rho_new[zi] : 1.0;
+        const double dR = A.dlnR ? A.dlnR[zi] : 0.0, db = A.dlnb ? A.dlnb[zi] : 0.0;
+        z.c = (rn * an * an * an) / (ro * ao * ao * ao);
+        z.s0 = 1.0 + ((an / ao - 1.0) - dR);
+        z.s1 = db - dR;
+    }
+    double* rowP = sP + tid * LD;
+    // source edges S_m = s_m T_m (eq. a79 at edge m; the Eddington factor of an edge is the mean of
+    // its two groups, the end groups' own at the two ends)
+    double Sv[NT + 1];
 #pragma unroll
-        for (int m = 0; m <= NT; ++m) {
-            if (m <= N) {
-                auto hh = [&](int k) { return rowH ? rowH[k] : 1.0 / 3.0; };
-                const double h = (m == 0) ? hh(0) : (m == N) ? hh(N - 1) : 0.5 * (hh(m - 1) + hh(m));
-                Sv[m] = (z.s0 - z.s1 * h) * sT[m];
-            } else {
-                Sv[m] = Sv[m - 1];
-            }
+    for (int m = 0; m <= NT; ++m) {
+        if (m <= N) {
+            auto hh = [&](int k) { return gH ? rowP[k] : 1.0 / 3.0; };
+            const double h = (m == 0) ? hh(0) : (m == N) ? hh(N - 1) : 0.5 * (hh(m - 1) + hh(m));
+            Sv[m] = (z.s0 - z.s1 * h) * sT[m];
+        } else {
+            Sv[m] = Sv[m - 1];
         }
+    }
+    __syncthreads();                                              // the Eddington factors have been read
+    stage(gP);
+    __syncthreads();
+
+    if (tid < nb) {
+        double Dn[NT];
 
         // window values (indices are compile-time after unrolling; entries die after their last use).
         // Index j + 2 holds group j, so the two ghost groups below are entries 0 and 1; groups at or above
@@ -134,7 +161,7 @@ __global__ __launch_bounds__(kEaBlock) void k_energy_advect(EaArgs A) {
                 Dv[gt] = w;
                 RW[gt] = rw;
                 ok = ok && (w > 0.0);
-                e_src += Nk * sqrt((S_hi * S_hi + S_hi * S_lo + S_lo * S_lo) * kThird);   // eq. p3, before
+                e_src += Nk * sqrt_newton((S_hi * S_hi + S_hi * S_lo + S_lo * S_lo) * kThird);   // eq. p3, before
                 e_n += Nk * sE[t];
             } else {
                 Av[gt] = Av[gt - 1];
@@ -172,9 +199,11 @@ __global__ __launch_bounds__(kEaBlock) void k_energy_advect(EaArgs A) {
                 const double sj = SL[g0], sj1 = SL[g1];
                 const double diff = aj1 - aj;
                 const double q = Q[g1];                           // 1 / (d0 + d1)
-                const double rB = drcp(2.0 * d0 + d1), rC = drcp(2.0 * d1 + d0);
+                // three reciprocals from one
+                const double wB = 2.0 * d0 + d1, wC = 2.0 * d1 + d0, wA = dm + d0 + d1 + d2, wBC = wB * wC;
+                const double rABC = drcp(wBC * wA), rA = rABC * wBC, rBC = rABC * wA, rB = rBC * wC, rC = rBC * wB;
                 double v = aj + d0 * q * diff +
-                           drcp(dm + d0 + d1 + d2) *
+                           rA *
                                (2.0 * d1 * d0 * q * ((dm + d0) * rB - (d2 + d1) * rC) * diff -
                                 d0 * (dm + d0) * rB * sj1 + d1 * (d1 + d2) * rC * sj);
                 v = fmax(v, fmin(aj, aj1));
@@ -271,10 +300,7 @@ __global__ __launch_bounds__(kEaBlock) void k_energy_advect(EaArgs A) {
         if (A.flags) A.flags[zs] = flags;
     }
     __syncthreads();
-    for (int e = tid; e < nb * N; e += kEaBlock) {
-        const int r = e / N, k = e - r * N;
-        gP[e] = sP[r * LD + k];
-    }
+    for (int e = tid; e < nb * N; e += kEaBlock) gP[e] = sP[slot(e)];
 }
 
 hipError_t launch_energy_advect(const EaArgs& a, hipStream_t st) {
