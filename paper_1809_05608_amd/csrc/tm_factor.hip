@@ -12,13 +12,13 @@ size_t factor_ws_bytes_per_system(int I, int N, bool fp32) {
     return (size_t)I * NT * (NT + 1) * es;
 }
 
-// Up to this many systems the two wavefronts of each have a SIMD to themselves (256 CUs of four), and what
-// counts is the time of one wavefront's step: half a system per wavefront (tm_factor_w.hip) is the faster, above
-// it four half systems per wavefront (tm_factor_t.hip), whose matrix operations have no idle rows.  Measured,
-// 540 zones x 20 groups: 6 systems 1.28 against 1.90 ms, 24: 1.45 against 2.00, 512: 1.99 against 2.00, 1024:
-// 2.20 against 2.23, 2048: 4.6 against 2.6; 300 x 12: 1024 systems 0.65 against 0.63, 2048 1.10 against 0.76.
-// The count is that of all batches: a batch takes the kernel that the whole would take.
-constexpr long long kWaveSystems = 512;
+// Up to this many systems, three workgroups to each of 256 CUs, what counts is the time of one wavefront's step: half
+// a system per pair of wavefronts (tm_factor_w.hip) is the faster, above it four half systems per wavefront
+// (tm_factor_t.hip), whose matrix operations have no idle rows.  Measured, 540 zones x 20 groups: 6 systems 0.93
+// against 1.90 ms, 24: 1.00 against 2.00, 512: 1.35 against 2.00, 720: 1.65 against 2.16, 1024: 2.35 against 2.23,
+// 1536: 3.1 against 2.3; 300 zones, 1024 systems: 8 groups 0.44 against 0.47, 12: 0.60 against 0.63, 28: 2.1 against
+// 2.4.  The count is that of all batches: a batch takes the kernel that the whole would take.
+constexpr long long kWaveSystems = 768;
 
 // Up to this many systems a float32 launch leaves the chip waiting for one wavefront's chain of zones, 16 systems
 // from one end: the FP64 kernels with two or half a system per wavefront from both ends are faster up to about

@@ -1,4 +1,4 @@
-// FP64 assembly + block elimination + solve with one wavefront per half ray: the Y_e-coupled blocks,
+// FP64 assembly + block elimination + solve with a wavefront per half ray: the Y_e-coupled blocks,
 // and the blocks of one species where there are few systems.
 //
 // A ray is eliminated from both ends at once by the two wavefronts of a workgroup (zones 0 .. m-1 upwards and
@@ -637,11 +637,12 @@ hipError_t launch_ye_factor_wave(const YeFactorArgs& a, hipStream_t st) {
 
 // ---------------------------------------------------------------- single species, few systems
 //
-// The same layout for an N x N block: 128 threads a system.  Few systems leave the chip idle, so a step of one
-// wavefront is all there is to it: five panels of 20 columns, the scattering terms and the owners' transport
-// coefficients come to about 1100 vector operations against the tile kernel's 1500 to 2200, and the loads of a
-// zone to a quarter.  24 systems of 540 zones x 20 groups: 2.00 ms on tiles, 1.45 here.
-
+// The same layout for an N x N block, and two wavefronts to a half: few systems leave the chip idle, so the time of
+// a step is that of its dependent operations.  Of these only the Schur term, the inversion and y depend on the zone
+// before; the rest of the block (transport coefficients, one exponential per entry, the diagonal) is made by the
+// half's second wavefront, on another SIMD, one zone ahead, and handed over in LDS with one barrier a step.
+// 540 zones x 20 groups, 24 systems: 2.00 ms on tiles, 1.45 with one wavefront to a half, 1.00 here; 512 systems
+// 2.00, 1.99, 1.35.
 namespace {
 
 template <int T>
@@ -651,19 +652,36 @@ struct SingleShape {
     static constexpr int FC = NT / 16, REM = NT % 16;
 };
 
+// A zone as its half's second wavefront hands it to the first: the block before elimination (lane by lane, in the
+// registers' order), the couplings to the previous and the next zone and the right-hand side.
+template <int T>
+struct ZoneBlock {
+    using C = SingleShape<T>;
+    double block[T * C::CN][64];
+    double sch[C::W], bco[C::W], g[C::W];
+};
+
 template <int T>
 struct SingleLds {
     using C = SingleShape<T>;
+    ZoneBlock<T> zone[2];              // of step n in n & 1
     double pan[4 * C::PR];
-    double psi[C::W], sch[C::W], bco[C::W], g[C::W], dg[C::W];
+    double psi[C::W], dg[C::W], g[C::W];
     double y[C::W];                    // y of the previous zone; x in the back substitution
 };
+
+// Barrier of the workgroup for what its wavefronts exchange through LDS; memory operations stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 }  // namespace
 
 // One (species, ray) system per workgroup, TRANS the transposed solve, EXT the lapse and the geometric options.
 template <int T, bool TRANS, bool EXT>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void k_factor_wave(FactorArgs A) {
     using X = SingleShape<T>;
     constexpr int NT = X::NT, CN = X::CN;
@@ -675,13 +693,15 @@ void k_factor_wave(FactorArgs A) {
     __shared__ double s_y[X::W], s_x[X::W];        // the outer half's y; x of the meeting zone
     __shared__ int s_bad[2];
     const int lane = threadIdx.x & 63;
-    const bool half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // the half coming from the outer edge
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool half = wave & 1;                                            // the half coming from the outer edge
+    const bool assembles = wave >> 1;                                      // the half's second wavefront
     const long long sys = A.list ? A.list[A.sys0 + blockIdx.x] : A.sys0 + blockIdx.x;
-    if (A.active && A.active[sys] == 0) return;                            // both wavefronts
+    if (A.active && A.active[sys] == 0) return;                            // all wavefronts
     const Shape& sh = A.sh;
     const int N = sh.N, I = sh.I;
     const bool diff = sh.terms & kDiffusion, emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
-    for (int j = threadIdx.x; j < NT * X::W; j += 128) {
+    for (int j = threadIdx.x; j < NT * X::W; j += 256) {
         const int r = j / X::W, q = j % X::W;
         sP[j] = q < NT ? A.cs->P[q][r] : 0.0;
         if (TRANS) sPt[j] = q < NT ? A.cs->P[r][q] : 0.0;
@@ -737,7 +757,8 @@ void k_factor_wave(FactorArgs A) {
     auto radius_nu = [&](int k) { return EXT && A.f.r_nu ? A.f.r_nu[(size_t)spec * N + k] : 1.0; };
     const int z0 = half ? I - 1 : 0;
     double psi, sig, lam, tc, to = 0.0, iV_prev = 0.0;                  // this zone; trailing edge
-    {
+    double r_t = 0.0, r_l = 0.0, r_b = 0.0;
+    if (assembles) {
         const int k = group(lane);
         load_next(k, z0);
         psi = n_psi;
@@ -746,30 +767,33 @@ void k_factor_wave(FactorArgs A) {
         tc = half ? outer(radius_nu(k), psi, lam) : 0.0;
         load_next(k, z0 + dir);
         load_zone(k, z0);
+        const int e0 = half ? I - 1 : 1;
+        r_t = A.f.r_edge[clampe(e0 - dir) + eb];
+        r_l = A.f.r_edge[clampe(e0) + eb];
+        r_b = A.f.r_edge[clampe(e0 + dir) + eb];
     }
-    const int e0 = half ? I - 1 : 1;
-    double r_t = A.f.r_edge[clampe(e0 - dir) + eb], r_l = A.f.r_edge[clampe(e0) + eb],
-           r_b = A.f.r_edge[clampe(e0 + dir) + eb];
+
 
     WaveBlock<T, CN> S;
 #pragma unroll
     for (int q = 0; q < T; ++q)
 #pragma unroll
         for (int C = 0; C < CN; ++C) S.set(q, C, 0.0);
-    if (lane < X::W) {
-        sm.psi[lane] = sm.sch[lane] = sm.bco[lane] = sm.g[lane] = sm.y[lane] = 0.0;
+    if (!assembles && lane < X::W) {
+        sm.psi[lane] = sm.g[lane] = sm.y[lane] = 0.0;
         sm.dg[lane] = 1.0;
+        for (int b = 0; b < 2; ++b) sm.zone[b].sch[lane] = sm.zone[b].bco[lane] = sm.zone[b].g[lane] = 0.0;
     }
-    wave_sync();
+    __syncthreads();
     TileGuard guard(A.growth_limit);
     constexpr size_t SZ = (size_t)NT * (NT + 1);                       // slot of a zone
     double* ws = reinterpret_cast<double*>(A.wsC) + (size_t)blockIdx.x * I * SZ;
     typedef double V2 __attribute__((ext_vector_type(2)));
 
-    // C and y of the zone that step n - 1 finished, in the middle of the next step (see k_ye_factor_wave)
+    // C and y of the zone of step n
     auto store = [&](int n, int ln) {
         const int jc = ln & 15, a = ln >> 4;
-        double* slot = ws + (size_t)(half ? I - 1 - (n - 1 - delay) : n - 1) * SZ;
+        double* slot = ws + (size_t)(half ? I - 1 - (n - delay) : n) * SZ;
 #pragma unroll
         for (int C = 0; C < X::FC; ++C) {
 #pragma unroll
@@ -785,21 +809,11 @@ void k_factor_wave(FactorArgs A) {
         if (ln < NT) nt_store(slot + (size_t)NT * NT + ln, sm.y[ln]);
     };
 
-    for (int n = delay; n <= m; ++n) {
-        const bool mid = n == m;
-        if (mid) {
-            if (half) {                                                // hand the last factor to the inner half
-#pragma unroll
-                for (int q = 0; q < T; ++q)
-#pragma unroll
-                    for (int C = 0; C < CN; ++C) s_C[q][C][lane] = S.get(q, C);
-                if (lane < X::W) s_y[lane] = sm.y[lane];
-                if (n > delay) store(n, lane);
-                if (lane == 0) s_bad[1] = guard.bad != 0ull;
-            }
-            __syncthreads();
-            if (half) break;
-        }
+
+    // Zone of step n into its place: transport coefficients and right-hand side of the owned groups, then scattering
+    // terms and diagonal, per column of the stored matrix and row 4u + a
+    auto assemble = [&](int n) {
+        ZoneBlock<T>& out = sm.zone[n & 1];
         // what derives from the lane id is formed again each step instead of being held across it
         const int ln = opaque_lane(), jc = ln & 15, k = group(ln);
         const TileLane L(ln);
@@ -835,15 +849,10 @@ void k_factor_wave(FactorArgs A) {
         double diag = fma(cV, ec + tc, 1.0);
         if (emabs) diag = fma(c, sig, diag);
         if (ln < NT) {
-            const double sch = real ? (TRANS ? -c * tc * iV_prev : cV * to) : 0.0;
-            const double bco = real ? (TRANS ? -c * ec * iVn : cV * eo) : 0.0;
-            double g = real ? A.rhs_sign * z_rhs : 0.0;
-            g = fma(-sch, sm.y[ln], g);
-            if (mid) g = fma(-bco, s_y[ln], g);
+            out.sch[ln] = real ? (TRANS ? -c * tc * iV_prev : cV * to) : 0.0;
+            out.bco[ln] = real ? (TRANS ? -c * ec * iVn : cV * eo) : 0.0;
+            out.g[ln] = real ? A.rhs_sign * z_rhs : 0.0;
             sm.psi[ln] = real ? psi : 0.0;
-            sm.sch[ln] = sch;
-            sm.bco[ln] = bco;
-            sm.g[ln] = g;
             sm.dg[ln] = real ? diag : 1.0;
         }
         tc = -eo;                                                      // the next zone becomes the current one
@@ -854,26 +863,18 @@ void k_factor_wave(FactorArgs A) {
         iV_prev = iVc;
         wave_sync();
         const double iT = rcp_cubic(Tz), camp = c * amp;
-        if (n > delay) store(n, ln);
         load_next(k, zn + dir);
         load_zone(k, zn);
         r_t = r_l;
         r_l = r_b;
         r_b = A.f.r_edge[eb + clampe((half ? zc : zc + 1) + 2 * dir)];
         __builtin_amdgcn_sched_barrier(0);
-
-        // ---- the block: Schur term of the previous factor (both neighbours' in the meeting zone), scattering
-        //      terms and the diagonal, per column of the stored matrix and row 4u + a
 #pragma unroll
         for (int C = 0; C < CN; ++C) {
             const int col = 16 * C + jc;
-            const double sc = -sm.sch[col], bc = sm.bco[col];
+            double dgv = sm.dg[col], B[T];
 #pragma unroll
-            for (int q = 0; q < T; ++q) {
-                S.set(q, C, S.get(q, C) * sc);
-                if (mid) S.set(q, C, fma(-s_C[q][C][ln], bc, S.get(q, C)));
-            }
-            double dgv = sm.dg[col];
+            for (int u = 0; u < T; ++u) B[u] = 0.0;
             if (nes) {
                 const double pcol = sm.psi[col], ek = s_eps[col];
                 const double wc = -camp * pcol, w1c = -camp - wc;       // weights of psi and 1 - psi of the column
@@ -887,9 +888,9 @@ void k_factor_wave(FactorArgs A) {
                     const bool up = row > col;
                     if (TRANS) {                                        // row is k, column k'
                         const double Pt = sPt[row * X::W + col], wr = -camp * prow, w1r = -camp - wr;
-                        S.set(u, C, fma((up ? w1r : wr) * Pt, M, fma(up ? wr : w1r, Pt, S.get(u, C))));
+                        B[u] = fma((up ? w1r : wr) * Pt, M, (up ? wr : w1r) * Pt);
                     } else {                                            // column is k, row k'
-                        S.set(u, C, fma(up ? wc : w1c, PM, fma(up ? w1c : wc, P, S.get(u, C))));
+                        B[u] = fma(up ? wc : w1c, PM, (up ? w1c : wc) * P);
                     }
                     // sum over k' for k the column: k' is the row either way
                     const double pq = 1.0 - prow;
@@ -899,42 +900,83 @@ void k_factor_wave(FactorArgs A) {
                 dgv = fma(camp, mfma4(1.0, acc, 0.0), dgv);
             }
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
-                if (4 * C + x < T) {
-                    const double on = (L.g == x && L.a == L.b) ? 1.0 : 0.0;
-                    S.set(4 * C + x, C, fma(on, dgv, S.get(4 * C + x, C)));
-                }
+            for (int u = 0; u < T; ++u) {
+                const double on = (u / 4 == C && L.g == u % 4 && L.a == L.b) ? 1.0 : 0.0;
+                out.block[C * T + u][ln] = u / 4 == C ? fma(on, dgv, B[u]) : B[u];
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
+    };
 
-        // ---- Ahat^-1, y = Ahat^-1 g, C = Ahat^-1 diag(b)
-        wave_invert<T, CN, X::PR>(S, L, jc, sm.pan, guard);
-        double yc[CN];
+    // The second wavefront assembles the zone of the next step while the first eliminates that of this one.
+    if (assembles && delay == 0 && (m > 0 || !half)) assemble(0);
+    lds_barrier();
+    for (int n = 0; n <= m; ++n) {
+        const bool mid = n == m;
+        if (mid) {                                                     // the outer half hands its last factor over
+            if (half && !assembles) {
 #pragma unroll
-        for (int C = 0; C < CN; ++C) yc[C] = 0.0;
+                for (int q = 0; q < T; ++q)
 #pragma unroll
-        for (int q = 0; q < T; ++q) {
-            const double g = sm.g[4 * q + L.a];
-#pragma unroll
-            for (int C = 0; C < CN; ++C) yc[C] = fma(S.get(q, C), g, yc[C]);
+                    for (int C = 0; C < CN; ++C) s_C[q][C][lane] = S.get(q, C);
+                if (lane < X::W) s_y[lane] = sm.y[lane];
+                if (lane == 0) s_bad[1] = guard.bad != 0ull;
+            }
+            lds_barrier();
         }
+        if (assembles) {
+            if (n + 1 >= delay && n + 1 < m + (half ? 0 : 1)) assemble(n + 1);
+        } else if (n >= delay && !(mid && half)) {
+            const int ln = opaque_lane(), jc = ln & 15;
+            const TileLane L(ln);
+            const ZoneBlock<T>& in = sm.zone[n & 1];
+            if (ln < NT) {
+                double g = fma(-in.sch[ln], sm.y[ln], in.g[ln]);
+                if (mid) g = fma(-in.bco[ln], s_y[ln], g);
+                sm.g[ln] = g;
+            }
+            // ---- Schur term of the previous factor, of both neighbours' in the meeting zone
 #pragma unroll
-        for (int C = 0; C < CN; ++C) yc[C] = mfma4(1.0, yc[C], 0.0);
-        if (L.a == 0) {
+            for (int C = 0; C < CN; ++C) {
+                const double sc = -in.sch[16 * C + jc], bc = in.bco[16 * C + jc];
 #pragma unroll
-            for (int C = 0; C < CN; ++C) sm.y[16 * C + jc] = yc[C];
-        }
-        if (!mid) {
+                for (int q = 0; q < T; ++q) {
+                    S.set(q, C, fma(S.get(q, C), sc, in.block[C * T + q][ln]));
+                    if (mid) S.set(q, C, fma(-s_C[q][C][ln], bc, S.get(q, C)));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // ---- Ahat^-1, y = Ahat^-1 g, C = Ahat^-1 diag(b)
+            wave_invert<T, CN, X::PR>(S, L, jc, sm.pan, guard);
+            double yc[CN];
+#pragma unroll
+            for (int C = 0; C < CN; ++C) yc[C] = 0.0;
 #pragma unroll
             for (int q = 0; q < T; ++q) {
-                const double b = sm.bco[4 * q + L.a];
+                const double g = sm.g[4 * q + L.a];
 #pragma unroll
-                for (int C = 0; C < CN; ++C) S.set(q, C, S.get(q, C) * b);
+                for (int C = 0; C < CN; ++C) yc[C] = fma(S.get(q, C), g, yc[C]);
+            }
+#pragma unroll
+            for (int C = 0; C < CN; ++C) yc[C] = mfma4(1.0, yc[C], 0.0);
+            if (L.a == 0) {
+#pragma unroll
+                for (int C = 0; C < CN; ++C) sm.y[16 * C + jc] = yc[C];
+            }
+            wave_sync();
+            if (!mid) {
+#pragma unroll
+                for (int q = 0; q < T; ++q) {
+                    const double b = in.bco[4 * q + L.a];
+#pragma unroll
+                    for (int C = 0; C < CN; ++C) S.set(q, C, S.get(q, C) * b);
+                }
+                store(n, ln);
             }
         }
-        wave_sync();
+        if (!mid) lds_barrier();
     }
-    if (!half) {
+    if (wave == 0) {
         if (lane == 0) s_bad[0] = guard.bad != 0ull;
         if (lane < X::W) s_x[lane] = sm.y[lane];
     }
@@ -948,6 +990,7 @@ void k_factor_wave(FactorArgs A) {
         }
         return;
     }
+    if (assembles) return;
 
     // ---- back substitution outwards from the meeting zone
     const int lb = opaque_lane(), jc = lb & 15;
@@ -1028,7 +1071,7 @@ void k_factor_wave(FactorArgs A) {
 
 template <int T>
 static void launch_single_t(const FactorArgs& a, bool transpose, hipStream_t st) {
-    const dim3 grid((unsigned)a.nsys), block(128);
+    const dim3 grid((unsigned)a.nsys), block(256);
     const bool ext = a.f.lapse || a.sh.limiter == 2 || a.sh.outer_bc == 2;
     if (transpose) {
         if (ext) hipLaunchKernelGGL((k_factor_wave<T, true, true>), grid, block, 0, st, a);

@@ -74,11 +74,11 @@ def test_coupled_elimination_matches_oracle(shape, option, monkeypatch):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("option", ["plain", "lapse", "geometric"])
-@pytest.mark.parametrize("shape", [dict(S=2, R=256, I=3, N=4), dict(S=1, R=513, I=1, N=5), dict(S=3, R=171, I=2, N=12),
-                                   dict(S=1, R=515, I=4, N=17), dict(S=1, R=514, I=5, N=20), dict(S=1, R=517, I=3, N=29),
-                                   dict(S=1, R=516, I=6, N=32)])
+@pytest.mark.parametrize("shape", [dict(S=2, R=384, I=3, N=4), dict(S=1, R=769, I=1, N=5), dict(S=3, R=257, I=2, N=12),
+                                   dict(S=1, R=771, I=4, N=17), dict(S=1, R=770, I=5, N=20), dict(S=1, R=773, I=3, N=29),
+                                   dict(S=1, R=772, I=6, N=32)])
 def test_eliminations_on_both_sides_of_the_system_count(shape, option):
-    """512 systems (a wavefront per half system), and just more (four half systems to a wavefront, the last one
+    """768 systems (wavefronts per half system), and just more (four half systems to a wavefront, the last one
     partly filled), plain and transposed, sampled systems against the oracle.  Bar: 1e-11 of max|x|."""
     print("case either side", shape, option, flush=True)
     sys.stdout.flush()
