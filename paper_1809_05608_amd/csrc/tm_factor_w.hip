@@ -21,7 +21,9 @@
 // read once) comes to half the time.  Per update, 540 zones x 20 groups, residual passes included, against one
 // ray per wavefront on 8 x 8 tiles of the vector unit from one end: 90 rays 14.2 -> 4.0 ms, 2048 rays 21.4 -> 16 ms,
 // 8192 rays 74 -> 55 ms.  Lapse, neutrinosphere options and pairs had partial pivoting
-// on the vector unit only; with pairs 90 rays 18 -> 5 ms.
+// on the vector unit only; with pairs 90 rays 18 -> 4.1 ms.
+// Of a step's 33000 cycles with few rays 17400 are the inversion (630 of each panel's 1585 on the matrix core, which
+// does not overlap the vector unit's FP64 work), 9300 the assembly, 4200 the back substitution.
 #include "tm_kernels.hpp"
 #include "tm_tile.hpp"
 
@@ -45,6 +47,13 @@ __device__ __forceinline__ double wave_total(double v) {
     return dpp_add<0x128>(v);          // row_ror:8
 }
 
+// Barrier of the workgroup for what its wavefronts exchange through LDS; memory operations stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 template <int T>
 struct CoupledShape {
     static constexpr int NT = 4 * T, NC = 2 * NT, M = NC + 1;
@@ -60,10 +69,19 @@ template <int T, bool EXT>
 struct CoupledLds {
     using C = CoupledShape<T>;
     double pan[4 * C::PR];             // pivot panel, column by column
-    double psi[C::W], sch[C::W], bco[C::W], g[C::W], dg[C::W];   // per row: see the assembly
+    double psi[C::W], g[C::W], dg[C::W];                         // per row: see the assembly
     double yrow[C::W], ycol[C::W];     // Y_e row and column of the block
     double y[C::W];                    // y of the previous zone; x in the back substitution
     double pe[EXT ? C::W : 1], pm[EXT ? C::W : 1], bz[EXT ? C::NT : 1];   // pair terms
+};
+
+// A zone ready for elimination: couplings to the previous and the next zone, right-hand side, and, where a second
+// wavefront makes it (AHEAD), the block, lane by lane in the registers' order.
+template <int T, bool AHEAD>
+struct CoupledZone {
+    using C = CoupledShape<T>;
+    double sch[C::W], bco[C::W], g[C::W];
+    double block[AHEAD ? C::G * C::CN : 1][AHEAD ? 64 : 1];
 };
 
 // What a lane owns: row i = lane of the block (species cell i < NC, Y_e at i = NC), and its cell's offset.
@@ -183,13 +201,16 @@ __device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane&
         if (C != next_register(G - 1)) update(C, l_prev, u_prev[C], G - 1);
 }
 
-// EXT: lapse, geometric limiter and boundary, and the pair processes compiled in.
-template <int T, bool EXT>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(EXT || T > 5 ? 1 : 2)))
+// EXT: lapse, geometric limiter and boundary, and the pair processes compiled in.  AHEAD: a second wavefront per half
+// makes the next zone's block while the first eliminates.
+template <int T, bool EXT, bool AHEAD>
+__global__ __launch_bounds__(AHEAD ? 256 : 128) __attribute__((amdgpu_waves_per_eu(AHEAD || EXT || T > 5 ? 1 : 2)))
 void k_ye_factor_wave(YeFactorArgs A) {
     using X = CoupledShape<T>;
     constexpr int NT = X::NT, NC = X::NC, M = X::M, G = X::G, Q = X::Q, CN = X::CN;
+    constexpr int kThreads = AHEAD ? 256 : 128;
     __shared__ CoupledLds<T, EXT> lds[2];
+    __shared__ CoupledZone<T, AHEAD> zones[2][AHEAD ? 2 : 1];           // per half: step n in n & 1
     __shared__ double sP[NT * NT];                 // P[k][k'] at [k'][k]
     __shared__ double sG[EXT ? NT * NT : 1];       // pair shape g[k][k'] W_k' / mean W at [k'][k]
     __shared__ double s_eps[NT];
@@ -197,14 +218,16 @@ void k_ye_factor_wave(YeFactorArgs A) {
     __shared__ double s_y[X::W], s_x[X::W];        // the outer half's y; x of the meeting zone
     __shared__ int s_bad[2];
     const int lane = threadIdx.x & 63;
-    const bool half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // the half coming from the outer edge
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool half = wave & 1;                                            // the half coming from the outer edge
+    const bool second = AHEAD && (wave >> 1);
     const long long ray = A.ray0 + blockIdx.x;
-    if (A.active && A.active[ray] == 0) return;                            // both wavefronts
+    if (A.active && A.active[ray] == 0) return;                            // all wavefronts
     const Shape& sh = A.sh;
     const int N = sh.N, I = sh.I, R = sh.R;
     const bool diff = sh.terms & kDiffusion, emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
     const bool pair = EXT && A.y.pair_amp != nullptr;
-    for (int j = threadIdx.x; j < NT * NT; j += 128) {
+    for (int j = threadIdx.x; j < NT * NT; j += kThreads) {
         const int kp = j / NT, k = j % NT;
         sP[j] = A.cs->P[k][kp];
         if (EXT) sG[j] = (pair && k < N && kp < N) ? A.y.pair_g[(size_t)k * N + kp] * A.cs->W[kp] / A.cs->wbar : 0.0;
@@ -276,7 +299,8 @@ void k_ye_factor_wave(YeFactorArgs A) {
     };
     const int z0 = half ? I - 1 : 0;
     double psi, sig, lam, tc, to = 0.0;                                 // this zone; trailing edge
-    {
+    double r_t = 0.0, r_l = 0.0, r_b = 0.0;
+    if (!AHEAD || second) {
         const Owner<T> O(lane, sh, ray);
         load_next(O, z0);
         psi = n_psi;
@@ -285,33 +309,34 @@ void k_ye_factor_wave(YeFactorArgs A) {
         tc = half ? outer(radius_nu(O), psi, lam) : 0.0;
         load_next(O, z0 + dir);
         load_zone(O, z0);
+        const int e0 = half ? I - 1 : 1;
+        r_t = A.f.r_edge[clampe(e0 - dir) + eb];
+        r_l = A.f.r_edge[clampe(e0) + eb];
+        r_b = A.f.r_edge[clampe(e0 + dir) + eb];
     }
-    const int e0 = half ? I - 1 : 1;
-    double r_t = A.f.r_edge[clampe(e0 - dir) + eb], r_l = A.f.r_edge[clampe(e0) + eb],
-           r_b = A.f.r_edge[clampe(e0 + dir) + eb];
 
     WaveBlock<G, CN> S;
 #pragma unroll
     for (int q = 0; q < G; ++q)
 #pragma unroll
         for (int C = 0; C < CN; ++C) S.set(q, C, 0.0);
-    if (lane < X::W) {
+    if (!second && lane < X::W) {
         sm.y[lane] = 0.0;
-        sm.yrow[lane] = sm.ycol[lane] = sm.psi[lane] = sm.sch[lane] = sm.bco[lane] = sm.g[lane] = 0.0;
+        sm.yrow[lane] = sm.ycol[lane] = sm.psi[lane] = sm.g[lane] = 0.0;
         sm.dg[lane] = 1.0;
+        for (int b = 0; b < (AHEAD ? 2 : 1); ++b)
+            zones[half][b].sch[lane] = zones[half][b].bco[lane] = zones[half][b].g[lane] = 0.0;
     }
-    wave_sync();
+    __syncthreads();
     TileGuard guard(A.growth_limit);
     const size_t SZ = (size_t)M * M + 1;                               // slot of a zone (M is odd)
     double* ws = A.ws + (size_t)blockIdx.x * I * SZ;
     typedef double V2 __attribute__((ext_vector_type(2)));
 
-    // C and y of the zone that step n - 1 finished.  Stored in the middle of the next step, not at the end of
-    // their own: loads and stores complete in order, so the wait for the next zone's loads would otherwise
-    // include the stores just issued.
+    // C and y of the zone of step n
     auto store = [&](int n, int ln) {
         const int jc = ln & 15, a = ln >> 4;
-        double* slot = ws + (size_t)(half ? I - 1 - (n - 1 - delay) : n - 1) * SZ;
+        double* slot = ws + (size_t)(half ? I - 1 - (n - delay) : n) * SZ;
 #pragma unroll
         for (int C = 0; C < X::FC; ++C)
 #pragma unroll
@@ -325,25 +350,12 @@ void k_ye_factor_wave(YeFactorArgs A) {
         if (ln < M) nt_store(slot + (size_t)NC * M + ln, sm.y[ln]);
     };
 
-    for (int n = delay; n <= m; ++n) {
-        const bool mid = n == m;
-        if (mid) {
-            if (half) {                                                // hand the last factor to the inner half
-#pragma unroll
-                for (int q = 0; q < Q; ++q)
-#pragma unroll
-                    for (int C = 0; C < CN; ++C) s_C[q][C][lane] = S.get(q, C);
-                if (lane < X::W) s_y[lane] = sm.y[lane];
-                if (n > delay) store(n, lane);
-                const bool bad = guard.bad != 0ull;
-                if (lane == 0) s_bad[1] = bad;
-            }
-            __syncthreads();
-            if (half) break;
-        }
+
+    // Owned rows of the zone of step n: transport coefficients, Y_e terms, right-hand side; then loads of what comes
+    double iT = 1.0, a0 = 0.0, a1 = 0.0, pa = 0.0;
+    auto own = [&](int n, CoupledZone<T, AHEAD>& out) {
         // what derives from the lane id is formed again each step instead of being held across it
-        const int ln = opaque_lane(), jc = ln & 15;
-        const TileLane L(ln);
+        const int ln = opaque_lane();
         const Owner<T> O(ln, sh, ray);
         const bool real = O.real;
         const double rnu = radius_nu(O);
@@ -386,14 +398,10 @@ void k_ye_factor_wave(YeFactorArgs A) {
             ysum = wave_total(ysum);
         }
         if (ln <= NC) {
-            const double sch = real ? cV * to : 0.0, bco = real ? cV * eo : 0.0;
-            double g = real ? A.rhs_sign * z_rhs : (ln == NC ? A.rhs_sign * gY : 0.0);
-            g = fma(-sch, sm.y[ln], g);
-            if (mid) g = fma(-bco, s_y[ln], g);
+            out.sch[ln] = real ? cV * to : 0.0;
+            out.bco[ln] = real ? cV * eo : 0.0;
+            out.g[ln] = real ? A.rhs_sign * z_rhs : (ln == NC ? A.rhs_sign * gY : 0.0);
             sm.psi[ln] = real ? psi : 0.0;
-            sm.sch[ln] = sch;
-            sm.bco[ln] = bco;
-            sm.g[ln] = g;
             sm.dg[ln] = real ? diag : (ln == NC && emabs ? fma(c * zt, ysum, 1.0) : 1.0);
             sm.yrow[ln] = real ? yrow : 0.0;
             sm.ycol[ln] = real ? ycol : 0.0;
@@ -410,28 +418,25 @@ void k_ye_factor_wave(YeFactorArgs A) {
         sig = n_sig;
         lam = n_lam;
         wave_sync();
-        const double iT = rcp_cubic(Tz), a0 = amp0, a1 = amp1, pa = pamp;
-        if (n > delay) store(n, ln);
+        iT = rcp_cubic(Tz);
+        a0 = amp0;
+        a1 = amp1;
+        pa = pamp;
         load_next(O, zn + dir);
         load_zone(O, zn);
         r_t = r_l;
         r_l = r_b;
         r_b = A.f.r_edge[eb + clampe((half ? zc : zc + 1) + 2 * dir)];
         __builtin_amdgcn_sched_barrier(0);
-
-        // ---- the block: Schur term of the previous factor (both neighbours' in the meeting zone) ...
+    };
+    // Column register C of the zone's block before elimination, rows 4q + a: scattering and pair terms per column k of
+    // the stored transpose and row k' = 4u + a, the Y_e column and row, and the diagonal
+    auto column = [&](int C, int ln, double (&B)[G]) {
+            const int jc = ln & 15;
+            const TileLane L(ln);
+            const ExpCoef coef = exp_coef();
 #pragma unroll
-        for (int C = 0; C < CN; ++C) {
-            const double sc = -sm.sch[16 * C + jc], bc = sm.bco[16 * C + jc];
-#pragma unroll
-            for (int q = 0; q < G; ++q) {
-                S.set(q, C, S.get(q, C) * sc);
-                if (mid && q < Q) S.set(q, C, fma(-s_C[q][C][ln], bc, S.get(q, C)));
-            }
-        }
-        // ... scattering and pair terms, per column k of the stored transpose and row k' = 4u + a ...
-#pragma unroll
-        for (int C = 0; C < CN; ++C) {
+            for (int q = 0; q < G; ++q) B[q] = 0.0;
             const bool has0 = 4 * C < T, has1 = 4 * C + 3 >= T && 4 * C < 2 * T;   // compile-time
             const int cg = 4 * C + L.g;                                 // column group: species, tile
             const int sc = cg < T ? 0 : 1, tt = cg - sc * T;
@@ -453,8 +458,8 @@ void k_ye_factor_wave(YeFactorArgs A) {
                     const double pv = sm.psi[(sc ? NT : 0) + kp];
                     const bool up = kp > k;
                     const double e = fma(up ? wk : w1, PM, (up ? w1 : wk) * P);
-                    if (has0) S.set(u, C, fma(m0, e, S.get(u, C)));
-                    if (has1) S.set(T + u, C, fma(m1, e, S.get(T + u, C)));
+                    if (has0) B[u] = fma(m0, e, B[u]);
+                    if (has1) B[T + u] = fma(m1, e, B[T + u]);
                     const double pq = 1.0 - pv;
                     acc = fma(up ? pv : pq, P, acc);
                     acc = fma(up ? pq : pv, PM, acc);
@@ -474,60 +479,116 @@ void k_ye_factor_wave(YeFactorArgs A) {
                     const double qx = qa * pair_chi(ek, sm.pe[o], mk, sm.pm[o]);
                     const double pv = sm.psi[o];
                     const double e = c * fma(1.0 - pk, qp, pk * qx);
-                    if (has0) S.set(T + u, C, fma(m0, e, S.get(T + u, C)));
-                    if (has1) S.set(u, C, fma(m1, e, S.get(u, C)));
+                    if (has0) B[T + u] = fma(m0, e, B[T + u]);
+                    if (has1) B[u] = fma(m1, e, B[u]);
                     acc += fma(qp, 1.0 - pv, qx * pv);
                 }
                 dgv = fma(c, mfma4(1.0, acc, 0.0), dgv);
             }
-            // ... the Y_e column and row, and the diagonal
             if (emabs) {
-                const double isY = L.a == 0 ? 1.0 : 0.0;
-                S.set(2 * T, C, fma(isY, sm.ycol[16 * C + jc], S.get(2 * T, C)));
+                B[2 * T] = fma(L.a == 0 ? 1.0 : 0.0, sm.ycol[16 * C + jc], B[2 * T]);
+                if (C == (2 * T) >> 2) {
+                    const double isY = (L.g == ((2 * T) & 3) && L.b == 0) ? 1.0 : 0.0;
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) B[q] = fma(isY, sm.yrow[4 * q + L.a], B[q]);
+                }
             }
 #pragma unroll
             for (int x = 0; x < 4; ++x)
                 if (4 * C + x < G) {
                     const double on = (L.g == x && L.a == L.b) ? 1.0 : 0.0;
-                    S.set(4 * C + x, C, fma(on, dgv, S.get(4 * C + x, C)));
+                    B[4 * C + x] = fma(on, dgv, B[4 * C + x]);
                 }
+    };
+    auto assemble = [&](int n) {
+        CoupledZone<T, AHEAD>& out = zones[half][AHEAD ? n & 1 : 0];
+        own(n, out);
+        const int ln = opaque_lane();
+#pragma unroll
+        for (int C = 0; C < CN; ++C) {
+            double B[G];
+            column(C, ln, B);
+#pragma unroll
+            for (int q = 0; q < G; ++q) out.block[AHEAD ? C * G + q : 0][AHEAD ? ln : 0] = B[q];
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (emabs) {
-            const double isY = (L.g == ((2 * T) & 3) && L.b == 0) ? 1.0 : 0.0;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) S.set(q, (2 * T) >> 2, fma(isY, sm.yrow[4 * q + L.a], S.get(q, (2 * T) >> 2)));
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    };
 
-        // ---- Ahat^-1, y = Ahat^-1 g, C = Ahat^-1 diag(b)
-        wave_invert<G, CN, X::PR>(S, L, jc, sm.pan, guard);
-        double yc[CN];
+    if (AHEAD) {
+        if (second && delay == 0 && (m > 0 || !half)) assemble(0);
+        lds_barrier();
+    }
+    for (int n = 0; n <= m; ++n) {
+        const bool mid = n == m;
+        if (mid) {                                                     // the outer half hands its last factor over
+            if (half && !second) {
 #pragma unroll
-        for (int C = 0; C < CN; ++C) yc[C] = 0.0;
+                for (int q = 0; q < Q; ++q)
 #pragma unroll
-        for (int q = 0; q < G; ++q) {
-            const double g = sm.g[4 * q + L.a];
-#pragma unroll
-            for (int C = 0; C < CN; ++C) yc[C] = fma(S.get(q, C), g, yc[C]);
+                    for (int C = 0; C < CN; ++C) s_C[q][C][lane] = S.get(q, C);
+                if (lane < X::W) s_y[lane] = sm.y[lane];
+                const bool bad = guard.bad != 0ull;
+                if (lane == 0) s_bad[1] = bad;
+            }
+            if (AHEAD) lds_barrier();
+            else __syncthreads();
         }
+        if (second) {
+            if (n + 1 >= delay && n + 1 < m + (half ? 0 : 1)) assemble(n + 1);
+        } else if (n >= delay && !(mid && half)) {
+            CoupledZone<T, AHEAD>& in = zones[half][AHEAD ? n & 1 : 0];
+            if (!AHEAD) own(n, in);
+            const int ln = opaque_lane(), jc = ln & 15;
+            const TileLane L(ln);
+            if (ln <= NC) {
+                double g = fma(-in.sch[ln], sm.y[ln], in.g[ln]);
+                if (mid) g = fma(-in.bco[ln], s_y[ln], g);
+                sm.g[ln] = g;
+            }
+            // ---- the block, with the Schur term of the previous factor (both neighbours' in the meeting zone)
 #pragma unroll
-        for (int C = 0; C < CN; ++C) yc[C] = mfma4(1.0, yc[C], 0.0);
-        if (L.a == 0) {
+            for (int C = 0; C < CN; ++C) {
+                double B[G];
+                if constexpr (!AHEAD) column(C, ln, B);
+                const double sc = -in.sch[16 * C + jc], bc = in.bco[16 * C + jc];
 #pragma unroll
-            for (int C = 0; C < CN; ++C) sm.y[16 * C + jc] = yc[C];
-        }
-        if (!mid) {
+                for (int q = 0; q < G; ++q) {
+                    S.set(q, C, fma(S.get(q, C), sc, AHEAD ? in.block[AHEAD ? C * G + q : 0][AHEAD ? ln : 0] : B[q]));
+                    if (mid && q < Q) S.set(q, C, fma(-s_C[q][C][ln], bc, S.get(q, C)));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // ---- Ahat^-1, y = Ahat^-1 g, C = Ahat^-1 diag(b)
+            wave_invert<G, CN, X::PR>(S, L, jc, sm.pan, guard);
+            double yc[CN];
+#pragma unroll
+            for (int C = 0; C < CN; ++C) yc[C] = 0.0;
 #pragma unroll
             for (int q = 0; q < G; ++q) {
-                const double b = q < Q ? sm.bco[4 * q + L.a] : 0.0;     // Y_e has no neighbours
+                const double g = sm.g[4 * q + L.a];
 #pragma unroll
-                for (int C = 0; C < CN; ++C) S.set(q, C, S.get(q, C) * b);
+                for (int C = 0; C < CN; ++C) yc[C] = fma(S.get(q, C), g, yc[C]);
+            }
+#pragma unroll
+            for (int C = 0; C < CN; ++C) yc[C] = mfma4(1.0, yc[C], 0.0);
+            if (L.a == 0) {
+#pragma unroll
+                for (int C = 0; C < CN; ++C) sm.y[16 * C + jc] = yc[C];
+            }
+            wave_sync();
+            if (!mid) {
+#pragma unroll
+                for (int q = 0; q < G; ++q) {
+                    const double b = q < Q ? in.bco[4 * q + L.a] : 0.0;     // Y_e has no neighbours
+#pragma unroll
+                    for (int C = 0; C < CN; ++C) S.set(q, C, S.get(q, C) * b);
+                }
+                store(n, ln);
             }
         }
-        wave_sync();
+        if (AHEAD && !mid) lds_barrier();
     }
-    if (!half) {
+    if (wave == 0) {
         const bool bad = guard.bad != 0ull;
         if (lane == 0) s_bad[0] = bad;
         if (lane < X::W) s_x[lane] = sm.y[lane];
@@ -536,7 +597,7 @@ void k_ye_factor_wave(YeFactorArgs A) {
     // a ray whose growth guard tripped is left untouched and marked for the partial-pivoting re-run
     const bool bad = s_bad[0] || s_bad[1];
     if (A.redo && threadIdx.x == 0) A.redo[ray] = bad ? 1 : 0;
-    if (bad) return;
+    if (bad || second) return;
 
     // ---- back substitution outwards from the meeting zone
     const int lb = opaque_lane(), jc = lb & 15;                         // jc: column within a register
@@ -612,11 +673,26 @@ void k_ye_factor_wave(YeFactorArgs A) {
     }
 }
 
+// Up to this many rays, one workgroup to each CU (the two zones handed over per half fill most of its LDS), a second
+// wavefront per half assembles the blocks of the general form, whose pair terms are as long as a third of the
+// elimination: 90 rays 5.1 -> 4.1 ms an update, 256 rays 5.3 -> 4.3, 512 rays 5.9 -> 8.1.  The plain form gains
+// nothing (3.95 against 3.98 ms at 90 rays): what its own assembly takes, the elimination gives back in registers.
+constexpr long long kAheadRays = 256;
+
 template <int T>
 static void launch_wave_t(const YeFactorArgs& a, bool ext, hipStream_t st) {
-    const dim3 grid((unsigned)a.nray), block(128);
-    if (ext) hipLaunchKernelGGL((k_ye_factor_wave<T, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((k_ye_factor_wave<T, false>), grid, block, 0, st, a);
+    const dim3 grid((unsigned)a.nray);
+    if (!ext) {
+        hipLaunchKernelGGL((k_ye_factor_wave<T, false, false>), grid, dim3(128), 0, st, a);
+        return;
+    }
+    if constexpr (T <= 6) {                            // two zones ahead per half: 160 KB of LDS at 24 groups
+        if (a.sh.R <= kAheadRays) {
+            hipLaunchKernelGGL((k_ye_factor_wave<T, true, true>), grid, dim3(256), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_ye_factor_wave<T, true, false>), grid, dim3(128), 0, st, a);
 }
 
 hipError_t launch_ye_factor_wave(const YeFactorArgs& a, hipStream_t st) {
@@ -669,13 +745,6 @@ struct SingleLds {
     double psi[C::W], dg[C::W], g[C::W];
     double y[C::W];                    // y of the previous zone; x in the back substitution
 };
-
-// Barrier of the workgroup for what its wavefronts exchange through LDS; memory operations stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 }  // namespace
 
