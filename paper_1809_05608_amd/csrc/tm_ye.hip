@@ -9,7 +9,7 @@
 // the absorption and emission opacities of the pair are linear in Y_e over the step, with their
 // derivatives given as inputs.
 //
-//   k_ye_couple       one block per ray: completes the species residual (evaluated by the
+//   k_ye_couple       one block per ray, sixteen zones to a wavefront: completes the species residual (evaluated by the
 //                     single-species residual kernel with the opacities of Y_e^n) with the Y_e terms,
 //                     evaluates the Y_e residual, max|G|, the rounding level, the lepton number and the
 //                     Newton/line-search decisions.
@@ -22,9 +22,10 @@
 //                     applies the Newton update.  It runs the rays that the diagonal-pivot elimination
 //                     (k_ye_factor_wave, tm_factor_w.hip) leaves untouched because its growth guard tripped.
 //   k_ye_backtrack    line-search move-back of rejected trials.
-//   k_ye_temperature  one thread per zone: energy-weighted collision sources of every species, the
+//   k_ye_temperature  sixteen zones to a wavefront: energy-weighted collision sources of every species, the
 //                     matter energy change and the new temperature.
 #include "tm_kernels.hpp"
+#include "tm_nes.hpp"
 
 namespace tmk {
 
@@ -39,101 +40,142 @@ __device__ __forceinline__ double ye_zeta(double rho) { return kFourPiOverHc3 * 
 
 // ---------------------------------------------------------------- residual completion and decisions
 
-// PAIR compiles the pair sources in (their loops double the kernel's registers); the launch takes it
-// when pair inputs are given.
-template <int NT, bool PAIR>
+// Both kernels below take sixteen zones to a wavefront: lane 16 a + j holds groups a, 4 + a, 8 + a, ... of zone j, so
+// a sum over a zone's groups is T additions and one matrix product with ones, and the zone's own values are in
+// place in each of its lanes.  k_ye_couple is bound by its way through memory (the layout reads 32-byte pieces):
+// 2048 rays of 540 zones x 20 groups 0.88 -> 0.84 ms against one zone per wavefront with the sums by shuffles, with
+// pairs and 90 rays, where a zone's chain of latencies counted, 0.45 -> 0.18.  k_ye_temperature takes the scattering
+// sums from the matrix cores (tm_nes.hpp): 5.0 -> 0.64 ms and with pairs 0.58 -> 0.07 against one thread per zone,
+// whose rows of groups went to scratch memory.
+
+// Pair sums of one species' groups at a zone (eqs. d11-d14, Phi_0 terms, chi of eqs. d16-d22): creation with the other
+// species' blocking and annihilation, for the lane's groups k = 4t + a, over the other's groups k'.
+template <int T>
+struct PairLds {
+    double g[16 * T * T];              // shape g[k][k'] W_k' / mean W at [k'][k], zero for padding groups
+    double eps[4 * T], rnu[2][4 * T];
+    __device__ __forceinline__ void fill(const YeFields& y, const Fields& f, const Consts& cs, int N) {
+        for (int x = threadIdx.x; x < 16 * T * T; x += kBlock) {
+            const int kp = x / (4 * T), k = x % (4 * T);
+            g[x] = k < N && kp < N ? y.pair_g[(size_t)k * N + kp] * cs.W[kp] / cs.wbar : 0.0;
+        }
+        if (threadIdx.x < 4 * T) {
+            const int k = threadIdx.x;
+            eps[k] = k < N ? cs.eps[k] : 0.0;
+            for (int q = 0; q < 2; ++q) rnu[q][k] = k < N ? f.r_nu[(size_t)q * N + k] : 0.0;
+        }
+    }
+};
+template <int T>
+__device__ __forceinline__ void pair_sums(const PairLds<T>& sm, int N, int a, int q, double amp, double iT, double iR,
+                                          const double* eta_q, const double* psi_o, const double* eta_o,
+                                          double (&cre)[T], double (&ann)[T]) {
+    const ExpCoef coef = exp_coef();
+    double eo[T], mo[T], bk[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int k = t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1);
+        eo[t] = eta_q[k];
+        mo[t] = pair_limb_cosine(sm.rnu[q][k] * iR);
+        bk[t] = exp_nonpos(-sm.eps[k] * iT, coef);
+        cre[t] = ann[t] = 0.0;
+    }
+    for (int kp = 0; kp < N; ++kp) {
+        const double pb = psi_o[kp], eb = eta_o[kp], mb = pair_limb_cosine(sm.rnu[1 - q][kp] * iR);
+        const double cb = amp * exp_nonpos(-sm.eps[kp] * iT, coef) * (1.0 - pb), ab = amp * pb;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const double g = sm.g[kp * 4 * T + 4 * t + a];
+            cre[t] = fma(g * bk[t], cb, cre[t]);
+            ann[t] = fma(g * pair_chi(eo[t], eb, mo[t], mb), ab, ann[t]);
+        }
+    }
+}
+
+// PAIR compiles the pair sources in; the launch takes it when pair inputs are given.
+template <int T, bool PAIR>
 __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs,
                                                       const double* __restrict__ psi, const double* __restrict__ ye,
                                                       double* __restrict__ G, double* __restrict__ GY,
                                                       const double* __restrict__ level_sp, YeOut out) {
     __shared__ double red[kBlock / 64];
+    __shared__ PairLds<PAIR ? T : 1> sp;
     const long long ray = blockIdx.x;
     if (out.mode == kResTrial && out.pending[ray] == 0) return;          // no trial to evaluate
     const int R = sh.R, I = sh.I, N = sh.N;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int q = lane < NT ? 0 : 1;
-    const int k = lane - q * NT;
-    const bool real = lane < 2 * NT && k < N;                            // species q, group k
-    const int kk = real ? k : 0;
-    const double sgn = q == 0 ? 1.0 : -1.0;                              // nu_e carries +1, anti-nu_e -1
-    const double Wk = real ? cs->W[kk] : 0.0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a = lane >> 4, j = lane & 15;
     const double c = sh.c_dt;
     const bool emabs = sh.terms & kEmAbs;
     const double* re = f.r_edge + (size_t)ray * (I + 1);
-    const size_t cell0 = ((size_t)(real ? q : 0) * R + ray) * I * N;
     const size_t zb = (size_t)ray * I;
+    if constexpr (PAIR) {
+        sp.fill(y, f, *cs, N);
+        __syncthreads();
+    }
+    double W[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) W[t] = 4 * t + a < N ? cs->W[4 * t + a] : 0.0;
 
     double gmax = 0.0, mag_max = 0.0, lep = 0.0;
     int bad = 0;
-    const bool pair = PAIR && y.pair_amp != nullptr;
-    __shared__ double s_pair[PAIR ? kBlock / 64 : 1][3][64];   // psi, flux factor, limb cosine of both species' groups
-    __shared__ double s_bz[PAIR ? kBlock / 64 : 1][NT];        // exp(-eps_j / T) of the zone
-    for (int i = wave; i < I; i += kBlock / 64) {
-        const double Y = ye[zb + i], Yn = y.ye_n[zb + i];
+    for (int z0 = 16 * wave; z0 < I; z0 += 16 * (kBlock / 64)) {
+        const int i = z0 + j, ic = min(i, I - 1);
+        const bool in_zone = i < I;
+        const double Y = ye[zb + ic], Yn = y.ye_n[zb + ic], rho = y.rho[zb + ic];
+        const double az = f.lapse ? f.lapse[zb + ic] : 1.0;
         const double dy = Y - Yn;
         double sY = 0.0, sAbs = 0.0, sD = 0.0, sL = 0.0;
-        double spair = 0.0;
-        if (pair) {
-            // pair sources of the zone (eqs. d11-d14, Phi_0 terms, chi of eqs. d16-d22)
-            const double Rz = 0.5 * (re[i] + re[i + 1]);
-            double pown = 0.0, eown = 0.0, mown = 0.0;
-            if (real) {
-                const size_t ci = cell0 + (size_t)i * N + kk;
-                pown = psi[ci];
-                eown = y.pair_eta1[ci];
-                mown = pair_limb_cosine(f.r_nu[(size_t)q * N + kk] / Rz);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const double sgn = q == 0 ? 1.0 : -1.0;                      // nu_e carries +1, anti-nu_e -1
+            const size_t cz = (((size_t)q * R + ray) * I + ic) * N;
+            double cre[T], ann[T];
+            if constexpr (PAIR) {
+                const size_t co = (((size_t)(1 - q) * R + ray) * I + ic) * N;
+                pair_sums<T>(sp, N, a, q, y.pair_amp[zb + ic], drcp(f.temp[zb + ic]), drcp(0.5 * (re[ic] + re[ic + 1])),
+                             y.pair_eta1 + cz, psi + co, y.pair_eta1 + co, cre, ann);
             }
-            s_pair[wave][0][lane] = pown;
-            s_pair[wave][1][lane] = eown;
-            s_pair[wave][2][lane] = mown;
-            if (lane < NT) s_bz[wave][lane] = lane < N ? exp(-cs->eps[lane] / f.temp[zb + i]) : 0.0;
-            wave_sync();
-            if (real) {
-                const double a = y.pair_amp[zb + i], iw = 1.0 / cs->wbar, bzk = s_bz[wave][kk];
-                const int o = (1 - q) * NT;
-                double cre = 0.0, ann = 0.0;
-                for (int kp = 0; kp < N; ++kp) {
-                    const double qa = a * y.pair_g[(size_t)kk * N + kp] * cs->W[kp] * iw;
-                    const double pb = s_pair[wave][0][o + kp];
-                    cre = fma(qa * bzk * s_bz[wave][kp], 1.0 - pb, cre);
-                    ann = fma(qa * pair_chi(eown, s_pair[wave][1][o + kp], mown, s_pair[wave][2][o + kp]), pb, ann);
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int k = 4 * t + a;
+                const bool real = in_zone && (t + 1 < T || k < N);
+                const size_t ci = cz + (t + 1 < T ? k : min(k, N - 1));
+                const double p = psi[ci], h = 1.0 - p;
+                double g = G[ci];
+                if constexpr (PAIR) {
+                    const double sc = h * cre[t], sa = p * ann[t];
+                    g -= c * (sc - sa);
+                    // rounding level of the pair terms, counted as the other sources are
+                    const double mag = fabs(p) + c * (fabs(sc) + fabs(sa)) + fabs(p) * c * (cre[t] + ann[t]);
+                    mag_max = fmax(mag_max, real ? mag : 0.0);
                 }
-                spair = (1.0 - pown) * cre - pown * ann;
-                // rounding level of the pair terms, counted as the other sources are
-                mag_max = fmax(mag_max, fabs(pown) + c * (fabs((1.0 - pown) * cre) + fabs(pown * ann))
-                                            + fabs(pown) * c * (cre + ann));
+                if (emabs) {
+                    // with a lapse the fields are lapse-folded (a kappa_a, a eta): the derivatives get the same a
+                    const double dka = az * y.dka[ci], det = az * y.deta[ci];
+                    const double slope = det * h - dka * p;
+                    g -= c * dy * slope;                                 // opacities at Y_e instead of Y_e^n
+                    const double em = (f.eta[ci] + dy * det) * h, ab = (f.kappa_a[ci] + dy * dka) * p;
+                    const double sw = sgn * W[t];
+                    sY = fma(sw, em - ab, sY);
+                    sAbs = fma(W[t], fabs(em) + fabs(ab), sAbs);
+                    sD = fma(sw, slope, sD);
+                }
+                sL = fma(sgn * W[t], p, sL);
+                if (real) {
+                    G[ci] = g;
+                    bad |= !isfinite(g);
+                    gmax = fmax(gmax, fabs(g));
+                }
             }
-            wave_sync();                               // the rows are rewritten for this wave's next zone
         }
-        if (real) {
-            const size_t ci = cell0 + (size_t)i * N + kk;
-            const double p = psi[ci];
-            double g = G[ci] - c * spair;
-            if (emabs) {
-                // with a lapse the fields are lapse-folded (a kappa_a, a eta): the derivatives get the same a
-                const double az = f.lapse ? f.lapse[zb + i] : 1.0;
-                const double dka = az * y.dka[ci], det = az * y.deta[ci];
-                g += c * dy * (dka * p - det * (1.0 - p));              // opacities at Y_e instead of Y_e^n
-                const double em = (f.eta[ci] + dy * det) * (1.0 - p);
-                const double ab = (f.kappa_a[ci] + dy * dka) * p;
-                sY = sgn * Wk * (em - ab);
-                sAbs = Wk * (fabs(em) + fabs(ab));
-                sD = sgn * Wk * (det * (1.0 - p) - dka * p);
-            }
-            G[ci] = g;
-            sL = sgn * Wk * p;
-            bad |= !isfinite(g);
-            gmax = fmax(gmax, fabs(g));
-        }
-        sY = wave_sum(sY);
-        sAbs = wave_sum(sAbs);
-        sD = wave_sum(sD);
-        sL = wave_sum(sL);
-        if (lane == 0) {
-            const double rho = y.rho[zb + i];
+        sY = mfma4(1.0, sY, 0.0);
+        sAbs = mfma4(1.0, sAbs, 0.0);
+        sD = mfma4(1.0, sD, 0.0);
+        sL = mfma4(1.0, sL, 0.0);
+        if (a == 0 && in_zone) {
             // with a lapse: the neutrinos of the zone number (V / a^3) sum_k W_k psi and the folded sources
             // carry a, so the Y_e rate per unit folded source is zeta / a^3
-            const double ai3 = f.lapse ? 1.0 / (f.lapse[zb + i] * f.lapse[zb + i] * f.lapse[zb + i]) : 1.0;
+            const double ai3 = 1.0 / (az * az * az);
             const double z = ye_zeta(rho) * ai3;
             double gy = dy, mag = fabs(Y) + fabs(Yn), ayy = 1.0;
             if (emabs) {
@@ -636,99 +678,77 @@ struct SpeciesWeights {
 // T_i^{n+1} = T_i^n + (de_i - (Y_e^{n+1} - Y_e^n) de/dY_e) / (de/dT)      (eq. a62d)
 // S_qk is the collision source of species q at psi^{n+1}: emission/absorption (for species 0 and 1 with
 // the opacities at Y_e^{n+1}) and NES; isoenergetic scattering exchanges no energy.
-template <int NT>
+template <int T, bool PAIR>
 __global__ __launch_bounds__(kBlock) void k_ye_temperature(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs,
                                                            const double* __restrict__ psi, const double* __restrict__ ye,
                                                            SpeciesWeights wts, const double* __restrict__ de_dT,
                                                            const double* __restrict__ de_dye, double* __restrict__ de_out,
                                                            double* __restrict__ temp_out) {
-    const long long idx = (long long)blockIdx.x * kBlock + threadIdx.x;
-    const long long nz = (long long)sh.R * sh.I;
-    if (idx >= nz) return;
+    __shared__ NesLds<T> sm;
+    __shared__ PairLds<PAIR ? T : 1> sp;
     const int R = sh.R, I = sh.I, N = sh.N;
-    const long long ray = idx / I;
-    const int i = (int)(idx - ray * I);
     const bool emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
-    const double T = f.temp[idx];
-    const double dy = ye[idx] - y.ye_n[idx];
-    double d[NT];
+    if (nes) sm.fill(*cs);
+    if constexpr (PAIR) sp.fill(y, f, *cs, N);
+    __syncthreads();
+    const long long nz = (long long)R * I;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a = lane >> 4, j = lane & 15, b = lane & 3;
+    const long long idx = ((long long)blockIdx.x * (kBlock / 64) + wave) * 16 + j, zi = min(idx, nz - 1);
+    const double Tz = f.temp[zi], iT = drcp(Tz), dy = ye[zi] - y.ye_n[zi];
+    double eW[T], d[T];
+    {
+        const ExpCoef coef = exp_coef();
 #pragma unroll
-    for (int j = 0; j < NT; ++j) d[j] = (nes && j + 1 < N) ? exp(-cs->de[j] / T) : 0.0;
+        for (int t = 0; t < T; ++t) {
+            const int k = 4 * t + a;
+            eW[t] = k < N ? cs->eps[k] * cs->W[k] : 0.0;
+            d[t] = nes ? exp_nonpos(-(k + 1 < N ? cs->de[k] : 0.0) * iT, coef) : 0.0;
+        }
+    }
     double src = 0.0;
     for (int s = 0; s < sh.S; ++s) {
-        const size_t cz = (((size_t)s * R + ray) * I + i) * N;
-        double p[NT];
+        const size_t cz = ((size_t)s * nz + zi) * N;
+        double p[T], acc = 0.0;
 #pragma unroll
-        for (int k = 0; k < NT; ++k) p[k] = k < N ? psi[cz + k] : 0.0;
-        const double amp = nes ? f.nes_amp[((size_t)s * R + ray) * I + i] : 0.0;
-        double acc = 0.0;
+        for (int t = 0; t < T; ++t) p[t] = psi[cz + (t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1))];
+        if (nes) {
+            const double amp = f.nes_amp[(size_t)s * nz + zi];
+            double sin_[T], sout[T], sn = 0.0;
+            nes_sums<T>(sm, p, d, a, b, 4 * a + b, sin_, sout);
 #pragma unroll
-        for (int k = 0; k < NT; ++k) {
-            if (k >= N) break;
-            double sk = 0.0;
-            if (emabs) {
-                double kap = f.kappa_a[cz + k], eta = f.eta[cz + k];
+            for (int t = 0; t < T; ++t) sn = fma(eW[t], (1.0 - p[t]) * sin_[t] - p[t] * sout[t], sn);
+            acc = amp * sn;
+        }
+        if (emabs) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const size_t ci = cz + (t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1));
+                double kap = f.kappa_a[ci], eta = f.eta[ci];
                 if (s < 2) {
-                    kap += dy * y.dka[cz + k];
-                    eta += dy * y.deta[cz + k];
+                    kap = fma(dy, y.dka[ci], kap);
+                    eta = fma(dy, y.deta[ci], eta);
                 }
-                sk = eta * (1.0 - p[k]) - kap * p[k];
+                acc = fma(eW[t], eta * (1.0 - p[t]) - kap * p[t], acc);
             }
-            if (nes) {
-                double sin_ = 0.0, sout = 0.0, e = 1.0;
-#pragma unroll
-                for (int kp = k + 1; kp < NT; ++kp) {          // k' > k: out factor exp(-(eps_k' - eps_k)/T)
-                    if (kp >= N) break;
-                    e *= d[kp - 1];
-                    sout = fma(cs->P[k][kp] * e, 1.0 - p[kp], sout);
-                    sin_ = fma(cs->P[k][kp], p[kp], sin_);
-                }
-                e = 1.0;
-#pragma unroll
-                for (int kp = k - 1; kp >= 0; --kp) {          // k' < k: in factor exp(-(eps_k - eps_k')/T)
-                    e *= d[kp];
-                    sin_ = fma(cs->P[k][kp] * e, p[kp], sin_);
-                    sout = fma(cs->P[k][kp], 1.0 - p[kp], sout);
-                }
-                sk += amp * ((1.0 - p[k]) * sin_ - p[k] * sout);
-            }
-            acc = fma(cs->eps[k] * cs->W[k], sk, acc);
         }
-        src = fma(wts.w[s], sh.c_dt * acc, src);
-    }
-    if (y.pair_amp) {
-        // pair sources of species 0 and 1 (eqs. d11-d14) with their energy weights
-        const double* re = f.r_edge + (size_t)ray * (I + 1);
-        const double Rz = 0.5 * (re[i] + re[i + 1]);
-        const double a = y.pair_amp[idx], iw = 1.0 / cs->wbar;
-        double bz[NT];
+        if constexpr (PAIR) {
+            if (s < 2) {                                   // pair sources of species 0 and 1 (eqs. d11-d14)
+                const double* re = f.r_edge + (zi / I) * (I + 1) + zi % I;
+                const size_t co = ((size_t)(1 - s) * nz + zi) * N;
+                double cre[T], ann[T];
+                pair_sums<T>(sp, N, a, s, y.pair_amp[zi], iT, drcp(0.5 * (re[0] + re[1])), y.pair_eta1 + cz, psi + co,
+                             y.pair_eta1 + co, cre, ann);
 #pragma unroll
-        for (int j = 0; j < NT; ++j) bz[j] = j < N ? exp(-cs->eps[j] / T) : 0.0;
-        for (int qs = 0; qs < 2; ++qs) {
-            const size_t co = (((size_t)qs * R + ray) * I + i) * N, cb = (((size_t)(1 - qs) * R + ray) * I + i) * N;
-            double acc = 0.0;
-            for (int k = 0; k < N; ++k) {
-                const double p = psi[co + k], eo = y.pair_eta1[co + k];
-                const double mo = pair_limb_cosine(f.r_nu[(size_t)qs * N + k] / Rz);
-                const double bk = exp(-cs->eps[k] / T);
-                double cre = 0.0, ann = 0.0;
-#pragma unroll
-                for (int kp = 0; kp < NT; ++kp) {
-                    if (kp >= N) break;
-                    const double qa = a * y.pair_g[(size_t)k * N + kp] * cs->W[kp] * iw;
-                    const double pb = psi[cb + kp];
-                    const double mb = pair_limb_cosine(f.r_nu[(size_t)(1 - qs) * N + kp] / Rz);
-                    cre = fma(qa * bk * bz[kp], 1.0 - pb, cre);
-                    ann = fma(qa * pair_chi(eo, y.pair_eta1[cb + kp], mo, mb), pb, ann);
-                }
-                acc = fma(cs->eps[k] * cs->W[k], (1.0 - p) * cre - p * ann, acc);
+                for (int t = 0; t < T; ++t) acc = fma(eW[t], (1.0 - p[t]) * cre[t] - p[t] * ann[t], acc);
             }
-            src = fma(wts.w[qs], sh.c_dt * acc, src);
         }
+        src = fma(wts.w[s], sh.c_dt * mfma4(1.0, acc, 0.0), src);
     }
-    const double de = -kFourPiOverHc3 * kBaryonMassG / y.rho[idx] * src;
-    if (de_out) de_out[idx] = de;
-    temp_out[idx] = T + (de - dy * de_dye[idx]) / de_dT[idx];
+    if (idx < nz && a == 0) {
+        const double de = -kFourPiOverHc3 * kBaryonMassG / y.rho[idx] * src;
+        if (de_out) de_out[idx] = de;
+        temp_out[idx] = Tz + (de - dy * de_dye[idx]) / de_dT[idx];
+    }
 }
 
 // ---------------------------------------------------------------- launchers
@@ -750,11 +770,11 @@ hipError_t launch_ye_couple(const Shape& sh, const Fields& f, const YeFields& y,
                             hipStream_t st) {
     if (y.pair_amp)
         TM_YE_DISPATCH(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_ye_couple<NT, true>), dim3((unsigned)sh.R), dim3(kBlock), 0, st, sh, f, y, cs,
+                       hipLaunchKernelGGL((k_ye_couple<NT / 4, true>), dim3((unsigned)sh.R), dim3(kBlock), 0, st, sh, f, y, cs,
                                           psi, ye, G, GY, level_sp, out))
     else
         TM_YE_DISPATCH(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_ye_couple<NT, false>), dim3((unsigned)sh.R), dim3(kBlock), 0, st, sh, f, y,
+                       hipLaunchKernelGGL((k_ye_couple<NT / 4, false>), dim3((unsigned)sh.R), dim3(kBlock), 0, st, sh, f, y,
                                           cs, psi, ye, G, GY, level_sp, out))
     return hipGetLastError();
 }
@@ -789,10 +809,15 @@ hipError_t launch_ye_temperature(const Shape& sh, const Fields& f, const YeField
     SpeciesWeights w{};
     for (int s = 0; s < sh.S; ++s) w.w[s] = weights[s];
     const long long nz = (long long)sh.R * sh.I;
-    const unsigned blocks = (unsigned)((nz + kBlock - 1) / kBlock);
-    TM_YE_DISPATCH(padded_groups(sh.N),
-                   hipLaunchKernelGGL(k_ye_temperature<NT>, dim3(blocks), dim3(kBlock), 0, st, sh, f, y, cs, psi, ye, w,
-                                      de_dT, de_dye, de_out, temp_out))
+    const unsigned blocks = (unsigned)((nz + kBlock / 4 - 1) / (kBlock / 4));      // sixteen zones to a wavefront
+    if (y.pair_amp)
+        TM_YE_DISPATCH(padded_groups(sh.N),
+                       hipLaunchKernelGGL((k_ye_temperature<NT / 4, true>), dim3(blocks), dim3(kBlock), 0, st, sh, f, y, cs,
+                                          psi, ye, w, de_dT, de_dye, de_out, temp_out))
+    else
+        TM_YE_DISPATCH(padded_groups(sh.N),
+                       hipLaunchKernelGGL((k_ye_temperature<NT / 4, false>), dim3(blocks), dim3(kBlock), 0, st, sh, f, y, cs,
+                                          psi, ye, w, de_dT, de_dye, de_out, temp_out))
     return hipGetLastError();
 }
 
