@@ -9,7 +9,6 @@
 #include <cstring>
 #include <mutex>
 #include <string>
-#include <vector>
 
 #include "../../include/tm.h"
 #include "tm_kernels.hpp"
@@ -34,7 +33,7 @@ struct tm_ctx {
     int* flags = nullptr;       // [nsys]
     int* count = nullptr;       // [1]
     double* gbuf = nullptr;     // [cells] residual for the Newton right-hand side
-    int* h_count = nullptr;     // pinned host
+    int* h_count = nullptr;     // [4] pinned host
     int* guard = nullptr;       // [nsys] growth guard of the last diagonal-pivot launch
     double* res_acc = nullptr;  // [nsys] Newton line search: accepted residual
     double* tgt = nullptr;      // [nsys] stopping target at the accepted iterate
@@ -202,7 +201,7 @@ tm_status ensure_small(tm_ctx* c) {
     TM_TRY(hip_check(c, hipMalloc((void**)&c->iters, ns * sizeof(int)), "hipMalloc iters"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->flags, ns * sizeof(int)), "hipMalloc flags"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->count, sizeof(int)), "hipMalloc count"));
-    TM_TRY(hip_check(c, hipHostMalloc((void**)&c->h_count, sizeof(int)), "hipHostMalloc"));
+    TM_TRY(hip_check(c, hipHostMalloc((void**)&c->h_count, 4 * sizeof(int)), "hipHostMalloc"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->guard, ns * sizeof(int)), "hipMalloc guard"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->redo, ns * sizeof(int)), "hipMalloc redo"));
     TM_TRY(hip_check(c, hipMalloc((void**)&c->res_acc, ns * sizeof(double)), "hipMalloc res_acc"));
@@ -330,7 +329,9 @@ tmk::YeFields ye_fields_of(const tm_ye_inputs& y) {
     return f;
 }
 
-// `listed`: the set entries of `active` are the first so many of c->list.
+// A Newton update (psi_out set) leaves the count of systems that tripped the growth guard, and clearing their marks,
+// to the tally that follows, and sends them to partial pivoting without asking (no mark: the wavefronts return at
+// once).  `listed`: the set entries of `active` are the first so many of c->list.
 tm_status run_factor(tm_ctx* c, const tm_inputs* in, const double* psi, const double* rhs, double rhs_sign,
                      double* x, double* psi_out, const int* active, bool fp32, bool transpose,
                      double* dx = nullptr, const double* rhs_max = nullptr, long long listed = -1) {
@@ -360,7 +361,7 @@ tm_status run_factor(tm_ctx* c, const tm_inputs* in, const double* psi, const do
     a.wsY = (char*)c->ws + (size_t)(batch + tmk::kWsPadSystems) * c->p.n_zones * NT * NT * es;
     const long long ns = n_systems(c->p);
     const bool pivot_first = c->pivot_policy == 1;
-    if (!pivot_first)
+    if (!pivot_first && !psi_out)
         TM_TRY(hip_check(c, hipMemsetAsync(c->guard, 0, ns * sizeof(int), c->stream), "memset guard"));
     if (c->timing) TM_TRY(hip_check(c, hipEventRecord(c->kt[0], c->stream), "timing event"));
     {
@@ -390,15 +391,21 @@ tm_status run_factor(tm_ctx* c, const tm_inputs* in, const double* psi, const do
     if (pivot_first) return TM_OK;
     // systems whose diagonal-pivot elimination tripped the growth guard were left untouched:
     // re-factor exactly those with partial pivoting
-    TM_TRY(hip_check(c, tmk::launch_mark(c->guard, ns, c->redo, c->count, c->stream), "mark kernel"));
-    TM_TRY(hip_check(c, hipMemcpyAsync(c->h_count, c->count, sizeof(int), hipMemcpyDeviceToHost, c->stream),
-                     "copy count"));
-    TM_TRY(hip_check(c, hipStreamSynchronize(c->stream), "stream sync"));
-    const int nredo = *c->h_count;
-    if (nredo == 0) return TM_OK;
-    c->pivot_fallbacks += nredo;
-    if (c->pivot_policy == 2) return set_err(c, TM_ERR_SINGULAR, "diagonal-pivot growth guard tripped");
-    a.active = c->redo;
+    if (psi_out) {
+        if (c->pivot_policy == 2) return TM_OK;             // an error, found by the tally
+        a.active = c->guard;
+        a.guard = nullptr;
+    } else {
+        TM_TRY(hip_check(c, tmk::launch_mark(c->guard, ns, c->redo, c->count, c->stream), "mark kernel"));
+        TM_TRY(hip_check(c, hipMemcpyAsync(c->h_count, c->count, sizeof(int), hipMemcpyDeviceToHost, c->stream),
+                         "copy count"));
+        TM_TRY(hip_check(c, hipStreamSynchronize(c->stream), "stream sync"));
+        const int nredo = *c->h_count;
+        if (nredo == 0) return TM_OK;
+        c->pivot_fallbacks += nredo;
+        if (c->pivot_policy == 2) return set_err(c, TM_ERR_SINGULAR, "diagonal-pivot growth guard tripped");
+        a.active = c->redo;
+    }
     a.total = ns;
     for (long long s0 = 0; s0 < ns; s0 += batch) {
         a.sys0 = s0;
@@ -754,16 +761,17 @@ tm_status tm_newton_step(tm_ctx* c, const tm_inputs* in, const double* psi_n, do
     const tmk::Fields f = fields_of(*in);
     const bool fp32 = c->p.precision == TM_PREC_MIXED;
     TM_TRY(hip_check(c, tmk::launch_setup(in->e_edge, in->nes_g, sh.N, c->consts, c->stream), "setup kernel"));
-    TM_TRY(hip_check(c, hipMemsetAsync(c->iters, 0, ns * sizeof(int), c->stream), "memset iters"));
-    TM_TRY(hip_check(c, hipMemsetAsync(c->flags, 0, ns * sizeof(int), c->stream), "memset flags"));
-
-    auto count_of = [&](const int* flags_arr, int* out_n, int* list = nullptr) -> tm_status {
-        if (list) TM_TRY(hip_check(c, tmk::launch_list_active(flags_arr, ns, list, c->count, c->stream), "list kernel"));
-        else TM_TRY(hip_check(c, tmk::launch_count_active(flags_arr, ns, c->count, c->stream), "count kernel"));
-        TM_TRY(hip_check(c, hipMemcpyAsync(c->h_count, c->count, sizeof(int), hipMemcpyDeviceToHost, c->stream),
-                         "copy count"));
+    TM_TRY(hip_check(c, tmk::launch_begin(ns, c->iters, c->flags, c->pending, c->backtrack, c->guard, c->stream),
+                     "begin kernel"));
+    // one launch and one synchronisation after each residual pass
+    int nact = 0, nback = 0, ntrip = 0;
+    auto tally = [&]() -> tm_status {
+        TM_TRY(hip_check(c, tmk::launch_tally(c->active, c->backtrack, c->guard, ns, c->list, c->h_count, c->stream),
+                         "tally kernel"));
         TM_TRY(hip_check(c, hipStreamSynchronize(c->stream), "stream sync"));
-        *out_n = *c->h_count;
+        nact = c->h_count[0];
+        nback = c->h_count[1];
+        ntrip = c->h_count[2];
         return TM_OK;
     };
     tmk::ResidualOut o{};
@@ -787,16 +795,12 @@ tm_status tm_newton_step(tm_ctx* c, const tm_inputs* in, const double* psi_n, do
         o.budget = stats->budget_n;
         o.lum = stats->lum_n;
     }
-    TM_TRY(hip_check(c, hipMemsetAsync(c->pending, 0, ns * sizeof(int), c->stream), "memset pending"));
-    TM_TRY(hip_check(c, hipMemsetAsync(c->backtrack, 0, ns * sizeof(int), c->stream), "memset backtrack"));
     o.mode = tmk::kResInitial;
     TM_TRY(hip_check(c, tmk::launch_residual(sh, f, c->consts, psi_n, psi, c->gbuf, 1.0, o, c->stream),
                      "residual kernel"));
     const int max_trials = 9;                              // alpha = 1, 1/2, ..., 1/256
-    for (int it = 0; it < max_iter; ++it) {
-        int nact = 0;
-        TM_TRY(count_of(c->active, &nact, c->list));
-        if (nact == 0) break;
+    if (max_iter > 0) TM_TRY(tally());
+    for (int it = 0; it < max_iter && nact > 0; ++it) {
         // Newton update psi += delta for the active systems (delta kept for backtracking)
         // res holds max |G| of the residual in gbuf for every active system (scaling of the float32 solve)
         TM_TRY(run_factor(c, in, psi, c->gbuf, -1.0, nullptr, psi, c->active, fp32, false, c->dbuf, c->res, nact));
@@ -805,33 +809,23 @@ tm_status tm_newton_step(tm_ctx* c, const tm_inputs* in, const double* psi_n, do
         for (int t = 0; t < max_trials; ++t) {
             TM_TRY(hip_check(c, tmk::launch_residual(sh, f, c->consts, psi_n, psi, c->gbuf, 1.0, o, c->stream),
                              "residual kernel"));
-            int nback = 0;
-            TM_TRY(count_of(c->backtrack, &nback));
+            TM_TRY(tally());
+            if (ntrip > 0 && c->pivot_policy == 2)
+                return set_err(c, TM_ERR_SINGULAR, "diagonal-pivot growth guard tripped");
+            c->pivot_fallbacks += ntrip;
             if (nback == 0) break;
             TM_TRY(hip_check(c, tmk::launch_backtrack(sh, psi, c->dbuf, c->backtrack, c->alpha, c->stream),
                              "backtrack kernel"));
         }
     }
 
-    // final flags from the last evaluated residual of each system (its accepted state)
-    TM_TRY(hip_check(c, tmk::launch_final_flags(ns, c->res, c->tgt, rtol, c->flags, c->stream), "flags kernel"));
-    if (stats) {
-        auto cp = [&](void* dst, const void* src, size_t bytes) -> tm_status {
-            if (!dst) return TM_OK;
-            return hip_check(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->stream), "copy stats");
-        };
-        TM_TRY(cp(stats->res_inf, c->res, ns * sizeof(double)));
-        TM_TRY(cp(stats->res0_inf, c->res0, ns * sizeof(double)));
-        TM_TRY(cp(stats->iters, c->iters, ns * sizeof(int)));
-        TM_TRY(cp(stats->flags, c->flags, ns * sizeof(int)));
-    }
-    // worst status over systems
-    std::vector<int> fl(ns);
-    TM_TRY(hip_check(c, hipMemcpyAsync(fl.data(), c->flags, ns * sizeof(int), hipMemcpyDeviceToHost, c->stream),
-                     "copy flags"));
+    // final flags from the last evaluated residual of each system (its accepted state), the worst over systems
+    TM_TRY(hip_check(c, tmk::launch_finish(ns, c->res, c->res0, c->tgt, rtol, c->iters, c->flags,
+                                           stats ? stats->res_inf : nullptr, stats ? stats->res0_inf : nullptr,
+                                           stats ? stats->iters : nullptr, stats ? stats->flags : nullptr, c->h_count + 3,
+                                           c->stream), "finish kernel"));
     TM_TRY(hip_check(c, hipStreamSynchronize(c->stream), "stream sync"));
-    int any = 0;
-    for (int v : fl) any |= v;
+    const int any = c->h_count[3];
     if (any & TM_FLAG_NONFINITE) return set_err(c, TM_ERR_NONFINITE, "non-finite residual in some system");
     if (any & TM_FLAG_ZERO_PIVOT) return set_err(c, TM_ERR_SINGULAR, "zero pivot in some block");
     if (any & TM_FLAG_NOT_CONVERGED) return set_err(c, TM_ERR_NOT_CONVERGED, "some system missed rtol");
@@ -994,23 +988,12 @@ tm_status tm_ye_newton_step(tm_ctx* c, const tm_inputs* in, const tm_ye_inputs* 
                                                          c->stream), "backtrack kernel"));
         }
     }
-    TM_TRY(hip_check(c, tmk::launch_final_flags(R, c->y_res, c->y_tgt, rtol, c->y_flags, c->stream), "flags kernel"));
-    if (stats) {
-        auto cp = [&](void* dst, const void* src, size_t bytes) -> tm_status {
-            if (!dst) return TM_OK;
-            return hip_check(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->stream), "copy stats");
-        };
-        TM_TRY(cp(stats->res_inf, c->y_res, R * sizeof(double)));
-        TM_TRY(cp(stats->res0_inf, c->y_res0, R * sizeof(double)));
-        TM_TRY(cp(stats->iters, c->y_iters, R * sizeof(int)));
-        TM_TRY(cp(stats->flags, c->y_flags, R * sizeof(int)));
-    }
-    std::vector<int> fl(R);
-    TM_TRY(hip_check(c, hipMemcpyAsync(fl.data(), c->y_flags, R * sizeof(int), hipMemcpyDeviceToHost, c->stream),
-                     "copy flags"));
+    TM_TRY(hip_check(c, tmk::launch_finish(R, c->y_res, c->y_res0, c->y_tgt, rtol, c->y_iters, c->y_flags,
+                                           stats ? stats->res_inf : nullptr, stats ? stats->res0_inf : nullptr,
+                                           stats ? stats->iters : nullptr, stats ? stats->flags : nullptr, c->h_count + 3,
+                                           c->stream), "finish kernel"));
     TM_TRY(hip_check(c, hipStreamSynchronize(c->stream), "stream sync"));
-    int any = 0;
-    for (int v : fl) any |= v;
+    const int any = c->h_count[3];
     if (any & TM_FLAG_NONFINITE) return set_err(c, TM_ERR_NONFINITE, "non-finite residual in some ray");
     if (any & TM_FLAG_ZERO_PIVOT) return set_err(c, TM_ERR_SINGULAR, "zero pivot in some coupled block");
     if (any & TM_FLAG_NOT_CONVERGED) return set_err(c, TM_ERR_NOT_CONVERGED, "some ray missed rtol");

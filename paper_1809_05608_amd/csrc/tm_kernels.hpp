@@ -113,11 +113,14 @@ hipError_t launch_vjp(const Shape& sh, const Fields& f, const Consts* cs, const 
 hipError_t launch_lum_seed(const Shape& sh, const double* r_edge, const double* lapse_edge, const Consts* cs,
                            const double* add, double* seed, hipStream_t st);
 
-hipError_t launch_final_flags(long long n, const double* res, const double* tgt, double rtol, int* flags,
-                              hipStream_t st);
+hipError_t launch_finish(long long n, const double* res, const double* res0, const double* tgt, double rtol,
+                         const int* iters, int* flags, double* res_out, double* res0_out, int* iters_out, int* flags_out,
+                         int* any, hipStream_t st);
+hipError_t launch_begin(long long n, int* iters, int* flags, int* pending, int* backtrack, int* guard, hipStream_t st);
 hipError_t launch_sys_absmax(const double* v, long long nsys, long long per_sys, double* out, hipStream_t st);
-// the indices of the set entries in ascending order, and their number
-hipError_t launch_list_active(const int* active, long long n, int* list, int* count, hipStream_t st);
+// active systems in ascending order; out (host memory): active, rejected trials, guard marks (cleared)
+hipError_t launch_tally(const int* active, const int* backtrack, int* guard, long long n, int* list, int* out,
+                        hipStream_t st);
 hipError_t launch_count_active(const int* active, long long n, int* count, hipStream_t st);
 
 // psi += (alpha/2 - alpha) dx and alpha /= 2 for systems with backtrack set (which is cleared)

@@ -761,23 +761,50 @@ hipError_t launch_sys_absmax(const double* v, long long nsys, long long per_sys,
 // Final per-system flags of a Newton step from the last evaluated (accepted) residual: keeps the
 // factorisation's zero-pivot / fallback bits, sets 1 when rtol > 0 and max|G| is above its target,
 // 2 when the residual is not finite.
-__global__ __launch_bounds__(kBlock) void k_final_flags(long long n, const double* __restrict__ res,
-                                                        const double* __restrict__ tgt, double rtol,
-                                                        int* __restrict__ flags) {
-    const long long s = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (s >= n) return;
-    const double r = res[s];
-    int fl = flags[s] & (4 | 8);
-    if (!isfinite(r)) fl |= 2;
-    else if (rtol > 0.0 && !(r <= tgt[s])) fl |= 1;
-    flags[s] = fl;
+// One block; also the per-system statistics the caller asked for, and all flags together in *any (host memory).
+__global__ __launch_bounds__(1024) void k_finish(long long n, const double* __restrict__ res, const double* __restrict__ res0,
+                                                 const double* __restrict__ tgt, double rtol, const int* __restrict__ iters,
+                                                 int* __restrict__ flags, double* res_out, double* res0_out, int* iters_out,
+                                                 int* flags_out, int* any) {
+    __shared__ int s_any;
+    if (threadIdx.x == 0) s_any = 0;
+    __syncthreads();
+    int all = 0;
+    for (long long s = threadIdx.x; s < n; s += 1024) {
+        const double r = res[s];
+        int fl = flags[s] & (4 | 8);
+        if (!isfinite(r)) fl |= 2;
+        else if (rtol > 0.0 && !(r <= tgt[s])) fl |= 1;
+        flags[s] = fl;
+        all |= fl;
+        if (res_out) res_out[s] = r;
+        if (res0_out) res0_out[s] = res0[s];
+        if (iters_out) iters_out[s] = iters[s];
+        if (flags_out) flags_out[s] = fl;
+    }
+    atomicOr(&s_any, all);
+    __syncthreads();
+    if (threadIdx.x == 0) *any = s_any;
 }
 
-hipError_t launch_final_flags(long long n, const double* res, const double* tgt, double rtol, int* flags,
-                              hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_final_flags, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, n, res,
-                       tgt, rtol, flags);
+hipError_t launch_finish(long long n, const double* res, const double* res0, const double* tgt, double rtol,
+                         const int* iters, int* flags, double* res_out, double* res0_out, int* iters_out, int* flags_out,
+                         int* any, hipStream_t st) {
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, st, n, res, res0, tgt, rtol, iters, flags, res_out, res0_out,
+                       iters_out, flags_out, any);
+    return hipGetLastError();
+}
+
+// The per-system state of a Newton step at its start.
+__global__ __launch_bounds__(kBlock) void k_begin(long long n, int* iters, int* flags, int* pending, int* backtrack,
+                                                  int* guard) {
+    const long long s = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (s < n) iters[s] = flags[s] = pending[s] = backtrack[s] = guard[s] = 0;
+}
+
+hipError_t launch_begin(long long n, int* iters, int* flags, int* pending, int* backtrack, int* guard, hipStream_t st) {
+    hipLaunchKernelGGL(k_begin, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, n, iters, flags, pending,
+                       backtrack, guard);
     return hipGetLastError();
 }
 
@@ -789,35 +816,49 @@ __global__ __launch_bounds__(kBlock) void k_count(const int* __restrict__ active
     if (threadIdx.x == 0) *count = (int)s;
 }
 
-// One block: each wavefront counts its stretch, then writes the indices behind those of the stretches before it.
-__global__ __launch_bounds__(1024) void k_list(const int* __restrict__ active, long long n, int* __restrict__ list,
-                                               int* __restrict__ count) {
-    __shared__ int s_n[16];
+// What the host decides by after a residual pass, in one launch: the active systems in ascending order, and in `out`
+// (host memory) how many they are, how many trials were rejected and how many systems tripped the growth guard since
+// the last call (the marks are cleared).  One block: each wavefront counts its stretch, then writes the indices
+// behind those of the stretches before it.
+__global__ __launch_bounds__(1024) void k_tally(const int* __restrict__ active, const int* __restrict__ backtrack,
+                                                int* __restrict__ guard, long long n, int* __restrict__ list, int* out) {
+    __shared__ int s_n[16][3];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const long long len = ((n + 1023) / 1024) * 64, lo = wave * len, hi = min(n, lo + len);
-    int mine = 0;
-    for (long long j = lo + lane; j < hi; j += 64) mine += active[j] != 0;
+    int mine[3] = {0, 0, 0};
+    for (long long j = lo + lane; j < hi; j += 64) {
+        const int g = guard[j];
+        mine[0] += active[j] != 0;
+        mine[1] += backtrack[j] != 0;
+        mine[2] += g != 0;
+        if (g) guard[j] = 0;
+    }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
-    if (lane == 0) s_n[wave] = mine;
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mine[k] += __shfl_xor(mine[k], o);
+        if (lane == 0) s_n[wave][k] = mine[k];
+    }
     __syncthreads();
     int at = 0;
-    for (int w = 0; w < 16; ++w) {
-        if (w == wave) mine = at;
-        at += s_n[w];
-    }
+    for (int w = 0; w < wave; ++w) at += s_n[w][0];
     for (long long j0 = lo; j0 < hi; j0 += 64) {
         const long long j = j0 + lane;
         const bool on = j < hi && active[j] != 0;
         const unsigned long long m = __ballot(on);
-        if (on) list[mine + __popcll(m & ((1ull << lane) - 1))] = (int)j;
-        mine += __popcll(m);
+        if (on) list[at + __popcll(m & ((1ull << lane) - 1))] = (int)j;
+        at += __popcll(m);
     }
-    if (threadIdx.x == 0) *count = at;
+    if (threadIdx.x < 3) {
+        int sum = 0;
+        for (int w = 0; w < 16; ++w) sum += s_n[w][threadIdx.x];
+        out[threadIdx.x] = sum;
+    }
 }
 
-hipError_t launch_list_active(const int* active, long long n, int* list, int* count, hipStream_t st) {
-    hipLaunchKernelGGL(k_list, dim3(1), dim3(1024), 0, st, active, n, list, count);
+hipError_t launch_tally(const int* active, const int* backtrack, int* guard, long long n, int* list, int* out,
+                        hipStream_t st) {
+    hipLaunchKernelGGL(k_tally, dim3(1), dim3(1024), 0, st, active, backtrack, guard, n, list, out);
     return hipGetLastError();
 }
 
