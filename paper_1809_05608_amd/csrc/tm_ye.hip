@@ -43,7 +43,7 @@ __device__ __forceinline__ double ye_zeta(double rho) { return kFourPiOverHc3 * 
 // Both kernels below take sixteen zones to a wavefront: lane 16 a + j holds groups a, 4 + a, 8 + a, ... of zone j, so
 // a sum over a zone's groups is T additions and one matrix product with ones, and the zone's own values are in
 // place in each of its lanes.  k_ye_couple is bound by its way through memory (the layout reads 32-byte pieces):
-// 2048 rays of 540 zones x 20 groups 0.88 -> 0.84 ms against one zone per wavefront with the sums by shuffles, with
+// 2048 rays of 540 zones x 20 groups 0.88 -> 0.54 ms against one zone per wavefront with the sums by shuffles, with
 // pairs and 90 rays, where a zone's chain of latencies counted, 0.45 -> 0.18.  k_ye_temperature takes the scattering
 // sums from the matrix cores (tm_nes.hpp): 5.0 -> 0.64 ms and with pairs 0.58 -> 0.07 against one thread per zone,
 // whose rows of groups went to scratch memory.
@@ -92,6 +92,14 @@ __device__ __forceinline__ void pair_sums(const PairLds<T>& sm, int N, int a, in
     }
 }
 
+// The lane's groups of a zone's row, padding repeating the last one.  All pieces of a row are asked for at once: array
+// by array within the loop over t, its lines were gone when the next piece came (2.3 times the bytes).
+template <int T>
+__device__ __forceinline__ void load_groups(const double* row, int a, int N, double (&v)[T]) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) v[t] = row[t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1)];
+}
+
 // PAIR compiles the pair sources in; the launch takes it when pair inputs are given.
 template <int T, bool PAIR>
 __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs,
@@ -135,13 +143,21 @@ __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFiel
                 pair_sums<T>(sp, N, a, q, y.pair_amp[zb + ic], drcp(f.temp[zb + ic]), drcp(0.5 * (re[ic] + re[ic + 1])),
                              y.pair_eta1 + cz, psi + co, y.pair_eta1 + co, cre, ann);
             }
+            double v_p[T], v_g[T], v_dk[T], v_de[T], v_et[T], v_ka[T];
+            load_groups<T>(psi + cz, a, N, v_p);
+            load_groups<T>(G + cz, a, N, v_g);
+            if (emabs) {
+                load_groups<T>(y.dka + cz, a, N, v_dk);
+                load_groups<T>(y.deta + cz, a, N, v_de);
+                load_groups<T>(f.eta + cz, a, N, v_et);
+                load_groups<T>(f.kappa_a + cz, a, N, v_ka);
+            }
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 const int k = 4 * t + a;
                 const bool real = in_zone && (t + 1 < T || k < N);
-                const size_t ci = cz + (t + 1 < T ? k : min(k, N - 1));
-                const double p = psi[ci], h = 1.0 - p;
-                double g = G[ci];
+                const double p = v_p[t], h = 1.0 - p;
+                double g = v_g[t];
                 if constexpr (PAIR) {
                     const double sc = h * cre[t], sa = p * ann[t];
                     g -= c * (sc - sa);
@@ -151,10 +167,10 @@ __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFiel
                 }
                 if (emabs) {
                     // with a lapse the fields are lapse-folded (a kappa_a, a eta): the derivatives get the same a
-                    const double dka = az * y.dka[ci], det = az * y.deta[ci];
+                    const double dka = az * v_dk[t], det = az * v_de[t];
                     const double slope = det * h - dka * p;
                     g -= c * dy * slope;                                 // opacities at Y_e instead of Y_e^n
-                    const double em = (f.eta[ci] + dy * det) * h, ab = (f.kappa_a[ci] + dy * dka) * p;
+                    const double em = (v_et[t] + dy * det) * h, ab = (v_ka[t] + dy * dka) * p;
                     const double sw = sgn * W[t];
                     sY = fma(sw, em - ab, sY);
                     sAbs = fma(W[t], fabs(em) + fabs(ab), sAbs);
@@ -162,7 +178,7 @@ __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFiel
                 }
                 sL = fma(sgn * W[t], p, sL);
                 if (real) {
-                    G[ci] = g;
+                    G[cz + k] = g;
                     bad |= !isfinite(g);
                     gmax = fmax(gmax, fabs(g));
                 }
@@ -709,8 +725,7 @@ __global__ __launch_bounds__(kBlock) void k_ye_temperature(Shape sh, Fields f, Y
     for (int s = 0; s < sh.S; ++s) {
         const size_t cz = ((size_t)s * nz + zi) * N;
         double p[T], acc = 0.0;
-#pragma unroll
-        for (int t = 0; t < T; ++t) p[t] = psi[cz + (t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1))];
+        load_groups<T>(psi + cz, a, N, p);
         if (nes) {
             const double amp = f.nes_amp[(size_t)s * nz + zi];
             double sin_[T], sout[T], sn = 0.0;
@@ -720,16 +735,21 @@ __global__ __launch_bounds__(kBlock) void k_ye_temperature(Shape sh, Fields f, Y
             acc = amp * sn;
         }
         if (emabs) {
+            double kap[T], eta[T];
+            load_groups<T>(f.kappa_a + cz, a, N, kap);
+            load_groups<T>(f.eta + cz, a, N, eta);
+            if (s < 2) {
+                double dk[T], de[T];
+                load_groups<T>(y.dka + cz, a, N, dk);
+                load_groups<T>(y.deta + cz, a, N, de);
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const size_t ci = cz + (t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1));
-                double kap = f.kappa_a[ci], eta = f.eta[ci];
-                if (s < 2) {
-                    kap = fma(dy, y.dka[ci], kap);
-                    eta = fma(dy, y.deta[ci], eta);
+                for (int t = 0; t < T; ++t) {
+                    kap[t] = fma(dy, dk[t], kap[t]);
+                    eta[t] = fma(dy, de[t], eta[t]);
                 }
-                acc = fma(eW[t], eta * (1.0 - p[t]) - kap * p[t], acc);
             }
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc = fma(eW[t], eta[t] * (1.0 - p[t]) - kap[t] * p[t], acc);
         }
         if constexpr (PAIR) {
             if (s < 2) {                                   // pair sources of species 0 and 1 (eqs. d11-d14)
