@@ -20,6 +20,12 @@ size_t factor_ws_bytes_per_system(int I, int N, bool fp32) {
 // 2.4.  The count is that of all batches: a batch takes the kernel that the whole would take.
 constexpr long long kWaveSystems = 768;
 
+// Up to four groups a block is one tile, and the tile kernel's wavefront carries two systems where lanes by rows
+// carry four: above this many systems, where all SIMDs are busy, the lanes are the
+// faster.  Tiles against lanes, 300 zones x 4 groups: 8192 systems 0.75 against 1.25 ms, 16384: 1.33 against 1.36,
+// 32768: 2.40 against 1.91; one group, 32768 systems: 2.06 against 1.50.
+constexpr long long kLaneSystems = 16384;
+
 // Up to this many systems a float32 launch leaves the chip waiting for one wavefront's chain of zones, 16 systems
 // from one end: the FP64 kernels with two or half a system per wavefront from both ends are faster up to about
 // twice as many, float32 the faster above for half the bytes of factors.  float32 against FP64, 540 zones x 20
@@ -53,7 +59,8 @@ hipError_t launch_factor(const FactorArgs& a, bool fp32, bool transpose, bool pi
     // addresses the cells of two systems with 32-bit byte offsets.
     if (!fp32 && !pivot) {
         const bool few = a.total <= kWaveSystems, far = (long long)a.sh.I * a.sh.N >= (1ll << 27);
-        return few || far ? launch_factor_wave(a, transpose, st) : launch_factor_tile(a, transpose, st);
+        const bool lanes = a.sh.N <= 4 && a.total > kLaneSystems && !a.list;
+        if (!lanes) return few || far ? launch_factor_wave(a, transpose, st) : launch_factor_tile(a, transpose, st);
     }
     if (a.sh.limiter == 2 || a.sh.outer_bc == 2) return launch_factor_geo(a, fp32, transpose, pivot, st);
     return launch_lane<false>(a, fp32, transpose, pivot, st);

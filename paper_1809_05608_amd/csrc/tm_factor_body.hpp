@@ -1,8 +1,9 @@
 // Fused Jacobian assembly + block-Thomas factor/solve of the linearised transport
 // step (eq. a62ae), one (species, ray) system per SL-lane group of a wavefront.
 //
-// These lane kernels serve the partial-pivoting re-run (both precisions) and the float32 solves that the
-// quad kernel does not take; FP64 solves with diagonal pivots run on matrix-core tiles (tm_factor_t.hip).
+// These lane kernels serve the partial-pivoting re-run (both precisions), the float32 solves that the quad kernel
+// does not take and FP64 solves of very many systems of up to four groups; the other FP64 solves with diagonal
+// pivots run on matrix-core tiles (tm_factor_t.hip, tm_factor_w.hip).
 //
 // Layout on the chip: lane k of a group owns row k of the current zone's dense N x N
 // block (N <= NT <= 32, SL = 16 or 32 lanes per system, 4 or 2 systems per wave64).
@@ -617,7 +618,7 @@ static void launch_tp(const FactorArgs& a, bool tr, bool pv, hipStream_t st) {
     if (pv) {
         if (tr) launch_t<T, NT, true, true, GEO>(a, st);
         else launch_t<T, NT, false, true, GEO>(a, st);
-    } else if constexpr (std::is_same<T, float>::value) {           // FP64 with diagonal pivots: k_factor_tile
+    } else if constexpr (std::is_same<T, float>::value || NT == 4) {    // FP64 with diagonal pivots: k_factor_tile
         if (tr) launch_t<T, NT, true, false, GEO>(a, st);
         else launch_t<T, NT, false, false, GEO>(a, st);
     }

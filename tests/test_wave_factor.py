@@ -79,10 +79,12 @@ def test_coupled_elimination_matches_oracle(shape, option, monkeypatch):
 @pytest.mark.parametrize("option", ["plain", "lapse", "geometric"])
 @pytest.mark.parametrize("shape", [dict(S=2, R=384, I=3, N=4), dict(S=1, R=769, I=1, N=5), dict(S=3, R=257, I=2, N=12),
                                    dict(S=1, R=771, I=4, N=17), dict(S=1, R=770, I=5, N=20), dict(S=1, R=773, I=3, N=29),
-                                   dict(S=1, R=772, I=6, N=32)])
+                                   dict(S=1, R=772, I=6, N=32),
+                                   dict(S=1, R=16384, I=3, N=4), dict(S=1, R=16389, I=3, N=4), dict(S=3, R=5463, I=2, N=3)])
 def test_eliminations_on_both_sides_of_the_system_count(shape, option):
     """768 systems (wavefronts per half system), and just more (four half systems to a wavefront, the last one
-    partly filled), plain and transposed, sampled systems against the oracle.  Bar: 1e-11 of max|x|."""
+    partly filled), and up to four groups more than 16384 systems (lanes by rows), plain and transposed, sampled
+    systems against the oracle.  Bar: 1e-11 of max|x|."""
     print("case either side", shape, option, flush=True)
     sys.stdout.flush()
     w, over = _case(shape, option)
