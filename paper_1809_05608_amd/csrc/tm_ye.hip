@@ -67,21 +67,27 @@ struct PairLds {
     }
 };
 template <int T>
-__device__ __forceinline__ void pair_sums(const PairLds<T>& sm, int N, int a, int q, double amp, double iT, double iR,
+__device__ __forceinline__ void pair_sums(const PairLds<T>& sm, int N, int a, int q, double amp, double iT, double R,
                                           const double* eta_q, const double* psi_o, const double* eta_o,
                                           double (&cre)[T], double (&ann)[T]) {
     const ExpCoef coef = exp_coef();
+    // R_nu / R to the last bit (1 where they are equal): the cosine of a quotient one ulp from 1 is 1e-8, not 0
+    const double iR = drcp(R);
+    auto cosine = [&](double rnu) {
+        const double x = rnu * iR;
+        return pair_limb_cosine(fma(fma(-x, R, rnu), iR, x));
+    };
     double eo[T], mo[T], bk[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int k = t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1);
         eo[t] = eta_q[k];
-        mo[t] = pair_limb_cosine(sm.rnu[q][k] * iR);
+        mo[t] = cosine(sm.rnu[q][k]);
         bk[t] = exp_nonpos(-sm.eps[k] * iT, coef);
         cre[t] = ann[t] = 0.0;
     }
     for (int kp = 0; kp < N; ++kp) {
-        const double pb = psi_o[kp], eb = eta_o[kp], mb = pair_limb_cosine(sm.rnu[1 - q][kp] * iR);
+        const double pb = psi_o[kp], eb = eta_o[kp], mb = cosine(sm.rnu[1 - q][kp]);
         const double cb = amp * exp_nonpos(-sm.eps[kp] * iT, coef) * (1.0 - pb), ab = amp * pb;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
@@ -140,7 +146,7 @@ __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFiel
             double cre[T], ann[T];
             if constexpr (PAIR) {
                 const size_t co = (((size_t)(1 - q) * R + ray) * I + ic) * N;
-                pair_sums<T>(sp, N, a, q, y.pair_amp[zb + ic], drcp(f.temp[zb + ic]), drcp(0.5 * (re[ic] + re[ic + 1])),
+                pair_sums<T>(sp, N, a, q, y.pair_amp[zb + ic], drcp(f.temp[zb + ic]), 0.5 * (re[ic] + re[ic + 1]),
                              y.pair_eta1 + cz, psi + co, y.pair_eta1 + co, cre, ann);
             }
             double v_p[T], v_g[T], v_dk[T], v_de[T], v_et[T], v_ka[T];
@@ -756,7 +762,7 @@ __global__ __launch_bounds__(kBlock) void k_ye_temperature(Shape sh, Fields f, Y
                 const double* re = f.r_edge + (zi / I) * (I + 1) + zi % I;
                 const size_t co = ((size_t)(1 - s) * nz + zi) * N;
                 double cre[T], ann[T];
-                pair_sums<T>(sp, N, a, s, y.pair_amp[zi], iT, drcp(0.5 * (re[0] + re[1])), y.pair_eta1 + cz, psi + co,
+                pair_sums<T>(sp, N, a, s, y.pair_amp[zi], iT, 0.5 * (re[0] + re[1]), y.pair_eta1 + cz, psi + co,
                              y.pair_eta1 + co, cre, ann);
 #pragma unroll
                 for (int t = 0; t < T; ++t) acc = fma(eW[t], (1.0 - p[t]) * cre[t] - p[t] * ann[t], acc);
