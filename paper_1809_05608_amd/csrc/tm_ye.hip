@@ -98,6 +98,13 @@ __device__ __forceinline__ void pair_sums(const PairLds<T>& sm, int N, int a, in
     }
 }
 
+// 1/T of detailed-balance factors exp(-x/T): at T = 0 a factor is 0 and that of x = 0 is 1, at infinite T all are 1 (a
+// reciprocal by Newton steps is NaN at both).
+__device__ __forceinline__ double inv_temp(double T) {
+    const double r = 1.0 / T;
+    return r > 1e290 ? 1e290 : r;
+}
+
 // The lane's groups of a zone's row, padding repeating the last one.  All pieces of a row are asked for at once: array
 // by array within the loop over t, its lines were gone when the next piece came (2.3 times the bytes).
 template <int T>
@@ -146,7 +153,7 @@ __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFiel
             double cre[T], ann[T];
             if constexpr (PAIR) {
                 const size_t co = (((size_t)(1 - q) * R + ray) * I + ic) * N;
-                pair_sums<T>(sp, N, a, q, y.pair_amp[zb + ic], drcp(f.temp[zb + ic]), 0.5 * (re[ic] + re[ic + 1]),
+                pair_sums<T>(sp, N, a, q, y.pair_amp[zb + ic], inv_temp(f.temp[zb + ic]), 0.5 * (re[ic] + re[ic + 1]),
                              y.pair_eta1 + cz, psi + co, y.pair_eta1 + co, cre, ann);
             }
             double v_p[T], v_g[T], v_dk[T], v_de[T], v_et[T], v_ka[T];
@@ -716,7 +723,7 @@ __global__ __launch_bounds__(kBlock) void k_ye_temperature(Shape sh, Fields f, Y
     const long long nz = (long long)R * I;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a = lane >> 4, j = lane & 15, b = lane & 3;
     const long long idx = ((long long)blockIdx.x * (kBlock / 64) + wave) * 16 + j, zi = min(idx, nz - 1);
-    const double Tz = f.temp[zi], iT = drcp(Tz), dy = ye[zi] - y.ye_n[zi];
+    const double Tz = f.temp[zi], iT = inv_temp(Tz), dy = ye[zi] - y.ye_n[zi];
     double eW[T], d[T];
     {
         const ExpCoef coef = exp_coef();

@@ -1,7 +1,9 @@
-"""Pair processes where a rounding shows: a neutrinosphere radius equal to a zone centre, where the limb cosine of
-eq. d22 is exactly 0 and the root of 1 - (R_nu/R)^2 turns an ulp of the quotient into 1e-8.
+"""Pair processes where a rounding or a limit shows: a neutrinosphere radius equal to a zone centre, where the limb
+cosine of eq. d22 is exactly 0 and the root of 1 - (R_nu/R)^2 turns an ulp of the quotient into 1e-8, and zones at
+T = 0, where every detailed-balance factor is 0.
 
-Bar: 1e-13 of the sum of a zone's pair terms (about 50 roundings, with up to 5 ulp of the cosines at the next zone).
+Bars: 1e-13 of the sum of a zone's pair terms (about 50 roundings, with up to 5 ulp of the cosines at the next zone);
+the coupled step's 1e-12 otherwise.
 """
 import dataclasses
 import sys
@@ -14,6 +16,7 @@ import oracle
 import synth
 from oracle import ye_coupled as yc
 from paper_1809_05608_amd import tm
+from test_gpu_pair import BAR, _compare, _oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +58,38 @@ def test_neutrinosphere_at_a_zone_centre(R, I, N):
         de_o, _ = yc.temperature_update(cs, [], yc.pack(psi[0, r], psi[1, r], cs.ye_n), [], (1.0, 1.0), wn["temp"][r],
                                         yn["de_dT"][r], yn["de_dye"][r])
         assert np.max(np.abs(de[r] - de_o) / scale) < 1e-13, r
+
+
+@pytest.mark.parametrize("N", [4, 20])
+def test_zones_at_zero_temperature(N):
+    """As temperatures of 1e-30 MeV, which the oracle takes."""
+    print("case pair zero temperature", N, flush=True)
+    sys.stdout.flush()
+    w = synth.make_custom(S=3, R=3, I=24, N=N)
+    T = w.temp.clone()
+    T[:, ::5] = 0.0
+    T[2] = 0.0
+    w = dataclasses.replace(w, temp=T.contiguous())
+    near = dataclasses.replace(w, temp=torch.where(T == 0.0, torch.full_like(T, 1e-30), T).contiguous())
+    y = dataclasses.replace(synth.ye_inputs(w, 0, R_full=3, pairs=True), pair_amp=torch.full_like(w.temp, 1e-7))
+    rng = np.random.default_rng(3)
+    psi = rng.uniform(0.0, 1.0, tuple(w.psi_n.shape))
+    T1, de = _temperature(w, y, psi)                   # with scattering
+    wn, yn = near.numpy(), y.numpy()
+    sy = oracle.systems_from_workload(wn)
+    for r, cs in enumerate(yc.coupled_systems(wn, yn)):
+        de_o, T_o = yc.temperature_update(cs, [sy[2][r]], yc.pack(psi[0, r], psi[1, r], cs.ye_n), [psi[2, r]], (1.0,) * 3,
+                                          wn["temp"][r], yn["de_dT"][r], yn["de_dye"][r])
+        assert np.max(np.abs(de[r] - de_o)) <= 1e-12 * np.max(np.abs(de_o))
+        assert np.max(np.abs(T1[r] - T_o)) <= 1e-12 * np.max(np.abs(T_o))
+    terms = dict(terms=synth.TERM_DIFFUSION | synth.TERM_EMABS)    # the species residual divides by T
+    w, near = dataclasses.replace(w, **terms), dataclasses.replace(near, **terms)
+    wd, yd = w.to("cuda"), y.to("cuda")
+    ctx = tm.Context(tm.problem_of(wd))
+    p, ye = wd.psi_n.clone(), yd.ye_n.clone()
+    st, stats = ctx.ye_newton_step(tm.DeviceFields.of(wd), yd, wd.psi_n, p, ye, 3, 0.0, raise_on_status=False)
+    torch.cuda.synchronize()
+    assert st == tm.TM_OK and np.all(stats["iters"].cpu().numpy() == 3)
+    e, ey = _compare(w, p.cpu().numpy(), ye.cpu().numpy(), _oracle(near, y, 3, 0.0))
+    assert e < BAR and ey < BAR
+    ctx.close()
