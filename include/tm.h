@@ -289,7 +289,8 @@ tm_status tm_luminosity_seed(tm_ctx *ctx, const tm_inputs *in, const double *add
  * free path (diffusion) stays at the opacities of Y_e^n.  NES does not depend on Y_e.
  * The linearised system is block tridiagonal with (2N+1)-square diagonal blocks (psi of
  * both species and Y_e of a zone) and diagonal off-diagonal blocks whose Y_e entries are
- * zero; it is eliminated by block-Thomas with partial pivoting inside each block.
+ * zero; it is eliminated by block-Thomas with diagonal pivots under the growth guard of
+ * tm_factor_solve, a ray that trips it with partial pivoting inside each block.
  * Species 2..S-1 are independent of Y_e and are advanced by tm_newton_step on a problem
  * of their own (their arrays are the tail of the cell, sysz arrays).
  * --------------------------------------------------------------------------------- */
@@ -322,7 +323,8 @@ typedef struct {             /* every array is per ray [R], device memory       
                                 sum_i V_i [rho_i Y_e,i / m_B + (4 pi/(hc)^3) sum_k W_k
                                 (psi_0 - psi_1)] at the returned state (may be NULL)         */
     int32_t *iters;          /* Newton updates applied                                      */
-    int32_t *flags;          /* TM_FLAG_* bits (TM_FLAG_ZERO_PIVOT: a zero pivot met)          */
+    int32_t *flags;          /* TM_FLAG_* bits (TM_FLAG_ZERO_PIVOT: a zero pivot met;
+                                TM_FLAG_PIVOT_FALLBACK as for a system of the single-species step) */
 } tm_ye_stats;
 
 /* Device bytes of workspace needed to factor `batch_rays` coupled systems per launch
