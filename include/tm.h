@@ -130,7 +130,7 @@ typedef struct {
     const double *kappa_a;  /* cell, cm^-1, absorption inverse mean free path            */
     const double *eta;      /* cell, cm^-1, emissivity j (emission per state per length)  */
     const double *kappa_s;  /* cell, cm^-1, isoenergetic scattering (transport opacity)   */
-    const double *temp;     /* zone, MeV (> 0), used by the NES detailed balance          */
+    const double *temp;     /* zone, MeV (> 0), used by the detailed balance of NES and pairs */
     const double *nes_amp;  /* sysz, cm^-1; may be NULL when TM_TERM_NES is off          */
     const double *nes_g;    /* [N][N] symmetric shape; may be NULL when TM_TERM_NES is off */
     const double *lapse;    /* zone [R][I], lapse a_i at zone centres (> 0); NULL: a = 1       */
@@ -308,7 +308,7 @@ typedef struct {
      * of W), Q^p = exp(-(eps_k + eps_k')/T_i) Q^a (eq. d12), chi = min(chi_1, chi_2) with
      * chi_1 = 1 - (3/2) eta_k eta'_k' (the ratio that defines eq. d16, for the flux factors
      * eta = psi1/psi0 given here) and chi_2 of eq. d19 from the cosines of eq. d22 at the zone
-     * centre (R_nu from tm_inputs.r_nu, which is then required).  The sources join the species
+     * centre (R_nu from tm_inputs.r_nu; it and tm_inputs.temp are then required).  The sources join the species
      * residuals (minus c dt S), the coupled Jacobian (cross-species blocks) and the
      * temperature update's collision energy.                                            */
     const double *pair_amp;  /* zone [R][I] cm^-1, kernel amplitude a_i, or NULL           */

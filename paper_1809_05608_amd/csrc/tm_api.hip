@@ -868,6 +868,8 @@ tm_status tm_ye_newton_step(tm_ctx* c, const tm_inputs* in, const tm_ye_inputs* 
     TM_TRY(check_ye_inputs(c, yin));
     if (yin->pair_amp && !in->r_nu)
         return set_err(c, TM_ERR_INVALID_ARG, "the pair processes need r_nu (their angular factor uses R_nu)");
+    if (yin->pair_amp && !in->temp)
+        return set_err(c, TM_ERR_INVALID_ARG, "the pair processes need temp (detailed balance)");
     if (yin->pair_amp && in->lapse)
         return set_err(c, TM_ERR_INVALID_ARG, "the pair processes take no lapse (lapse must be NULL with pair_amp)");
     if (c->p.precision != TM_PREC_FP64)

@@ -5,6 +5,7 @@ T = 0, where every detailed-balance factor is 0.
 Bars: 1e-13 of the sum of a zone's pair terms (about 50 roundings, with up to 5 ulp of the cosines at the next zone);
 the coupled step's 1e-12 otherwise.
 """
+import ctypes
 import dataclasses
 import sys
 
@@ -92,4 +93,20 @@ def test_zones_at_zero_temperature(N):
     assert st == tm.TM_OK and np.all(stats["iters"].cpu().numpy() == 3)
     e, ey = _compare(w, p.cpu().numpy(), ye.cpu().numpy(), _oracle(near, y, 3, 0.0))
     assert e < BAR and ey < BAR
+    ctx.close()
+
+
+def test_pairs_without_a_temperature_are_refused():
+    """Scattering off, pairs on, temp NULL: refused before any device work (the kernels read it)."""
+    print("case pair without temp", flush=True)
+    sys.stdout.flush()
+    w = synth.make_custom(S=2, R=2, I=6, N=4, terms=synth.TERM_DIFFUSION | synth.TERM_EMABS)
+    y = synth.ye_inputs(w, 0, R_full=2, pairs=True)
+    wd, yd = w.to("cuda"), y.to("cuda")
+    ctx = tm.Context(tm.problem_of(wd))
+    inp, yin = ctx._inputs(tm.DeviceFields.of(wd)), ctx._ye_inputs(yd)
+    inp.temp = None
+    st = ctx.lib.tm_ye_newton_step(ctx._h, ctypes.byref(inp), ctypes.byref(yin), tm._ptr(wd.psi_n), tm._ptr(wd.psi_n.clone()),
+                                   tm._ptr(yd.ye_n.clone()), 1, 0.0, None)
+    assert tm.STATUS_NAMES[st] == "TM_ERR_INVALID_ARG"
     ctx.close()
