@@ -172,6 +172,68 @@ __device__ __forceinline__ D& at(D* base, unsigned off) {
     return *(D*)((uintptr_t)base + off);
 }
 
+// A residual pass's end for one system, by all threads of its block: max|G|, the rounding level, the Newton and
+// line-search decisions, the conservation sums.  `bad`: the thread met a G that is not finite.
+struct ResidualSums {
+    double n = 0.0, nold = 0.0, e = 0.0, q = 0.0, nes = 0.0, b = 0.0;
+};
+__device__ __forceinline__ void residual_end(const Shape& sh, const Fields& f, const ResidualOut& out, long long sys,
+                                             double gmax, double gscale, int bad, ResidualSums s, double* red) {
+    const int I = sh.I, ray = (int)(sys % sh.R);
+    const double res = block_max(gmax, red);
+    const double floor_g = 32.0 * 2.220446049250313e-16 * block_max(gscale, red);
+    bad = block_or(bad, red);
+    if (out.stats) {
+        s.n = block_sum(s.n, red);
+        s.nold = block_sum(s.nold, red);
+        s.e = block_sum(s.e, red);
+        s.q = block_sum(s.q, red);
+        s.nes = block_sum(s.nes, red);
+        s.b = block_sum(s.b, red);
+    }
+    if (threadIdx.x == 0) {
+        const double rr = bad ? __builtin_nan("") : res;
+        out.res[sys] = rr;
+        if (out.level) out.level[sys] = floor_g;
+        const int it = out.iters ? out.iters[sys] : 0;
+        if (out.mode == kResInitial) {
+            // Newton stopping rule: max|G| <= target = max(rtol * max|G_0|, rounding level of G), or no
+            // halving of max|G| within 1000x of the target; rtol = 0 means a fixed number of updates
+            const double target = fmax(out.rtol * rr, floor_g);
+            out.res0[sys] = rr;
+            out.res_acc[sys] = rr;
+            out.tgt[sys] = target;
+            const bool stop = out.rtol > 0.0 && !bad && rr <= target;
+            out.active[sys] = (!stop && !bad && it < out.max_iter && rr > 0.0) ? 1 : 0;
+        } else if (out.mode == kResTrial) {
+            // backtracking line search: accept the trial on sufficient decrease of max|G|, at the
+            // shortest step, or when the previous iterate was already within 1000x of its target
+            const double racc = out.res_acc[sys], a = out.alpha[sys];
+            const bool near = racc <= 1e3 * out.tgt[sys];
+            const bool accept = near || rr <= (1.0 - kArmijo * a) * racc || a <= kAlphaMin;
+            if (accept) {
+                const double target = fmax(out.rtol * out.res0[sys], floor_g);
+                out.pending[sys] = 0;
+                out.backtrack[sys] = 0;
+                out.res_acc[sys] = rr;
+                out.tgt[sys] = target;
+                const bool stop = out.rtol > 0.0 && !bad && (rr <= target || (rr <= 1e3 * target && rr > 0.5 * racc));
+                out.active[sys] = (!stop && !bad && it < out.max_iter && rr > 0.0) ? 1 : 0;
+            } else {
+                out.backtrack[sys] = 1;
+            }
+        }
+        if (out.stats) {
+            const double rI = f.r_edge[(size_t)ray * (I + 1) + I], rout = rI * rI * lapse_edge_inv2(f, (size_t)ray * (I + 1) + I);
+            const double b = sh.c_dt * rout * s.b;
+            if (out.n_tot) out.n_tot[sys] = s.n;
+            if (out.e_tot) out.e_tot[sys] = s.e;
+            if (out.budget) out.budget[sys] = s.n - s.nold + b - s.q - s.nes;
+            if (out.lum) out.lum[sys] = kCLight * rout * s.b;
+        }
+    }
+}
+
 // GEO compiles the neutrinosphere options (limiter 2, outer boundary 2) in.
 template <int T, bool GEO>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(T <= 3 ? 4 : T <= 6 ? 3 : 2)))
@@ -207,7 +269,7 @@ void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double*
 
     double gmax = 0.0, gscale = 0.0;
     int bad = 0;
-    double s_n = 0.0, s_nold = 0.0, s_e = 0.0, s_q = 0.0, s_nes = 0.0, s_b = 0.0;
+    ResidualSums sums;
     const size_t cells = (size_t)sys * I * N;
     const double* const zT = f.temp ? f.temp + (size_t)ray * I : re;
     const double* const zA = f.nes_amp ? f.nes_amp + (size_t)sys * I : re;
@@ -348,15 +410,15 @@ void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double*
                 w_e = fma(s_We[k], p[t], w_e);
                 w_q = fma(Wk, em, w_q);
                 w_nes = fma(Wk, S, w_nes);
-                if (i == I - 1 && diff) s_b = fma(Wk, H, s_b);
+                if (i == I - 1 && diff) sums.b = fma(Wk, H, sums.b);
             }
         }
         if (out.stats && out_row) {
-            s_n = fma(V, w_n, s_n);
-            s_nold = fma(V, w_old, s_nold);
-            s_e = fma(V, w_e, s_e);
-            s_q = fma(-c * V, w_q, s_q);
-            s_nes = fma(c * V * amp, w_nes, s_nes);
+            sums.n = fma(V, w_n, sums.n);
+            sums.nold = fma(V, w_old, sums.nold);
+            sums.e = fma(V, w_e, sums.e);
+            sums.q = fma(-c * V, w_q, sums.q);
+            sums.nes = fma(c * V * amp, w_nes, sums.nes);
         }
         wave_sync();
         if (G_out) {
@@ -370,58 +432,237 @@ void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double*
         wave_sync();
     }
 
-    const double res = block_max(gmax, red);
-    const double floor_g = 32.0 * 2.220446049250313e-16 * block_max(gscale, red);
-    bad = block_or(bad, red);
-    if (out.stats) {
-        s_n = block_sum(s_n, red);
-        s_nold = block_sum(s_nold, red);
-        s_e = block_sum(s_e, red);
-        s_q = block_sum(s_q, red);
-        s_nes = block_sum(s_nes, red);
-        s_b = block_sum(s_b, red);
-    }
-    if (threadIdx.x == 0) {
-        const double rr = bad ? __builtin_nan("") : res;
-        out.res[sys] = rr;
-        if (out.level) out.level[sys] = floor_g;
-        const int it = out.iters ? out.iters[sys] : 0;
-        if (out.mode == kResInitial) {
-            // Newton stopping rule: max|G| <= target = max(rtol * max|G_0|, rounding level of G), or no
-            // halving of max|G| within 1000x of the target; rtol = 0 means a fixed number of updates
-            const double target = fmax(out.rtol * rr, floor_g);
-            out.res0[sys] = rr;
-            out.res_acc[sys] = rr;
-            out.tgt[sys] = target;
-            const bool stop = out.rtol > 0.0 && !bad && rr <= target;
-            out.active[sys] = (!stop && !bad && it < out.max_iter && rr > 0.0) ? 1 : 0;
-        } else if (out.mode == kResTrial) {
-            // backtracking line search: accept the trial on sufficient decrease of max|G|, at the
-            // shortest step, or when the previous iterate was already within 1000x of its target
-            const double racc = out.res_acc[sys], a = out.alpha[sys];
-            const bool near = racc <= 1e3 * out.tgt[sys];
-            const bool accept = near || rr <= (1.0 - kArmijo * a) * racc || a <= kAlphaMin;
-            if (accept) {
-                const double target = fmax(out.rtol * out.res0[sys], floor_g);
-                out.pending[sys] = 0;
-                out.backtrack[sys] = 0;
-                out.res_acc[sys] = rr;
-                out.tgt[sys] = target;
-                const bool stop = out.rtol > 0.0 && !bad && (rr <= target || (rr <= 1e3 * target && rr > 0.5 * racc));
-                out.active[sys] = (!stop && !bad && it < out.max_iter && rr > 0.0) ? 1 : 0;
-            } else {
-                out.backtrack[sys] = 1;
+    residual_end(sh, f, out, sys, gmax, gscale, bad, sums, red);
+}
+
+// Up to four groups a zone is a single column of the matrix products above, a quarter to all of it padding, and a
+// chunk's way through LDS and the sums of products cost more than they save: here a thread is a cell.  The 256 threads
+// form 64 rows of four groups; row r of a chunk holds zone z0 - 1 + r, the first and the last row being halo.  Every
+// cell brings psi and its mean free path to LDS, computes the flux at its upper edge, and then G from both fluxes of
+// its zone and the scattering sums over the zone's row, in Horner form.  The next chunk's loads are in flight while
+// a chunk is worked on.  Latency and LDS bound it.  100 zones, against the sixteen-zone chunks above: 65536 systems
+// of one group 0.45 against 0.55 ms, of four 0.52 against 0.60; 256 systems of four 19.9 against 21.5 us.
+// LAPSE and GEO compile the lapse factors and the neutrinosphere options in.
+template <bool LAPSE, bool GEO>
+__global__ __launch_bounds__(kBlock) void k_residual_rows(Shape sh, Fields f, const Consts* __restrict__ cs,
+                                                          const double* __restrict__ psi_n,
+                                                          const double* __restrict__ psi, double* __restrict__ G_out,
+                                                          double g_sign, ResidualOut out) {
+    constexpr int NT = 4;
+    constexpr int RZ = kBlock / NT;             // rows per chunk (zones incl. one halo on each side)
+    constexpr int ZB = RZ - 2;                  // output zones per chunk
+    constexpr int PS = NT + 1;                  // padded LDS row stride (conflict-free column reads)
+    static_assert(3 * RZ + 2 <= kBlock, "one zone value per thread");
+    __shared__ double s_P[NT * PS];
+    __shared__ double s_psi[RZ][PS];
+    __shared__ double2 s_pq[RZ][NT];            // psi and 1 - psi of the row (the NES sums read both at once)
+    __shared__ double s_lam[RZ][PS];
+    __shared__ double s_d[RZ][PS];
+    __shared__ double s_H[RZ][PS];              // flux at the upper edge of the row's zone
+    __shared__ double s_du[RZ][PS];             // its derivative with respect to the lower zone
+    __shared__ double s_dv[RZ][PS];             // ... and to the upper zone
+    __shared__ double s_z[3 * RZ + 2];          // edges z0-1 .. z0+RZ, then T and amp of the rows
+    __shared__ double red[kBlock / 64];
+    double* const s_re = s_z;
+    double* const s_T = s_z + RZ + 2;
+    double* const s_amp = s_z + 2 * RZ + 2;
+    const long long sys = blockIdx.x;
+    if (out.mode == kResTrial && out.pending[sys] == 0) return;         // no trial to evaluate
+    if (out.mode == kResEval && out.pending && out.pending[sys % sh.R] == 0) return;
+    const int I = sh.I, N = sh.N;
+    const int ray = (int)(sys % sh.R);
+    const double* re = f.r_edge + (size_t)ray * (I + 1);
+    const double c = sh.c_dt;
+    const bool diff = sh.terms & kDiffusion, emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
+    const int t = threadIdx.x, zl = t / NT, k = t - zl * NT;
+    const bool lane_ok = k < N;
+    const bool out_row = zl >= 1 && zl <= RZ - 2;
+
+    if (nes)
+        for (int j = t; j < NT * NT; j += kBlock) s_P[(j / NT) * PS + (j % NT)] = cs->P[j / NT][j % NT];
+
+    double gmax = 0.0, gscale = 0.0;
+    int bad = 0;
+    ResidualSums sums;
+    const double Wk = lane_ok ? cs->W[k] : 0.0;
+    const double epsk = lane_ok ? cs->eps[k] : 0.0;
+    const bool geo = GEO && (sh.limiter == 2 || sh.outer_bc == 2);   // neutrinosphere radii in use
+    const double rnuk = (geo && lane_ok) ? f.r_nu[(size_t)(sys / sh.R) * N + k] : 0.0;
+    const double dek = (lane_ok && k + 1 < N) ? cs->de[k] : 0.0;
+    const size_t sys_cell0 = (size_t)sys * I * N;
+
+    // per-thread inputs of one chunk: the cell's fields and one zone value
+    struct In {
+        double p, ka, et, ks, pn, zv;
+    };
+    // Every load is issued unconditionally from a clamped, in-bounds address and the value selected
+    // afterwards: straight-line code lets the wait for a chunk's data count exactly the loads
+    // issued after it, instead of draining the memory pipe.
+    auto load = [&](int z0, In& v) {
+        const int i = z0 - 1 + zl;
+        const bool in_zone = lane_ok && i >= 0 && i < I;
+        const bool outc = in_zone && out_row;
+        const size_t cb = sys_cell0 + (in_zone ? (size_t)i * N + k : 0);
+        const double lp = psi[cb], lka = f.kappa_a[cb], let = f.eta[cb], lks = f.kappa_s[cb], lpn = psi_n[cb];
+        const bool opac = diff ? in_zone : (emabs && outc);
+        v.p = (diff ? in_zone : outc) ? lp : 0.0;
+        v.ka = opac ? lka : 0.0;
+        v.et = opac ? let : 0.0;
+        v.ks = (diff && in_zone) ? lks : 0.0;
+        v.pn = outc ? lpn : 0.0;
+        const double* src = re;
+        bool zok = false;
+        double zdef = 0.0;
+        if (t < RZ + 2) {
+            const int j = z0 - 1 + t;
+            zok = j >= 0 && j <= I;
+            src = re + (zok ? j : 0);
+        } else if (t < 2 * RZ + 2) {
+            const int j = z0 - 1 + (t - RZ - 2);
+            zok = nes && j >= 0 && j < I;
+            src = zok ? f.temp + (size_t)ray * I + j : re;
+            zdef = 1.0;
+        } else if (t < 3 * RZ + 2) {
+            const int j = z0 - 1 + (t - 2 * RZ - 2);
+            zok = nes && j >= 0 && j < I;
+            src = zok ? f.nes_amp + (size_t)sys * I + j : re;
+        }
+        const double lz = *src;
+        v.zv = zok ? lz : zdef;
+    };
+
+    In cur;
+    load(0, cur);
+    for (int z0 = 0; z0 < I; z0 += ZB) {
+        In nxt;
+        load(z0 + ZB, nxt);                                 // in flight while this chunk is processed
+        const int i = z0 - 1 + zl;                          // this row's zone (may be a halo or outside)
+        const bool in_zone = lane_ok && i >= 0 && i < I;
+        const double p = cur.p;
+        const double lam = (diff && in_zone) ? drcp(cur.ka + cur.et + cur.ks) : 0.0;
+        __syncthreads();                                    // previous chunk done with the LDS rows
+        s_psi[zl][k] = p;
+        if (nes) s_pq[zl][k] = make_double2(p, 1.0 - p);
+        s_lam[zl][k] = lam;
+        if (t < 3 * RZ + 2) s_z[t] = cur.zv;
+        __syncthreads();
+        s_d[zl][k] = (nes && in_zone && out_row && k + 1 < N) ? exp(-dek * drcp(s_T[zl])) : 0.0;
+        // flux at the upper edge of this row's zone, computed once per edge
+        if (diff) {
+            double H = 0.0, du = 0.0, dv = 0.0;
+            if (in_zone && zl + 1 < RZ) {
+                if (i + 1 < I) {
+                    const double rlo = s_re[zl], rhi = s_re[zl + 1], rp = s_re[zl + 2];
+                    const double D = 0.5 * (rhi + rp) - 0.5 * (rlo + rhi);
+                    const EdgeFlux e = edge_flux(p, s_psi[zl + 1][k], sqrt(lam * s_lam[zl + 1][k]), D,
+                                                 sh.psi_floor, sh.limiter,
+                                                 (GEO && sh.limiter == 2) ? limb_factor(rhi, rnuk) : -1.0);
+                    H = e.H;
+                    du = e.dHu;
+                    dv = e.dHv;
+                } else if (sh.outer_bc == 1) {
+                    H = p;                              // free streaming, eq. a22 limit
+                    du = 1.0;
+                } else if (GEO && sh.outer_bc == 2) {   // ghost zone of eq. a62af
+                    const double rlo = s_re[zl], rhi = s_re[zl + 1];
+                    const Ghost gh = outer_ghost(rlo, rhi, rnuk);
+                    const EdgeFlux e = edge_flux(p, gh.ratio * p, lam, gh.D, sh.psi_floor, sh.limiter,
+                                                 sh.limiter == 2 ? limb_factor(rhi, rnuk) : -1.0);
+                    H = e.H;
+                    du = e.dHu + gh.ratio * e.dHv;
+                }
             }
+            s_H[zl][k] = H;                             // the edge below zone 0 has zero flux
+            s_du[zl][k] = du;
+            s_dv[zl][k] = dv;
         }
+        __syncthreads();
+        const In now = cur;
+        cur = nxt;
+        if (!in_zone || !out_row) continue;
+
+        const size_t cb = sys_cell0 + (size_t)i * N + k;
+        const double pn = now.pn;
+        double G = p - pn;
+        double scale = fabs(p) + fabs(pn);
+        const double rlo = s_re[zl], rhi = s_re[zl + 1];
+        double V = shell_volume(rlo, rhi);
+        double A_lo = rlo * rlo, A_hi = rhi * rhi;
+        if (LAPSE && f.lapse) {                             // eq. a58 times a_i c dt: V / a^3 and A / a^2
+            const double a0 = f.lapse[(size_t)ray * I + i];
+            const double e0 = f.lapse_edge[(size_t)ray * (I + 1) + i], e1 = f.lapse_edge[(size_t)ray * (I + 1) + i + 1];
+            V /= a0 * a0 * a0;
+            A_lo /= e0 * e0;
+            A_hi /= e1 * e1;
+        }
+        double Hh = 0.0;
+        double jd = 1.0;                                    // |dG_ik/dpsi_ik| bound, for the rounding level
+        if (diff) {
+            const double Hlo = s_H[zl - 1][k], dlo = s_dv[zl - 1][k];
+            Hh = s_H[zl][k];
+            const double dhi = s_du[zl][k];
+            const double iV = drcp(V);
+            G += c * (A_hi * Hh - A_lo * Hlo) * iV;
+            scale += c * (fabs(A_hi * Hh) + fabs(A_lo * Hlo)) * iV;
+            jd += c * (A_hi * fabs(dhi) + A_lo * fabs(dlo)) * iV;
+        }
+        const double ka = now.ka, et = now.et;
+        if (emabs) {
+            G += c * (ka * p - et * (1.0 - p));
+            scale += c * (fabs(ka * p) + fabs(et * (1.0 - p)));
+            jd += c * (ka + et);
+        }
+        double S = 0.0;
+        if (nes) {
+            const double amp = s_amp[zl];
+            // k' > k: the out kernel carries exp(-(eps_k' - eps_k)/T) = prod_{j=k}^{k'-1} d_j.  The weighted sum
+            // of those products is taken in Horner form from the last group down, one multiply-add and one
+            // multiply per term: h <- (h + P_kk' (1 - psi_k')) d_{k'-1}.
+            double hup = 0.0, sin_ = 0.0;
+#pragma unroll
+            for (int kp = NT - 1; kp >= 1; --kp) {
+                if (kp > k) {                         // padding groups add exact zeros (P = 0 there)
+                    const double Pk = s_P[k * PS + kp];
+                    const double2 pq = s_pq[zl][kp];
+                    hup = fma(Pk, pq.y, hup) * s_d[zl][kp - 1];
+                    sin_ = fma(Pk, pq.x, sin_);
+                }
+            }
+            // k' < k: the in kernel carries exp(-(eps_k - eps_k')/T) = prod_{j=k'}^{k-1} d_j, in Horner form from
+            // group 0 up: h <- (h + P_kk' psi_k') d_k'
+            double hdn = 0.0, sout = hup;
+#pragma unroll
+            for (int kp = 0; kp < NT - 1; ++kp) {
+                if (kp < k) {
+                    const double Pk = s_P[k * PS + kp];
+                    const double2 pq = s_pq[zl][kp];
+                    hdn = fma(Pk, pq.x, hdn) * s_d[zl][kp];
+                    sout = fma(Pk, pq.y, sout);
+                }
+            }
+            sin_ += hdn;
+            S = amp * ((1.0 - p) * sin_ - p * sout);
+            G -= c * S;
+            scale += c * amp * (fabs(1.0 - p) * fabs(sin_) + fabs(p) * fabs(sout));
+            jd += c * amp * (fabs(sin_) + fabs(sout));
+        }
+        scale += fabs(p) * jd;                              // G changes by jd * ulp(psi) per ulp of psi
+        bad |= !isfinite(G);
+        gmax = fmax(gmax, fabs(G));
+        gscale = fmax(gscale, scale);
+        if (G_out) G_out[cb] = g_sign * G;
         if (out.stats) {
-            const double rout = re[I] * re[I] * lapse_edge_inv2(f, (size_t)ray * (I + 1) + I);
-            const double b = c * rout * s_b;
-            if (out.n_tot) out.n_tot[sys] = s_n;
-            if (out.e_tot) out.e_tot[sys] = s_e;
-            if (out.budget) out.budget[sys] = s_n - s_nold + b - s_q - s_nes;
-            if (out.lum) out.lum[sys] = kCLight * rout * s_b;
+            const double vw = V * Wk;
+            sums.n = fma(vw, p, sums.n);
+            sums.nold = fma(vw, pn, sums.nold);
+            sums.e = fma(vw * epsk, p, sums.e);
+            if (emabs) sums.q = fma(c * vw, et * (1.0 - p) - ka * p, sums.q);
+            if (nes) sums.nes = fma(c * vw, S, sums.nes);
+            if (i == I - 1 && diff) sums.b = fma(Wk, Hh, sums.b);
         }
     }
+
+    residual_end(sh, f, out, sys, gmax, gscale, bad, sums, red);
 }
 
 // ---------------------------------------------------------------- debug Jacobian blocks
@@ -925,7 +1166,19 @@ hipError_t launch_residual(const Shape& sh, const Fields& f, const Consts* cs, c
                            const double* psi, double* G_out, double g_sign, const ResidualOut& out,
                            hipStream_t st) {
     const long long nsys = (long long)sh.S * sh.R;
-    if (sh.limiter == 2 || sh.outer_bc == 2) {
+    const bool geo = sh.limiter == 2 || sh.outer_bc == 2;
+    // Up to four groups: threads by cells, except that the geometric options (more registers and arithmetic a cell)
+    // gain by the chunks once the chip is full: 768 systems of 100 zones x 4 groups 25 against 28 us, 1024: 30 against
+    // 28.5, 32768: 0.37 against 0.34 ms.
+    if (sh.N <= 4 && !(geo && nsys > 768)) {
+        const dim3 grid((unsigned)nsys), block(kBlock);
+        if (geo) hipLaunchKernelGGL((k_residual_rows<true, true>), grid, block, 0, st, sh, f, cs, psi_n, psi, G_out, g_sign, out);
+        else if (f.lapse)
+            hipLaunchKernelGGL((k_residual_rows<true, false>), grid, block, 0, st, sh, f, cs, psi_n, psi, G_out, g_sign, out);
+        else hipLaunchKernelGGL((k_residual_rows<false, false>), grid, block, 0, st, sh, f, cs, psi_n, psi, G_out, g_sign, out);
+        return hipGetLastError();
+    }
+    if (geo) {
         TM_DISPATCH_NT(padded_groups(sh.N),
                        hipLaunchKernelGGL((k_residual<NT / 4, true>), dim3((unsigned)nsys), dim3(kBlock), 0, st, sh, f,
                                           cs, psi_n, psi, G_out, g_sign, out));
