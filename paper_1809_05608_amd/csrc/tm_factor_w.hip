@@ -596,10 +596,7 @@ void k_ye_factor_wave(YeFactorArgs A) {
     __syncthreads();
     // a ray whose growth guard tripped is left untouched and marked for the partial-pivoting re-run
     const bool bad = s_bad[0] || s_bad[1];
-    if (threadIdx.x == 0) {
-        if (A.redo) A.redo[ray] = bad ? 1 : 0;
-        if (bad && A.flags) A.flags[ray] |= 8;
-    }
+    if (A.redo && threadIdx.x == 0) A.redo[ray] = bad ? 1 : 0;
     if (bad || second) return;
 
     // ---- back substitution outwards from the meeting zone

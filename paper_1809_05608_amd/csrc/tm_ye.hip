@@ -660,7 +660,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WEU))) v
     }
     const bool any_zp = __ballot(zp) != 0ull;
     if (lane == 0) {
-        if (any_zp && A.flags) A.flags[ray] |= 4;
+        const int fl = (any_zp ? 4 : 0) | (A.redo ? 8 : 0);    // a marked ray, taken over from the diagonal pivots
+        if (fl && A.flags) A.flags[ray] |= fl;
         A.iters[ray] += 1;
         A.pending[ray] = 1;                    // trial psi + delta awaits the line search
         A.alpha[ray] = 1.0;
