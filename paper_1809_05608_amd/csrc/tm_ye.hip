@@ -23,7 +23,8 @@
 //                     (k_ye_factor_wave, tm_factor_w.hip) leaves untouched because its growth guard tripped.
 //   k_ye_backtrack    line-search move-back of rejected trials.
 //   k_ye_temperature  sixteen zones to a wavefront: energy-weighted collision sources of every species, the
-//                     matter energy change and the new temperature.
+//                     matter energy change and the new temperature (k_ye_temperature_zone: one thread per zone, for
+//                     very many zones of up to five groups).
 #include "tm_kernels.hpp"
 #include "tm_nes.hpp"
 
@@ -708,8 +709,10 @@ struct SpeciesWeights {
 // T_i^{n+1} = T_i^n + (de_i - (Y_e^{n+1} - Y_e^n) de/dY_e) / (de/dT)      (eq. a62d)
 // S_qk is the collision source of species q at psi^{n+1}: emission/absorption (for species 0 and 1 with
 // the opacities at Y_e^{n+1}) and NES; isoenergetic scattering exchanges no energy.
+// Up to three tiles held to three wavefronts a SIMD: with pairs, two tiles took 170 registers, two more than allow it
+// (8192 rays of 100 zones x 8 groups 0.46 -> 0.39 ms).
 template <int T, bool PAIR>
-__global__ __launch_bounds__(kBlock) void k_ye_temperature(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(T <= 3 ? 3 : 1))) void k_ye_temperature(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs,
                                                            const double* __restrict__ psi, const double* __restrict__ ye,
                                                            SpeciesWeights wts, const double* __restrict__ de_dT,
                                                            const double* __restrict__ de_dye, double* __restrict__ de_out,
@@ -785,6 +788,114 @@ __global__ __launch_bounds__(kBlock) void k_ye_temperature(Shape sh, Fields f, Y
     }
 }
 
+// The same for up to five groups and many zones: one thread per zone, its groups in registers.  A zone of few groups
+// leaves most lanes of the sixteen-zone layout to padding (three of four at one group, three of eight at five), so
+// with the chip full that layout is bound by the extra wavefronts.  The rows are asked for whole before they are used:
+// piece by piece within the loop over groups, five groups took 0.19 ms instead of 0.09.  100 zones, against the layout
+// above: 8192 rays of one group 0.040 against 0.073 ms, with pairs 0.046 against 0.145; of five 0.091 against 0.149,
+// with pairs 0.137 against 0.325.
+template <int N, bool PAIR>
+__global__ __launch_bounds__(kBlock) void k_ye_temperature_zone(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs,
+                                                                const double* __restrict__ psi, const double* __restrict__ ye,
+                                                                SpeciesWeights wts, const double* __restrict__ de_dT,
+                                                                const double* __restrict__ de_dye,
+                                                                double* __restrict__ de_out, double* __restrict__ temp_out) {
+    const int R = sh.R, I = sh.I;
+    const long long nz = (long long)R * I, idx = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (idx >= nz) return;
+    const bool emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
+    const double T = f.temp[idx], dy = ye[idx] - y.ye_n[idx];
+    double d[N], eW[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        d[k] = (nes && k + 1 < N) ? exp(-cs->de[k] / T) : 0.0;
+        eW[k] = cs->eps[k] * cs->W[k];
+    }
+    double src = 0.0;
+    for (int s = 0; s < sh.S; ++s) {
+        const size_t cz = ((size_t)s * nz + idx) * N;
+        double p[N], kap[N], eta[N], acc = 0.0;
+        auto row = [&](const double* from, double (&v)[N]) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = from[cz + k];
+        };
+        row(psi, p);
+        if (emabs) {
+            row(f.kappa_a, kap);
+            row(f.eta, eta);
+            if (s < 2) {
+                double dk[N], de[N];
+                row(y.dka, dk);
+                row(y.deta, de);
+#pragma unroll
+                for (int k = 0; k < N; ++k) {
+                    kap[k] += dy * dk[k];
+                    eta[k] += dy * de[k];
+                }
+            }
+        }
+        const double amp = nes ? f.nes_amp[(size_t)s * nz + idx] : 0.0;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            double sk = emabs ? eta[k] * (1.0 - p[k]) - kap[k] * p[k] : 0.0;
+            if (nes) {
+                double sin_ = 0.0, sout = 0.0, e = 1.0;
+#pragma unroll
+                for (int kp = k + 1; kp < N; ++kp) {           // k' > k: out factor exp(-(eps_k' - eps_k)/T)
+                    e *= d[kp - 1];
+                    sout = fma(cs->P[k][kp] * e, 1.0 - p[kp], sout);
+                    sin_ = fma(cs->P[k][kp], p[kp], sin_);
+                }
+                e = 1.0;
+#pragma unroll
+                for (int kp = k - 1; kp >= 0; --kp) {          // k' < k: in factor exp(-(eps_k - eps_k')/T)
+                    e *= d[kp];
+                    sin_ = fma(cs->P[k][kp] * e, p[kp], sin_);
+                    sout = fma(cs->P[k][kp], 1.0 - p[kp], sout);
+                }
+                sk += amp * ((1.0 - p[k]) * sin_ - p[k] * sout);
+            }
+            acc = fma(eW[k], sk, acc);
+        }
+        src = fma(wts.w[s], sh.c_dt * acc, src);
+    }
+    if constexpr (PAIR) {                                      // pair sources of species 0 and 1 (eqs. d11-d14)
+        const double* re = f.r_edge + (idx / I) * (I + 1) + idx % I;
+        const double Rz = 0.5 * (re[0] + re[1]), a = y.pair_amp[idx], iw = 1.0 / cs->wbar;
+        double bz[N], mu[2][N], eta[2][N], p[2][N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            bz[k] = exp(-cs->eps[k] / T);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const size_t c = ((size_t)q * nz + idx) * N + k;
+                mu[q][k] = pair_limb_cosine(f.r_nu[q * N + k] / Rz);
+                eta[q][k] = y.pair_eta1[c];
+                p[q][k] = psi[c];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            double acc = 0.0;
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                double cre = 0.0, ann = 0.0;
+#pragma unroll
+                for (int kp = 0; kp < N; ++kp) {
+                    const double qa = a * y.pair_g[k * N + kp] * cs->W[kp] * iw, pb = p[1 - q][kp];
+                    cre = fma(qa * bz[k] * bz[kp], 1.0 - pb, cre);
+                    ann = fma(qa * pair_chi(eta[q][k], eta[1 - q][kp], mu[q][k], mu[1 - q][kp]), pb, ann);
+                }
+                acc = fma(eW[k], (1.0 - p[q][k]) * cre - p[q][k] * ann, acc);
+            }
+            src = fma(wts.w[q], sh.c_dt * acc, src);
+        }
+    }
+    const double de = -kFourPiOverHc3 * kBaryonMassG / y.rho[idx] * src;
+    if (de_out) de_out[idx] = de;
+    temp_out[idx] = T + (de - dy * de_dye[idx]) / de_dT[idx];
+}
+
 // ---------------------------------------------------------------- launchers
 
 #define TM_YE_DISPATCH(NTV, ...)                                        \
@@ -843,6 +954,33 @@ hipError_t launch_ye_temperature(const Shape& sh, const Fields& f, const YeField
     SpeciesWeights w{};
     for (int s = 0; s < sh.S; ++s) w.w[s] = weights[s];
     const long long nz = (long long)sh.R * sh.I;
+    // A thread per zone from where it is the faster, 100 zones a ray: one to three groups from 512 rays (two groups
+    // 0.025 against 0.027 ms, with pairs 0.027 against 0.035; 256 rays alike); four and five with pairs from 1024
+    // (0.035 against 0.048 and 0.039 against 0.061; 512 rays alike), without from 8192 (0.075 against 0.099, 0.091
+    // against 0.149; 4096 rays alike).  From six groups on the rows no longer pay (six groups, 8192 rays: 0.19 ms with
+    // the group count at run time, against 0.16 for sixteen zones to a wavefront).
+    const long long per_zone = sh.N <= 3 ? 51200 : sh.N > 5 ? nz + 1 : y.pair_amp ? 102400 : 819200;
+    if (nz >= per_zone) {
+        const dim3 grid((unsigned)((nz + kBlock - 1) / kBlock)), block(kBlock);
+#define TM_ZONE_CASE(NG)                                                                                                   \
+    case NG:                                                                                                               \
+        if (y.pair_amp)                                                                                                    \
+            hipLaunchKernelGGL((k_ye_temperature_zone<NG, true>), grid, block, 0, st, sh, f, y, cs, psi, ye, w, de_dT, de_dye,  \
+                               de_out, temp_out);                                                                          \
+        else                                                                                                               \
+            hipLaunchKernelGGL((k_ye_temperature_zone<NG, false>), grid, block, 0, st, sh, f, y, cs, psi, ye, w, de_dT, de_dye, \
+                               de_out, temp_out);                                                                          \
+        break;
+        switch (sh.N) {
+            TM_ZONE_CASE(1)
+            TM_ZONE_CASE(2)
+            TM_ZONE_CASE(3)
+            TM_ZONE_CASE(4)
+            TM_ZONE_CASE(5)
+        }
+#undef TM_ZONE_CASE
+        return hipGetLastError();
+    }
     const unsigned blocks = (unsigned)((nz + kBlock / 4 - 1) / (kBlock / 4));      // sixteen zones to a wavefront
     if (y.pair_amp)
         TM_YE_DISPATCH(padded_groups(sh.N),
