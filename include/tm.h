@@ -180,7 +180,9 @@ tm_status tm_destroy(tm_ctx *ctx);
 /* Device bytes of workspace needed to factor `batch_systems` systems per launch
  * (0 means all S*R systems at once): (b + 15) slots of I*NT*(NT+1) values (NT = N
  * padded to a multiple of 4; float32 in TM_PREC_MIXED, else double), the 15 spare
- * slots filling a last partial wave group.  Returns 0 for an invalid problem.    */
+ * slots filling a last partial wave group; with TM_PREC_MIXED and S*R <= 4096, whose Newton
+ * updates are solved in FP64 (see tm_newton_step), b + 1 slots of doubles if that is more.
+ * Returns 0 for an invalid problem.    */
 size_t tm_workspace_bytes(const tm_problem *problem, int64_t batch_systems);
 
 /* Hand the context caller-owned device workspace (>= tm_workspace_bytes(p, b) or
@@ -241,9 +243,14 @@ tm_status tm_factor_solve_noalloc(tm_ctx *ctx, const tm_inputs *in, const double
  * largest sum over a cell of the magnitudes of the terms of G (the level below which
  * G itself is rounding).  rtol = 0 runs exactly max_iter updates (unless G is exactly
  * zero).  In TM_PREC_MIXED each update is an FP32 solve of the FP64 residual, so the
- * iteration is iterative refinement to the same stopping rule; with 4096 systems or fewer
- * still iterating the update is solved in FP64, which is then the faster (never with
- * TM_FACTOR_KERNEL set at tm_create).  `stats` (all pointers
+ * iteration is iterative refinement to the same stopping rule.  With 4096 systems or fewer
+ * still iterating the update is solved in FP64, which is then the faster; it stays in FP32
+ * with TM_PIVOT=always or TM_FACTOR_KERNEL set at tm_create, with more than 768 but not all
+ * systems iterating in a problem of 2^29 cells or more, and with more than 768 systems of up to 4
+ * or more than 20 groups where the workspace holds the doubles of fewer.  The kernel, and in
+ * TM_PREC_MIXED the precision of an update, thus follow the number of systems in the problem
+ * and of those still iterating: the same ray solved in a larger or smaller problem (a shard of the
+ * rays, say) agrees within the stopping rule, not bit for bit.  `stats` (all pointers
  * device, may be NULL as a whole) receives the per-system results at the returned
  * psi.  Returns TM_OK, or the worst of TM_ERR_NONFINITE, TM_ERR_SINGULAR,
  * TM_ERR_NOT_CONVERGED over systems (per-system detail in stats.flags).           */

@@ -220,6 +220,13 @@ tm_status ensure_gbuf(tm_ctx* c) {
     return TM_OK;
 }
 
+// Bytes in which so many systems of a mixed problem take an FP64 Newton update in one launch (whole pairs of slots of
+// twice the float32 size); 0 where the whole problem's updates stay in float32.
+size_t fp64_update_bytes(const tm_problem& p, long long systems) {
+    if (!tmk::factor_in_fp64(shape_of(p), n_systems(p), n_systems(p))) return 0;
+    return (size_t)(systems + 1) * tmk::factor_ws_bytes_per_system(p.n_zones, p.n_groups, false);
+}
+
 // Systems per factor launch that fit the workspace; allocates all-systems workspace if none.
 tm_status factor_batch(tm_ctx* c, bool fp32, long long* batch) {
     const size_t per = tmk::factor_ws_bytes_per_system(c->p.n_zones, c->p.n_groups, fp32);
@@ -236,8 +243,7 @@ tm_status factor_batch(tm_ctx* c, bool fp32, long long* batch) {
         long long b = ns;
         while (b > 1 && (double)(b + tmk::kWsPadSystems) * per > 0.7 * (double)freeb) b = (b + 1) / 2;
         size_t bytes = (size_t)(b + tmk::kWsPadSystems) * per;
-        if (fp32 && tmk::factor_in_fp64(shape_of(c->p), ns))        // Newton updates in FP64 take twice the bytes
-            bytes = std::max(bytes, std::min((size_t)(ns + 1) * 2 * per, (size_t)(0.7 * (double)freeb)));
+        if (fp32) bytes = std::max(bytes, std::min(fp64_update_bytes(c->p, ns), (size_t)(0.7 * (double)freeb)));
         hipError_t e = hipMalloc(&c->ws, bytes);
         if (e != hipSuccess) {
             c->ws = nullptr;
@@ -367,8 +373,9 @@ tm_status run_factor(tm_ctx* c, const tm_inputs* in, const double* psi, const do
     {
         // diagonal pivots in FP64, also for the float32 Newton updates of few systems; systems at rest then
         // take neither slots nor wavefronts
+        const long long slots = tmk::factor_fp64_slots(a.sh, c->ws_bytes);
         const bool few = fp32 && psi_out && !pivot_first && !c->factor_forced &&
-                         tmk::factor_in_fp64(a.sh, listed >= 0 ? listed : ns);
+                         tmk::factor_in_fp64(a.sh, listed >= 0 ? listed : ns, slots);
         const bool as32 = fp32 && !few;
         tmk::FactorArgs d = a;
         d.total = ns;
@@ -376,7 +383,7 @@ tm_status run_factor(tm_ctx* c, const tm_inputs* in, const double* psi, const do
             d.list = c->list;
             d.total = listed;
         }
-        const long long step = few ? std::min(d.total, tmk::factor_fp64_slots(a.sh, c->ws_bytes)) : batch;
+        const long long step = few ? std::min(d.total, slots) : batch;
         if (step < 1) return set_err(c, TM_ERR_WORKSPACE, "workspace smaller than one system's factors");
         for (long long s0 = 0; s0 < d.total; s0 += step) {
             d.sys0 = s0;
@@ -531,8 +538,9 @@ size_t tm_workspace_bytes(const tm_problem* p, int64_t batch_systems) {
     if (!valid_problem(p, nullptr) || batch_systems < 0) return 0;
     const long long ns = n_systems(*p);
     const long long b = batch_systems == 0 ? ns : std::min<long long>(batch_systems, ns);
-    return (size_t)(b + tmk::kWsPadSystems) *
-           tmk::factor_ws_bytes_per_system(p->n_zones, p->n_groups, p->precision == TM_PREC_MIXED);
+    const bool fp32 = p->precision == TM_PREC_MIXED;
+    const size_t bytes = (size_t)(b + tmk::kWsPadSystems) * tmk::factor_ws_bytes_per_system(p->n_zones, p->n_groups, fp32);
+    return fp32 ? std::max(bytes, fp64_update_bytes(*p, b)) : bytes;
 }
 
 tm_status tm_create(const tm_problem* p, void* stream, tm_ctx** out) {

@@ -40,8 +40,15 @@ bool factor_takes_list(const Shape& sh, long long systems) {
     return systems <= kWaveSystems || near_cells(sh);       // the tile kernel reaches a pair's cells with 32-bit offsets
 }
 
-bool factor_in_fp64(const Shape& sh, long long systems) {
-    return systems <= kFp64Systems && (systems == (long long)sh.S * sh.R || factor_takes_list(sh, systems));
+// A workspace of float32 size holds half as many FP64 systems.  Two launches that each wait for the chain then cost
+// more than the one of float32, except where that is slowest (one wavefront's quads, 5 to 20 groups) and where the
+// wavefront per half ray is the quickest: a step of 4 updates, 300 zones, float32 against two launches of FP64: 4096
+// systems x 24 groups 18.4 against 21.0 ms, 32: 28.4 against 33.9, 2048 x 32: 20.3 against 21.3; 4096 x 20: 14.9
+// against 11.5, 4096 x 8: 4.4 against 4.1; 100 zones, 768 systems of 4 groups 0.85 against 0.74, 4096: 1.03
+// against 1.16.
+bool factor_in_fp64(const Shape& sh, long long systems, long long slots) {
+    return systems <= kFp64Systems && (systems == (long long)sh.S * sh.R || factor_takes_list(sh, systems)) &&
+           (systems <= slots || systems <= kWaveSystems || (sh.N > 4 && sh.N <= 20));
 }
 
 long long factor_fp64_slots(const Shape& sh, size_t bytes) {

@@ -93,8 +93,9 @@ enum FactorKernel : int {
     kFactorQuadBf16x3 = 4,
     kFactorQuadBf16 = 5
 };
-// Whether a Newton update of this many systems, for which float32 would do, is the faster in FP64
-bool factor_in_fp64(const Shape& sh, long long systems);
+// Whether a Newton update of this many systems, for which float32 would do, is the faster in FP64, with FP64 slots for
+// so many a launch
+bool factor_in_fp64(const Shape& sh, long long systems, long long slots);
 // Whether the FP64 diagonal-pivot launch of this many systems takes them through a list
 bool factor_takes_list(const Shape& sh, long long systems);
 // FP64 slots of one system per launch that a workspace of so many bytes holds
