@@ -231,7 +231,8 @@ size_t fp64_update_bytes(const tm_problem& p, long long systems) {
 tm_status factor_batch(tm_ctx* c, bool fp32, long long* batch) {
     const size_t per = tmk::factor_ws_bytes_per_system(c->p.n_zones, c->p.n_groups, fp32);
     const long long ns = n_systems(c->p);
-    if (c->ws && c->ws_owned && c->ws_kind != 0) {     // sized for the coupled step: size it again
+    // sized for the coupled step, or for a few systems in float32 where this solve is in FP64: size it again
+    if (c->ws && c->ws_owned && (c->ws_kind != 0 || c->ws_bytes / per <= (size_t)tmk::kWsPadSystems)) {
         TM_TRY(hip_check(c, hipStreamSynchronize(c->stream), "stream sync"));
         (void)hipFree(c->ws);
         c->ws = nullptr;
