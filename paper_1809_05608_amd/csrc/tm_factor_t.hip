@@ -409,7 +409,7 @@ void k_factor_tile(FactorArgs A) {
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- Ahat^-1, y = Ahat^-1 g, C = Ahat^-1 diag(b)
-        tile_invert<T>(S, L, sm.piv, guard);
+        tile_invert<T, TRANS>(S, L, sm.piv, guard);
         double yn[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {

@@ -119,7 +119,7 @@ struct WaveBlock {
 // inverse there); every lane reads the pivot tile and its A operands back.  The column register of the coming
 // pivot is updated and published first; the rest of a pivot's update runs on the matrix cores under the
 // inversion of the next pivot's tile.
-template <int G, int CN, int PR>
+template <int G, int CN, int PR, bool COLS = false>
 __device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane& L, int jc, double* pan, TileGuard& guard) {
     constexpr int RF = G / 4, RM = G % 4;
     struct Panel {                                                     // A operands of a pivot's panel
@@ -142,6 +142,16 @@ __device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane&
         for (int x = 0; x < RM; ++x)
             if (4 * RF + x != p) S.r[x][C] = mfma4_neg(l.r[x], u, S.r[x][C]);
         S.set(p, C, u);
+    };
+    auto watch = [&](int p) {                                          // minus the multipliers of panel p's columns
+        if constexpr (COLS && G > 1) {
+            double m = 0.0;                                             // a NaN among them reaches a later pivot
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+                if (q != p) m = fmax(m, fabs(S.get(q, p >> 2)));
+            guard.see(m, 0x000F000F000F000Full << (4 * (p & 3)));
+            guard.pin();
+        }
     };
     auto next_register = [&](int p) { return (p + 1 < G ? p + 1 : p) >> 2; };
     publish(0);
@@ -173,21 +183,22 @@ __device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane&
                     rest += RF + RM;
                 }
         }
-        const double xa = tile_inverse(e, L, guard);                   // transpose of the inverse: its A operand
+        const double xa = tile_inverse<COLS>(e, L, guard);             // transpose of the inverse: its A operand
 #pragma unroll
         for (int j = 0; j < rest; ++j) {                                // one product, then a few vector operations
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (p > 0) watch(p - 1);                                        // its products have come by now
         const double xn = mfma4(xa, L.id, 0.0);
         double u[CN];
 #pragma unroll
         for (int C = 0; C < CN; ++C) {
             u[C] = mfma4(xa, S.get(p, C), 0.0);                         // zero in the panel's own columns
-            guard.see(u[C]);
+            if (!COLS) guard.see(u[C]);
         }
-        guard.pin();
+        if (!COLS) guard.pin();
         u[C0] = L.g == (p & 3) ? xn : u[C0];
         if (C0 < RF) l.f[C0 < RF ? C0 : 0] = L.g == (p & 3) ? 0.0 : l.f[C0 < RF ? C0 : 0];   // the pivot rows stay
         update(next_register(p), l, u[next_register(p)], p);
@@ -199,6 +210,7 @@ __device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane&
 #pragma unroll
     for (int C = 0; C < CN; ++C)
         if (C != next_register(G - 1)) update(C, l_prev, u_prev[C], G - 1);
+    watch(G - 1);
 }
 
 // EXT: lapse, geometric limiter and boundary, and the pair processes compiled in.  AHEAD: a second wavefront per half
@@ -1016,7 +1028,7 @@ void k_factor_wave(FactorArgs A) {
             }
             __builtin_amdgcn_sched_barrier(0);
             // ---- Ahat^-1, y = Ahat^-1 g, C = Ahat^-1 diag(b)
-            wave_invert<T, CN, X::PR>(S, L, jc, sm.pan, guard);
+            wave_invert<T, CN, X::PR, TRANS>(S, L, jc, sm.pan, guard);
             double yc[CN];
 #pragma unroll
             for (int C = 0; C < CN; ++C) yc[C] = 0.0;

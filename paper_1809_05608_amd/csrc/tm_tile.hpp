@@ -104,6 +104,7 @@ struct TileGuard {
     unsigned long long bad = 0;        // one bit per lane
     __device__ __forceinline__ explicit TileGuard(double l) : limit(l) {}
     __device__ __forceinline__ void see(double x) { bad |= __ballot(!(fabs(x) <= limit)); }
+    __device__ __forceinline__ void see(double x, unsigned long long lanes) { bad |= __ballot(!(fabs(x) <= limit)) & lanes; }
     // keeps the record current: deferred by the compiler, it would hold every step's multipliers
     __device__ __forceinline__ void pin() { asm volatile("" : "+s"(bad)); }
 };
@@ -121,30 +122,53 @@ struct TileEntries {
 // Inverse of a tile in natural order from its entries: every lane solves for its own column with 2 x 2 block
 // pivots (two reciprocals in sequence instead of four) and keeps its row.  The pivots are diagonal: no
 // exchange between the two halves of the tile.
+//
+// What the guard watches are the multipliers of the Jacobian's columns, whose dominance bounds them.  The block is
+// stored as the transposed Jacobian's (COLS false: the multipliers are those of the stored rows), for the transposed
+// solve as the Jacobian's own (COLS true: those of the stored columns).  The multipliers of the Jacobian's rows grow with
+// the scattering at no cost in accuracy: watched in the transposed solve, at 100 times the synthetic amplitude they sent
+// every system to partial pivoting (4096 systems of 300 zones x 20 groups 9.5 ms, 2.4 so).
+template <bool COLS>
 __device__ __forceinline__ double tile_inverse(const TileEntries& e, const TileLane& L, TileGuard& G) {
     const double2 r0 = e.v[0], r0b = e.v[1], r1 = e.v[2], r1b = e.v[3], r2 = e.v[4], r2b = e.v[5], r3 = e.v[6],
                   r3b = e.v[7];
     const double d1 = fma(r0.x, r1.y, -(r0.y * r1.x));
     const double i1 = rcp_cubic(d1);
     const double e00 = r1.y * i1, e01 = -(r0.y * i1), e10 = -(r1.x * i1), e11 = r0.x * i1;
-    const double g00 = fma(r2.x, e00, r2.y * e10), g01 = fma(r2.x, e01, r2.y * e11);
-    const double g10 = fma(r3.x, e00, r3.y * e10), g11 = fma(r3.x, e01, r3.y * e11);
-    const double s00 = fma(-g00, r0b.x, fma(-g01, r1b.x, r2b.x)), s01 = fma(-g00, r0b.y, fma(-g01, r1b.y, r2b.y));
-    const double s10 = fma(-g10, r0b.x, fma(-g11, r1b.x, r3b.x)), s11 = fma(-g10, r0b.y, fma(-g11, r1b.y, r3b.y));
+    // the multipliers of one half by the other's inverse (those between tiles are seen by the caller); a first
+    // determinant that is zero or not finite makes them NaN, a second one makes its reciprocal NaN
+    double h00, h01, h10, h11, s00, s01, s10, s11;
+    if constexpr (COLS) {                                              // upper half's inverse times the right half
+        h00 = fma(e00, r0b.x, e01 * r1b.x), h01 = fma(e00, r0b.y, e01 * r1b.y);
+        h10 = fma(e10, r0b.x, e11 * r1b.x), h11 = fma(e10, r0b.y, e11 * r1b.y);
+        s00 = fma(-r2.x, h00, fma(-r2.y, h10, r2b.x)), s01 = fma(-r2.x, h01, fma(-r2.y, h11, r2b.y));
+        s10 = fma(-r3.x, h00, fma(-r3.y, h10, r3b.x)), s11 = fma(-r3.x, h01, fma(-r3.y, h11, r3b.y));
+    } else {                                                           // lower half times the upper's inverse
+        h00 = fma(r2.x, e00, r2.y * e10), h01 = fma(r2.x, e01, r2.y * e11);
+        h10 = fma(r3.x, e00, r3.y * e10), h11 = fma(r3.x, e01, r3.y * e11);
+        s00 = fma(-h00, r0b.x, fma(-h01, r1b.x, r2b.x)), s01 = fma(-h00, r0b.y, fma(-h01, r1b.y, r2b.y));
+        s10 = fma(-h10, r0b.x, fma(-h11, r1b.x, r3b.x)), s11 = fma(-h10, r0b.y, fma(-h11, r1b.y, r3b.y));
+    }
     const double d2 = fma(s00, s11, -(s01 * s10));
     const double i2 = rcp_cubic(d2);
-    // multipliers of the lower 2 x 2 half (those between tiles are seen by the caller); a first determinant
-    // that is zero or not finite makes them NaN, a second one makes its reciprocal NaN
-    G.see(g00);
-    G.see(g01);
-    G.see(g10);
-    G.see(g11);
+    G.see(h00);
+    G.see(h01);
+    G.see(h10);
+    G.see(h11);
     G.bad |= __ballot(!(i2 == i2));
     G.pin();
-    const double t0 = fma(-g00, L.u0, fma(-g01, L.u1, L.u2)), t1 = fma(-g10, L.u0, fma(-g11, L.u1, L.u3));
-    const double x2 = fma(s11, t0, -(s01 * t1)) * i2, x3 = fma(s00, t1, -(s10 * t0)) * i2;
-    const double w0 = fma(-r0b.x, x2, fma(-r0b.y, x3, L.u0)), w1 = fma(-r1b.x, x2, fma(-r1b.y, x3, L.u1));
-    const double x0 = fma(e00, w0, e01 * w1), x1 = fma(e10, w0, e11 * w1);
+    double x0, x1, x2, x3;
+    if constexpr (COLS) {
+        const double y0 = fma(e00, L.u0, e01 * L.u1), y1 = fma(e10, L.u0, e11 * L.u1);
+        const double t0 = fma(-r2.x, y0, fma(-r2.y, y1, L.u2)), t1 = fma(-r3.x, y0, fma(-r3.y, y1, L.u3));
+        x2 = fma(s11, t0, -(s01 * t1)) * i2, x3 = fma(s00, t1, -(s10 * t0)) * i2;
+        x0 = fma(-h00, x2, fma(-h01, x3, y0)), x1 = fma(-h10, x2, fma(-h11, x3, y1));
+    } else {
+        const double t0 = fma(-h00, L.u0, fma(-h01, L.u1, L.u2)), t1 = fma(-h10, L.u0, fma(-h11, L.u1, L.u3));
+        x2 = fma(s11, t0, -(s01 * t1)) * i2, x3 = fma(s00, t1, -(s10 * t0)) * i2;
+        const double w0 = fma(-r0b.x, x2, fma(-r0b.y, x3, L.u0)), w1 = fma(-r1b.x, x2, fma(-r1b.y, x3, L.u1));
+        x0 = fma(e00, w0, e01 * w1), x1 = fma(e10, w0, e11 * w1);
+    }
     const double lo = (L.a & 1) ? x1 : x0, hi = (L.a & 1) ? x3 : x2;
     return (L.a & 2) ? hi : lo;
 }
@@ -154,7 +178,7 @@ __device__ __forceinline__ double tile_inverse(const TileEntries& e, const TileL
 // terms except on the diagonal, so entries far below the block's norm keep their relative accuracy.  The coming
 // pivot's tile is updated first and gathered through LDS (transposed, so that its inverse comes out as an A
 // operand); the rest of a pivot's update runs on the matrix cores under the inversion of the next one.
-template <int T>
+template <int T, bool COLS>
 __device__ __forceinline__ void tile_invert(double (&S)[T][T], const TileLane& L, double* piv, TileGuard& G) {
     double* q = piv + L.g * kPivStride;
     double ct[T], xn = 0.0;
@@ -171,6 +195,16 @@ __device__ __forceinline__ void tile_invert(double (&S)[T][T], const TileLane& L
         }
         S[p][p] = xn;
     };
+    auto watch = [&](int p) {                                          // minus the multipliers of pivot p's columns
+        if constexpr (COLS && T > 1) {
+            double m = 0.0;                                             // a NaN among them reaches a later pivot
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+                if (i != p) m = fmax(m, fabs(S[i][p]));
+            G.see(m);
+            G.pin();
+        }
+    };
     q[4 * L.b + L.a] = S[0][0];
     wave_sync();
 #pragma unroll
@@ -180,7 +214,7 @@ __device__ __forceinline__ void tile_invert(double (&S)[T][T], const TileLane& L
         wave_sync();
         __builtin_amdgcn_sched_barrier(0);
         if (p > 0) rest(p - 1);
-        const double xa = tile_inverse(e, L, G);
+        const double xa = tile_inverse<COLS>(e, L, G);
         if (p > 0) {
 #pragma unroll
             for (int j = 0; j < T * (T - 1) - 1; ++j) {                 // one product, then a few vector operations
@@ -189,6 +223,7 @@ __device__ __forceinline__ void tile_invert(double (&S)[T][T], const TileLane& L
             }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (p > 0) watch(p - 1);                                        // its products have come by now
         xn = mfma4(xa, L.id, 0.0);
 #pragma unroll
         for (int ii = 1; ii < T; ++ii) ct[(p + ii) % T] = mfma4(S[(p + ii) % T][p], L.id, 0.0);   // A operands of the column
@@ -196,9 +231,9 @@ __device__ __forceinline__ void tile_invert(double (&S)[T][T], const TileLane& L
         for (int jj = 1; jj < T; ++jj) {
             const int j = (p + jj) % T;
             S[p][j] = mfma4(xa, S[p][j], 0.0);
-            G.see(S[p][j]);
+            if (!COLS) G.see(S[p][j]);
         }
-        G.pin();
+        if (!COLS) G.pin();
         if (p + 1 < T) {
             S[p + 1][p + 1] = mfma4_neg(ct[p + 1], S[p][p + 1], S[p + 1][p + 1]);
             q[4 * L.b + L.a] = S[p + 1][p + 1];
@@ -206,6 +241,7 @@ __device__ __forceinline__ void tile_invert(double (&S)[T][T], const TileLane& L
         }
     }
     rest(T - 1);
+    watch(T - 1);
 }
 
 // Owner form of a row-form vector (element 4b + a, and 16 + 4b + a).
