@@ -614,37 +614,39 @@ static void launch_t(const FactorArgs& a, hipStream_t st) {
 }
 
 template <typename T, int NT, bool GEO>
-static void launch_tp(const FactorArgs& a, bool tr, bool pv, hipStream_t st) {
+static hipError_t launch_tp(const FactorArgs& a, bool tr, bool pv, hipStream_t st) {
     if (pv) {
         if (tr) launch_t<T, NT, true, true, GEO>(a, st);
         else launch_t<T, NT, false, true, GEO>(a, st);
-    } else if constexpr (std::is_same<T, float>::value || NT == 4) {    // FP64 with diagonal pivots: k_factor_tile
+        return hipGetLastError();
+    }
+    if constexpr (std::is_same<T, float>::value || NT == 4) {
         if (tr) launch_t<T, NT, true, false, GEO>(a, st);
         else launch_t<T, NT, false, false, GEO>(a, st);
+        return hipGetLastError();
     }
+    return hipErrorInvalidValue;     // FP64 with diagonal pivots above four groups: the tile and wave kernels
 }
 
 template <int NT, bool GEO>
-static void launch_nt(const FactorArgs& a, bool fp32, bool tr, bool pv, hipStream_t st) {
-    if (fp32) launch_tp<float, NT, GEO>(a, tr, pv, st);
-    else launch_tp<double, NT, GEO>(a, tr, pv, st);
+static hipError_t launch_nt(const FactorArgs& a, bool fp32, bool tr, bool pv, hipStream_t st) {
+    return fp32 ? launch_tp<float, NT, GEO>(a, tr, pv, st) : launch_tp<double, NT, GEO>(a, tr, pv, st);
 }
 
 // Launch of the lane kernels for every padded group count, GEO instantiations or not.
 template <bool GEO>
 static hipError_t launch_lane(const FactorArgs& a, bool fp32, bool transpose, bool pivot, hipStream_t st) {
     switch (padded_groups(a.sh.N)) {
-        case 4: launch_nt<4, GEO>(a, fp32, transpose, pivot, st); break;
-        case 8: launch_nt<8, GEO>(a, fp32, transpose, pivot, st); break;
-        case 12: launch_nt<12, GEO>(a, fp32, transpose, pivot, st); break;
-        case 16: launch_nt<16, GEO>(a, fp32, transpose, pivot, st); break;
-        case 20: launch_nt<20, GEO>(a, fp32, transpose, pivot, st); break;
-        case 24: launch_nt<24, GEO>(a, fp32, transpose, pivot, st); break;
-        case 28: launch_nt<28, GEO>(a, fp32, transpose, pivot, st); break;
-        case 32: launch_nt<32, GEO>(a, fp32, transpose, pivot, st); break;
+        case 4: return launch_nt<4, GEO>(a, fp32, transpose, pivot, st);
+        case 8: return launch_nt<8, GEO>(a, fp32, transpose, pivot, st);
+        case 12: return launch_nt<12, GEO>(a, fp32, transpose, pivot, st);
+        case 16: return launch_nt<16, GEO>(a, fp32, transpose, pivot, st);
+        case 20: return launch_nt<20, GEO>(a, fp32, transpose, pivot, st);
+        case 24: return launch_nt<24, GEO>(a, fp32, transpose, pivot, st);
+        case 28: return launch_nt<28, GEO>(a, fp32, transpose, pivot, st);
+        case 32: return launch_nt<32, GEO>(a, fp32, transpose, pivot, st);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace tmk
