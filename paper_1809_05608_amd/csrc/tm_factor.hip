@@ -16,13 +16,14 @@ size_t factor_ws_bytes_per_system(int I, int N, bool fp32) {
 // a system per pair of wavefronts (tm_factor_w.hip) is the faster, above it four half systems per wavefront
 // (tm_factor_t.hip), whose matrix operations have no idle rows.  Measured, 540 zones x 20 groups: 6 systems 0.93
 // against 1.90 ms, 24: 1.00 against 2.00, 512: 1.35 against 2.00, 720: 1.65 against 2.16, 1024: 2.35 against 2.23,
-// 1536: 3.1 against 2.3; 300 zones, 1024 systems: 8 groups 0.44 against 0.47, 12: 0.60 against 0.63, 28: 2.1 against
-// 2.4.  The count is that of all batches: a batch takes the kernel that the whole would take.
+// 1536: 3.1 against 2.3.  The line is that of 20 groups for all: at others the two cross later, so a little above it
+// (300 zones, 1024 systems) the tiles are the slower by 7% at 8 groups (0.44 against 0.47), 5% at 12 (0.60 against
+// 0.63) and 14% at 28 (2.1 against 2.4).  The count is that of all batches: a batch takes the kernel that the whole
+// would take.
 constexpr long long kWaveSystems = 768;
 
 // Up to four groups a block is one tile, and the tile kernel's wavefront carries two systems where lanes by rows
-// carry four: above this many systems, where all SIMDs are busy, the lanes are the
-// faster.  Tiles against lanes, 300 zones x 4 groups: 8192 systems 0.75 against 1.25 ms, 16384: 1.33 against 1.36,
+// carry four: above this many systems, where all SIMDs are busy, the lanes are the faster.  Tiles against lanes, 300 zones x 4 groups: 8192 systems 0.75 against 1.25 ms, 16384: 1.33 against 1.36,
 // 32768: 2.40 against 1.91; one group, 32768 systems: 2.06 against 1.50.
 constexpr long long kLaneSystems = 16384;
 
@@ -61,9 +62,10 @@ hipError_t launch_factor(const FactorArgs& a, bool fp32, bool transpose, bool pi
     if (kernel != kFactorLane && fp32 && !transpose && !pivot &&
         launch_factor_quad(a, st, kernel))
         return hipGetLastError();
-    // FP64 with diagonal pivots: on the matrix cores, both ends of a ray at once, for every group count and
-    // option (one row per lane: 8.2 ms against 2.1 at 720 systems, 122 against 57 at 65536).  The tile kernel
-    // addresses the cells of two systems with 32-bit byte offsets.
+    // FP64 with diagonal pivots: on the matrix cores, both ends of a ray at once, for every option and, but for very
+    // many systems of up to four groups, every group count (one row per lane: 8.2 ms against 2.1 at 720 systems of 540
+    // zones x 20 groups, 122 against 58 at 65536; five groups of 100 zones, 65536 systems: 2.92 against 2.63).  The tile
+    // kernel addresses the cells of two systems with 32-bit byte offsets.
     if (!fp32 && !pivot) {
         const bool few = a.total <= kWaveSystems, far = (long long)a.sh.I * a.sh.N >= (1ll << 27);
         const bool lanes = a.sh.N <= 4 && a.total > kLaneSystems && !a.list;

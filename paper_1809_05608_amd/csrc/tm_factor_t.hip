@@ -14,7 +14,7 @@
 //
 // What bounds it: with few systems, the chain of zones (540 zones: 2.0 ms, of it 1.2 us per step in the
 // back substitution and the rest in assembly and five dependent tile inversions); with the chip full, the
-// round trip of C through HBM (119 GB each way at 65536 systems of 540 x 20; 58.7 ms a launch) together with the issue of
+// round trip of C through HBM (119 GB each way at 65536 systems of 540 x 20; 58 ms a launch) together with the issue of
 // two waves per SIMD.  The one-row-per-lane kernel before it took 7.7 ms and 122 ms (transposed: 9.0 and
 // 130 ms): it exchanged every pivot row through LDS and ran every zone of a ray in sequence.  To fit two
 // waves per SIMD at 20 groups, only one matrix is held in registers (the previous factor becomes the Schur

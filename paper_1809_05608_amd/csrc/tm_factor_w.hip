@@ -19,9 +19,9 @@
 // latency of one wavefront: 11 dependent panels of an LDS round trip, a 4 x 4 inversion (about 75 vector
 // operations) and the products.  With many rays the factors' way through memory (13.4 kB a zone, written once and
 // read once) comes to half the time.  Per update, 540 zones x 20 groups, residual passes included, against one
-// ray per wavefront on 8 x 8 tiles of the vector unit from one end: 90 rays 14.2 -> 4.0 ms, 2048 rays 21.4 -> 16 ms,
-// 8192 rays 74 -> 55 ms.  Lapse, neutrinosphere options and pairs had partial pivoting
-// on the vector unit only; with pairs 90 rays 18 -> 4.1 ms.
+// ray per wavefront on 8 x 8 tiles of the vector unit from one end: 90 rays 14.2 -> 3.8 ms, 2048 rays 21.4 -> 14.2 ms,
+// 8192 rays 74 -> 54 ms.  Lapse, neutrinosphere options and pairs had partial pivoting
+// on the vector unit only; with pairs 90 rays 18 -> 3.8 ms.
 // Of a step's 33000 cycles with few rays 17400 are the inversion (630 of each panel's 1585 on the matrix core, which
 // does not overlap the vector unit's FP64 work), 9300 the assembly, 4200 the back substitution.
 #include "tm_kernels.hpp"

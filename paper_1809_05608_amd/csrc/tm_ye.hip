@@ -712,11 +712,10 @@ struct SpeciesWeights {
 // Up to three tiles held to three wavefronts a SIMD: with pairs, two tiles took 170 registers, two more than allow it
 // (8192 rays of 100 zones x 8 groups 0.46 -> 0.39 ms).
 template <int T, bool PAIR>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(T <= 3 ? 3 : 1))) void k_ye_temperature(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs,
-                                                           const double* __restrict__ psi, const double* __restrict__ ye,
-                                                           SpeciesWeights wts, const double* __restrict__ de_dT,
-                                                           const double* __restrict__ de_dye, double* __restrict__ de_out,
-                                                           double* __restrict__ temp_out) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(T <= 3 ? 3 : 1)))
+void k_ye_temperature(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs, const double* __restrict__ psi,
+                      const double* __restrict__ ye, SpeciesWeights wts, const double* __restrict__ de_dT,
+                      const double* __restrict__ de_dye, double* __restrict__ de_out, double* __restrict__ temp_out) {
     __shared__ NesLds<T> sm;
     __shared__ PairLds<PAIR ? T : 1> sp;
     const int R = sh.R, I = sh.I, N = sh.N;
