@@ -145,11 +145,11 @@ __device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane&
     };
     auto watch = [&](int p) {                                          // minus the multipliers of panel p's columns
         if constexpr (COLS && G > 1) {
-            double m = 0.0;                                             // a NaN among them reaches a later pivot
+            unsigned m = 0;
 #pragma unroll
             for (int q = 0; q < G; ++q)
-                if (q != p) m = fmax(m, fabs(S.get(q, p >> 2)));
-            guard.see(m, 0x000F000F000F000Full << (4 * (p & 3)));
+                if (q != p) m = max(m, abs_key_bits(S.get(q, p >> 2)));
+            guard.see_key(m, 0x000F000F000F000Full << (4 * (p & 3)));
             guard.pin();
         }
     };
@@ -190,7 +190,6 @@ __device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane&
             __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (p > 0) watch(p - 1);                                        // its products have come by now
         const double xn = mfma4(xa, L.id, 0.0);
         double u[CN];
 #pragma unroll
@@ -199,6 +198,7 @@ __device__ __forceinline__ void wave_invert(WaveBlock<G, CN>& S, const TileLane&
             if (!COLS) guard.see(u[C]);
         }
         if (!COLS) guard.pin();
+        else if (p > 0) watch(p - 1);                                   // while these products are on their way
         u[C0] = L.g == (p & 3) ? xn : u[C0];
         if (C0 < RF) l.f[C0 < RF ? C0 : 0] = L.g == (p & 3) ? 0.0 : l.f[C0 < RF ? C0 : 0];   // the pivot rows stay
         update(next_register(p), l, u[next_register(p)], p);

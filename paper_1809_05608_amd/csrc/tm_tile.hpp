@@ -104,7 +104,10 @@ struct TileGuard {
     unsigned long long bad = 0;        // one bit per lane
     __device__ __forceinline__ explicit TileGuard(double l) : limit(l) {}
     __device__ __forceinline__ void see(double x) { bad |= __ballot(!(fabs(x) <= limit)); }
-    __device__ __forceinline__ void see(double x, unsigned long long lanes) { bad |= __ballot(!(fabs(x) <= limit)) & lanes; }
+    // by the upper word of the magnitude (abs_key_bits; a NaN's is above any limit's), in the given lanes
+    __device__ __forceinline__ void see_key(unsigned key, unsigned long long lanes = ~0ull) {
+        bad |= __ballot(key > abs_key_bits(limit)) & lanes;
+    }
     // keeps the record current: deferred by the compiler, it would hold every step's multipliers
     __device__ __forceinline__ void pin() { asm volatile("" : "+s"(bad)); }
 };
@@ -197,11 +200,11 @@ __device__ __forceinline__ void tile_invert(double (&S)[T][T], const TileLane& L
     };
     auto watch = [&](int p) {                                          // minus the multipliers of pivot p's columns
         if constexpr (COLS && T > 1) {
-            double m = 0.0;                                             // a NaN among them reaches a later pivot
+            unsigned m = 0;
 #pragma unroll
             for (int i = 0; i < T; ++i)
-                if (i != p) m = fmax(m, fabs(S[i][p]));
-            G.see(m);
+                if (i != p) m = max(m, abs_key_bits(S[i][p]));
+            G.see_key(m);
             G.pin();
         }
     };
