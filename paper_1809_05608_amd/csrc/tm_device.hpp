@@ -205,7 +205,8 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Block-wide deterministic reductions over kBlock threads (fixed shuffle + LDS order).
+// Block-wide deterministic reductions over THREADS threads (fixed shuffle + LDS order).
+template <int THREADS = kBlock>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -214,10 +215,11 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
     if (l == 0) sh[w] = v;
     __syncthreads();
     double s = 0.0;
-    for (int j = 0; j < kBlock / 64; ++j) s += sh[j];
+    for (int j = 0; j < THREADS / 64; ++j) s += sh[j];
     return s;
 }
 
+template <int THREADS = kBlock>
 __device__ __forceinline__ double block_max(double v, double* sh) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
@@ -226,12 +228,13 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
     if (l == 0) sh[w] = v;
     __syncthreads();
     double s = sh[0];
-    for (int j = 1; j < kBlock / 64; ++j) s = fmax(s, sh[j]);
+    for (int j = 1; j < THREADS / 64; ++j) s = fmax(s, sh[j]);
     return s;
 }
 
+template <int THREADS = kBlock>
 __device__ __forceinline__ int block_or(int v, double* sh) {
-    return block_max(v ? 1.0 : 0.0, sh) > 0.0 ? 1 : 0;
+    return block_max<THREADS>(v ? 1.0 : 0.0, sh) > 0.0 ? 1 : 0;
 }
 
 // Zone geometry from three consecutive edges (lo = i-1/2, hi = i+1/2, hi2 = i+3/2):

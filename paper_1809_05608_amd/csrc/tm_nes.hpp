@@ -12,13 +12,15 @@ template <int T>
 struct NesLds {
     double P[T * T * 16];          // tile (t, s) as an A operand: P[4t + b][4s + a] at 4a + b
     double near[T][6][4];          // P[k][k - n] (n = 1..3), then P[k][k + n], of row a of tile t
-    // by all threads of a block of kBlock; the caller synchronises
+    // by all threads of a block; the caller synchronises
+    template <int THREADS = kBlock>
     __device__ __forceinline__ void fill(const Consts& cs) {
-        for (int x = threadIdx.x; x < T * T * 16; x += kBlock) {
+#pragma unroll
+        for (int x = threadIdx.x; x < T * T * 16; x += THREADS) {
             const int tile = x / 16, ka = (x % 16) / 4, kb = x % 4;
             P[x] = cs.P[4 * (tile / T) + kb][4 * (tile % T) + ka];
         }
-        for (int x = threadIdx.x; x < T * 24; x += kBlock) {
+        for (int x = threadIdx.x; x < T * 24; x += THREADS) {
             const int n = (x / 4) % 6, row = x % 4, k = 4 * (x / 24) + row;
             const int col = n < 3 ? row - 1 - n : row + n - 2;           // within the tile
             near[x / 24][n][row] = col >= 0 && col < 4 ? cs.P[k][k - row + col] : 0.0;

@@ -1,10 +1,11 @@
 // FP64 kernels of libtm over cells: grid constants, residual with per-system norms and
 // conservation sums, debug Jacobian blocks, and the adjoint vector-Jacobian product.
 //
-// Mapping of the residual and VJP kernels: one 256-thread block per (species, ray) system, a chunk
+// Mapping of the residual and VJP kernels: one block per (species, ray) system, a chunk
 // of zones at a time; each edge flux is computed once, and the block reduces per-system quantities
 // in a fixed order (deterministic, no atomics).
 #include <algorithm>
+#include <type_traits>
 
 #include "tm_kernels.hpp"
 #include "tm_nes.hpp"
@@ -130,14 +131,14 @@ __device__ __forceinline__ double inv_mfp(const Fields& f, size_t c) {
 
 // ---------------------------------------------------------------- residual / statistics
 
-// Mapping: one block per system, its four wavefronts taking a quarter of the ray each, in chunks of 16 zones.
+// Mapping: one block per system, its one to four wavefronts taking consecutive parts of the ray, in chunks of 16 zones.
 // Lane 16 a + j holds groups a, 4 + a, 8 + a, ... of the chunk's zone j: the natural order of the 4 x 4 x 4
 // matrix products with the sixteen zones as columns.  The NES sums over k' are products of the constant shape
 // matrix with vectors per zone, so they go to the matrix cores, tile by tile (nes_sums); a neighbouring zone's
 // value is one lane away (two DPP moves); LDS holds only the constants.  Each edge flux is computed once, by the
 // zone below the edge; a chunk's last row serves as the upper neighbour only, and the flux below its first row
 // comes from the chunk before.
-// The sums over k' in Horner form, one cell per thread, took 38 steps of three LDS reads (32 bytes a lane) and were
+// The sums over k' in Horner form, one cell per thread (the kernel by cells below), took 38 steps of three LDS reads (32 bytes a lane) and were
 // bound by LDS; now vector issue (63% of the cycles) and memory share the time: 32768 systems of 540 zones x 20
 // groups 7.3 -> 4.6 ms (48 bytes a cell once: 3.9 ms at the 4.4 TB/s of a copy), with the geometric options 9.6 ->
 // 5.0, 16384 systems of 300 x 32 4.5 -> 2.6, of 300 x 12 1.0 -> 0.9, 720 of 540 x 20 0.26 -> 0.14.  Loading in the
@@ -177,19 +178,20 @@ __device__ __forceinline__ D& at(D* base, unsigned off) {
 struct ResidualSums {
     double n = 0.0, nold = 0.0, e = 0.0, q = 0.0, nes = 0.0, b = 0.0;
 };
+template <int THREADS>
 __device__ __forceinline__ void residual_end(const Shape& sh, const Fields& f, const ResidualOut& out, long long sys,
                                              double gmax, double gscale, int bad, ResidualSums s, double* red) {
     const int I = sh.I, ray = (int)(sys % sh.R);
-    const double res = block_max(gmax, red);
-    const double floor_g = 32.0 * 2.220446049250313e-16 * block_max(gscale, red);
-    bad = block_or(bad, red);
+    const double res = block_max<THREADS>(gmax, red);
+    const double floor_g = 32.0 * 2.220446049250313e-16 * block_max<THREADS>(gscale, red);
+    bad = block_or<THREADS>(bad, red);
     if (out.stats) {
-        s.n = block_sum(s.n, red);
-        s.nold = block_sum(s.nold, red);
-        s.e = block_sum(s.e, red);
-        s.q = block_sum(s.q, red);
-        s.nes = block_sum(s.nes, red);
-        s.b = block_sum(s.b, red);
+        s.n = block_sum<THREADS>(s.n, red);
+        s.nold = block_sum<THREADS>(s.nold, red);
+        s.e = block_sum<THREADS>(s.e, red);
+        s.q = block_sum<THREADS>(s.q, red);
+        s.nes = block_sum<THREADS>(s.nes, red);
+        s.b = block_sum<THREADS>(s.b, red);
     }
     if (threadIdx.x == 0) {
         const double rr = bad ? __builtin_nan("") : res;
@@ -234,18 +236,18 @@ __device__ __forceinline__ void residual_end(const Shape& sh, const Fields& f, c
     }
 }
 
-// GEO compiles the neutrinosphere options (limiter 2, outer boundary 2) in.
-template <int T, bool GEO>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(T <= 3 ? 4 : T <= 6 ? 3 : 2)))
+// GEO compiles the neutrinosphere options (limiter 2, outer boundary 2) in; W is the block's number of wavefronts.
+template <int T, bool GEO, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(T <= 3 ? 4 : T <= 5 ? 3 : 2)))
 void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double* __restrict__ psi_n,
                 const double* __restrict__ psi, double* __restrict__ G_out, double g_sign, ResidualOut out) {
     constexpr int NT = 4 * T;
     __shared__ NesLds<T> sm;
     __shared__ double s_W[NT], s_We[NT], s_de[NT], s_rnu[GEO ? NT : 1];
     constexpr int PS = NT + 1;                            // row stride: the 16 rows of a group in different banks
-    __shared__ double s_cell[kBlock / 64][4][16 * PS + 1];    // a chunk's psi, then psi_n, then G; kappa_a, eta, kappa_s
-    __shared__ double2 s_edge[kBlock / 64][T][4];         // flux and derivative at the edge above row 14
-    __shared__ double red[kBlock / 64];
+    __shared__ double s_cell[W][4][16 * PS + 1];          // a chunk's psi, then psi_n, then G; kappa_a, eta, kappa_s
+    __shared__ double2 s_edge[W][T][4];         // flux and derivative at the edge above row 14
+    __shared__ double red[W];
     const long long sys = blockIdx.x;
     if (out.mode == kResTrial && out.pending[sys] == 0) return;         // no trial to evaluate
     if (out.mode == kResEval && out.pending && out.pending[sys % sh.R] == 0) return;
@@ -257,7 +259,7 @@ void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double*
     const bool geo = GEO && (sh.limiter == 2 || sh.outer_bc == 2);      // neutrinosphere radii in use
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-    if (nes) sm.fill(*cs);
+    if (nes) sm.template fill<64 * W>(*cs);
     if (threadIdx.x < NT) {
         const int k = threadIdx.x;
         s_W[k] = k < N ? cs->W[k] : 0.0;
@@ -274,8 +276,10 @@ void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double*
     const double* const zT = f.temp ? f.temp + (size_t)ray * I : re;
     const double* const zA = f.nes_amp ? f.nes_amp + (size_t)sys * I : re;
 
-    // this wavefront's zones lo .. hi - 1; row 0 of its first chunk is the zone below them
-    const int per = (I + 3) / 4, lo = min(I, wave * per), hi = min(I, lo + per);
+    // this wavefront's zones lo .. hi - 1; row 0 of its first chunk is the zone below them.  Whole chunks, so that no
+    // wavefront takes another one for a zone or two: 15 zones each, one of them the zone below but in the first.
+    const int per = 15 * ((I + W - 1 + 15 * W - 1) / (15 * W)) - 1;
+    const int lo = wave == 0 ? 0 : min(I, wave * per + 1), hi = min(I, (wave + 1) * per + 1);
     if ((threadIdx.x & 63) < 4 * T)                      // the edge below zone 0 has zero flux
         s_edge[wave][(threadIdx.x & 63) >> 2][threadIdx.x & 3] = make_double2(0.0, 0.0);
     const int zf = lo == hi ? hi : lo > 0 ? lo - 1 : 0;
@@ -284,7 +288,9 @@ void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double*
         // what derives from the lane id, the constants in LDS among it, is fetched again for each chunk
         const int lane = opaque_lane(), a = lane >> 4, j = lane & 15, b = lane & 3, ab = 4 * a + b;
         const int i = z0 + j, ic = min(i, I - 1);
-        const bool out_row = j < 15 && i >= lo && i < hi;
+        int lo_v = lo, hi_v = hi;                             // in vector registers: the geometric options spill scalars
+        if (GEO) asm volatile("" : "+v"(lo_v), "+v"(hi_v));
+        const bool out_row = j < 15 && i >= lo_v && i < hi_v;
         // a chunk's cells are contiguous: loaded and stored in order, turned into zones by groups in LDS
         const size_t chunk = cells + (size_t)z0 * N;
         const int last = min(16, I - z0) * N - 1;
@@ -422,7 +428,7 @@ void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double*
         }
         wave_sync();
         if (G_out) {
-            const int x0 = (max(z0, lo) - z0) * N, x1 = (min(z0 + 15, hi) - z0) * N;      // the rows put out
+            const int x0 = (max(z0, lo_v) - z0) * N, x1 = (min(z0 + 15, hi_v) - z0) * N;      // the rows put out
 #pragma unroll
             for (int q = 0; q < T; ++q) {
                 const int x = 64 * q + lane;
@@ -432,23 +438,23 @@ void k_residual(Shape sh, Fields f, const Consts* __restrict__ cs, const double*
         wave_sync();
     }
 
-    residual_end(sh, f, out, sys, gmax, gscale, bad, sums, red);
+    residual_end<64 * W>(sh, f, out, sys, gmax, gscale, bad, sums, red);
 }
 
 // Up to four groups a zone is a single column of the matrix products above, a quarter to all of it padding, and a
-// chunk's way through LDS and the sums of products cost more than they save: here a thread is a cell.  The 256 threads
-// form 64 rows of four groups; row r of a chunk holds zone z0 - 1 + r, the first and the last row being halo.  Every
-// cell brings psi and its mean free path to LDS, computes the flux at its upper edge, and then G from both fluxes of
-// its zone and the scattering sums over the zone's row, in Horner form.  The next chunk's loads are in flight while
+// chunk's way through LDS and the sums of products cost more than they save; on rays of a few zones most of a chunk's
+// sixteen are padding, and a wavefront works through their groups alone.  There a thread is a cell.  The 256 threads
+// form 256 / NT rows of NT groups; row r of a chunk holds zone z0 - 1 + r, and the first and the last row are halo.
+// Every cell brings psi and its mean free path to LDS, computes the flux at its upper edge, and then G from both fluxes
+// of its zone and the scattering sums over the zone's row, in Horner form.  The next chunk's loads are in flight while
 // a chunk is worked on.  Latency and LDS bound it.  100 zones, against the sixteen-zone chunks above: 65536 systems
 // of one group 0.45 against 0.55 ms, of four 0.52 against 0.60; 256 systems of four 19.9 against 21.5 us.
 // LAPSE and GEO compile the lapse factors and the neutrinosphere options in.
-template <bool LAPSE, bool GEO>
+template <int NT, bool LAPSE, bool GEO>
 __global__ __launch_bounds__(kBlock) void k_residual_rows(Shape sh, Fields f, const Consts* __restrict__ cs,
                                                           const double* __restrict__ psi_n,
                                                           const double* __restrict__ psi, double* __restrict__ G_out,
                                                           double g_sign, ResidualOut out) {
-    constexpr int NT = 4;
     constexpr int RZ = kBlock / NT;             // rows per chunk (zones incl. one halo on each side)
     constexpr int ZB = RZ - 2;                  // output zones per chunk
     constexpr int PS = NT + 1;                  // padded LDS row stride (conflict-free column reads)
@@ -475,7 +481,8 @@ __global__ __launch_bounds__(kBlock) void k_residual_rows(Shape sh, Fields f, co
     const double c = sh.c_dt;
     const bool diff = sh.terms & kDiffusion, emabs = sh.terms & kEmAbs, nes = sh.terms & kNes;
     const int t = threadIdx.x, zl = t / NT, k = t - zl * NT;
-    const bool lane_ok = k < N;
+    const bool tile = zl < RZ;                  // a row of the chunk: not the remainder of 256 threads by NT
+    const bool lane_ok = tile && k < N;
     const bool out_row = zl >= 1 && zl <= RZ - 2;
 
     if (nes)
@@ -541,40 +548,44 @@ __global__ __launch_bounds__(kBlock) void k_residual_rows(Shape sh, Fields f, co
         const double p = cur.p;
         const double lam = (diff && in_zone) ? drcp(cur.ka + cur.et + cur.ks) : 0.0;
         __syncthreads();                                    // previous chunk done with the LDS rows
-        s_psi[zl][k] = p;
-        if (nes) s_pq[zl][k] = make_double2(p, 1.0 - p);
-        s_lam[zl][k] = lam;
+        if (tile) {
+            s_psi[zl][k] = p;
+            if (nes) s_pq[zl][k] = make_double2(p, 1.0 - p);
+            s_lam[zl][k] = lam;
+        }
         if (t < 3 * RZ + 2) s_z[t] = cur.zv;
         __syncthreads();
-        s_d[zl][k] = (nes && in_zone && out_row && k + 1 < N) ? exp(-dek * drcp(s_T[zl])) : 0.0;
-        // flux at the upper edge of this row's zone, computed once per edge
-        if (diff) {
-            double H = 0.0, du = 0.0, dv = 0.0;
-            if (in_zone && zl + 1 < RZ) {
-                if (i + 1 < I) {
-                    const double rlo = s_re[zl], rhi = s_re[zl + 1], rp = s_re[zl + 2];
-                    const double D = 0.5 * (rhi + rp) - 0.5 * (rlo + rhi);
-                    const EdgeFlux e = edge_flux(p, s_psi[zl + 1][k], sqrt(lam * s_lam[zl + 1][k]), D,
-                                                 sh.psi_floor, sh.limiter,
-                                                 (GEO && sh.limiter == 2) ? limb_factor(rhi, rnuk) : -1.0);
-                    H = e.H;
-                    du = e.dHu;
-                    dv = e.dHv;
-                } else if (sh.outer_bc == 1) {
-                    H = p;                              // free streaming, eq. a22 limit
-                    du = 1.0;
-                } else if (GEO && sh.outer_bc == 2) {   // ghost zone of eq. a62af
-                    const double rlo = s_re[zl], rhi = s_re[zl + 1];
-                    const Ghost gh = outer_ghost(rlo, rhi, rnuk);
-                    const EdgeFlux e = edge_flux(p, gh.ratio * p, lam, gh.D, sh.psi_floor, sh.limiter,
-                                                 sh.limiter == 2 ? limb_factor(rhi, rnuk) : -1.0);
-                    H = e.H;
-                    du = e.dHu + gh.ratio * e.dHv;
+        if (tile) {
+            s_d[zl][k] = (nes && in_zone && out_row && k + 1 < N) ? exp(-dek * drcp(s_T[zl])) : 0.0;
+            // flux at the upper edge of this row's zone, computed once per edge
+            if (diff) {
+                double H = 0.0, du = 0.0, dv = 0.0;
+                if (in_zone && zl + 1 < RZ) {
+                    if (i + 1 < I) {
+                        const double rlo = s_re[zl], rhi = s_re[zl + 1], rp = s_re[zl + 2];
+                        const double D = 0.5 * (rhi + rp) - 0.5 * (rlo + rhi);
+                        const EdgeFlux e = edge_flux(p, s_psi[zl + 1][k], sqrt(lam * s_lam[zl + 1][k]), D,
+                                                     sh.psi_floor, sh.limiter,
+                                                     (GEO && sh.limiter == 2) ? limb_factor(rhi, rnuk) : -1.0);
+                        H = e.H;
+                        du = e.dHu;
+                        dv = e.dHv;
+                    } else if (sh.outer_bc == 1) {
+                        H = p;                              // free streaming, eq. a22 limit
+                        du = 1.0;
+                    } else if (GEO && sh.outer_bc == 2) {   // ghost zone of eq. a62af
+                        const double rlo = s_re[zl], rhi = s_re[zl + 1];
+                        const Ghost gh = outer_ghost(rlo, rhi, rnuk);
+                        const EdgeFlux e = edge_flux(p, gh.ratio * p, lam, gh.D, sh.psi_floor, sh.limiter,
+                                                     sh.limiter == 2 ? limb_factor(rhi, rnuk) : -1.0);
+                        H = e.H;
+                        du = e.dHu + gh.ratio * e.dHv;
+                    }
                 }
+                s_H[zl][k] = H;                             // the edge below zone 0 has zero flux
+                s_du[zl][k] = du;
+                s_dv[zl][k] = dv;
             }
-            s_H[zl][k] = H;                             // the edge below zone 0 has zero flux
-            s_du[zl][k] = du;
-            s_dv[zl][k] = dv;
         }
         __syncthreads();
         const In now = cur;
@@ -618,10 +629,14 @@ __global__ __launch_bounds__(kBlock) void k_residual_rows(Shape sh, Fields f, co
             // k' > k: the out kernel carries exp(-(eps_k' - eps_k)/T) = prod_{j=k}^{k'-1} d_j.  The weighted sum
             // of those products is taken in Horner form from the last group down, one multiply-add and one
             // multiply per term: h <- (h + P_kk' (1 - psi_k')) d_{k'-1}.
+            // The group index through an opaque copy: its compares, one a term, stay inside the zone loop instead of
+            // being kept across it as 2 (NT - 1) lane masks.
+            int kz = k;
+            asm volatile("" : "+v"(kz));
             double hup = 0.0, sin_ = 0.0;
 #pragma unroll
             for (int kp = NT - 1; kp >= 1; --kp) {
-                if (kp > k) {                         // padding groups add exact zeros (P = 0 there)
+                if (kp > kz) {                         // padding groups add exact zeros (P = 0 there)
                     const double Pk = s_P[k * PS + kp];
                     const double2 pq = s_pq[zl][kp];
                     hup = fma(Pk, pq.y, hup) * s_d[zl][kp - 1];
@@ -633,7 +648,7 @@ __global__ __launch_bounds__(kBlock) void k_residual_rows(Shape sh, Fields f, co
             double hdn = 0.0, sout = hup;
 #pragma unroll
             for (int kp = 0; kp < NT - 1; ++kp) {
-                if (kp < k) {
+                if (kp < kz) {
                     const double Pk = s_P[k * PS + kp];
                     const double2 pq = s_pq[zl][kp];
                     hdn = fma(Pk, pq.x, hdn) * s_d[zl][kp];
@@ -662,7 +677,7 @@ __global__ __launch_bounds__(kBlock) void k_residual_rows(Shape sh, Fields f, co
         }
     }
 
-    residual_end(sh, f, out, sys, gmax, gscale, bad, sums, red);
+    residual_end<kBlock>(sh, f, out, sys, gmax, gscale, bad, sums, red);
 }
 
 // ---------------------------------------------------------------- debug Jacobian blocks
@@ -1167,27 +1182,52 @@ hipError_t launch_residual(const Shape& sh, const Fields& f, const Consts* cs, c
                            hipStream_t st) {
     const long long nsys = (long long)sh.S * sh.R;
     const bool geo = sh.limiter == 2 || sh.outer_bc == 2;
-    // Up to four groups: threads by cells, except that the geometric options (more registers and arithmetic a cell)
-    // gain by the chunks once the chip is full: 768 systems of 100 zones x 4 groups 25 against 28 us, 1024: 30 against
-    // 28.5, 32768: 0.37 against 0.34 ms.
-    if (sh.N <= 4 && !(geo && nsys > 768)) {
+    const int groups = padded_groups(sh.N);
+    if (groups < 0) return hipErrorInvalidValue;
+    // Threads by cells or sixteen-zone chunks.  Up to four groups the cells, except that the geometric options (more
+    // registers and arithmetic a cell) gain by the chunks once the chip is full: 768 systems of 100 zones x 4 groups 25
+    // against 28 us, 1024: 30 against 28.5, 32768: 0.37 against 0.34 ms.  With more groups the chunks, but for rays so
+    // short that one wavefront works alone through the groups of a few zones, while a block of cells has them all at
+    // once: few systems (256 of 10 zones x 32 groups 28.5 against 33 us, of 4 x 24 22 against 27; 1024 of 15 x 32 43
+    // against 38), and a ray that is one chunk of rows up to 1024 systems (1024 of 4 zones x 20 groups 25 against 28 us,
+    // 8192: 73 against 68) or of more than 24 groups (8192 of 4 x 28 89 against 108, of 4 x 24 79 against 77).
+    const bool one_chunk = sh.I <= kBlock / groups - 2;
+    const bool by_cells = sh.N <= 4 ? !(geo && nsys > 768)
+                                    : (one_chunk && (nsys <= 1024 || sh.N > 24)) || (sh.I <= 15 && nsys <= 512);
+    if (by_cells) {
         const dim3 grid((unsigned)nsys), block(kBlock);
-        if (geo) hipLaunchKernelGGL((k_residual_rows<true, true>), grid, block, 0, st, sh, f, cs, psi_n, psi, G_out, g_sign, out);
-        else if (f.lapse)
-            hipLaunchKernelGGL((k_residual_rows<true, false>), grid, block, 0, st, sh, f, cs, psi_n, psi, G_out, g_sign, out);
-        else hipLaunchKernelGGL((k_residual_rows<false, false>), grid, block, 0, st, sh, f, cs, psi_n, psi, G_out, g_sign, out);
+        if (geo) {
+            TM_DISPATCH_NT(groups, hipLaunchKernelGGL((k_residual_rows<NT, true, true>), grid, block, 0, st, sh, f, cs, psi_n,
+                                                   psi, G_out, g_sign, out));
+        } else if (f.lapse) {
+            TM_DISPATCH_NT(groups, hipLaunchKernelGGL((k_residual_rows<NT, true, false>), grid, block, 0, st, sh, f, cs, psi_n,
+                                                   psi, G_out, g_sign, out));
+        } else {
+            TM_DISPATCH_NT(groups, hipLaunchKernelGGL((k_residual_rows<NT, false, false>), grid, block, 0, st, sh, f, cs, psi_n,
+                                                   psi, G_out, g_sign, out));
+        }
         return hipGetLastError();
     }
-    if (geo) {
-        TM_DISPATCH_NT(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_residual<NT / 4, true>), dim3((unsigned)nsys), dim3(kBlock), 0, st, sh, f,
-                                          cs, psi_n, psi, G_out, g_sign, out));
-    } else {
-        TM_DISPATCH_NT(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_residual<NT / 4, false>), dim3((unsigned)nsys), dim3(kBlock), 0, st, sh, f,
-                                          cs, psi_n, psi, G_out, g_sign, out));
-    }
-    return hipGetLastError();
+    // The fewest wavefronts that take no more chunks each than four would: one without zones holds registers and LDS for
+    // nothing.  Against four wavefronts with a quarter of the ray each, 40000 systems: of 4 zones x 8 groups 0.29 -> 0.091
+    // ms, 4 x 20 0.64 -> 0.23, 30 x 20 0.76 -> 0.60, 40 x 20 0.80 -> 0.64, 60 x 20 1.19 -> 0.95.
+    auto each = [&](int W) { return (sh.I + W - 1 + 15 * W - 1) / (15 * W); };
+    auto chunks = [&](auto waves) -> hipError_t {
+        constexpr int W = decltype(waves)::value;
+        const dim3 grid((unsigned)nsys), block(64 * W);
+        if (geo) {
+            TM_DISPATCH_NT(groups, hipLaunchKernelGGL((k_residual<NT / 4, true, W>), grid, block, 0, st, sh, f, cs,
+                                                                   psi_n, psi, G_out, g_sign, out));
+        } else {
+            TM_DISPATCH_NT(groups, hipLaunchKernelGGL((k_residual<NT / 4, false, W>), grid, block, 0, st, sh, f,
+                                                                   cs, psi_n, psi, G_out, g_sign, out));
+        }
+        return hipGetLastError();
+    };
+    if (each(1) == each(4)) return chunks(std::integral_constant<int, 1>());
+    if (each(2) == each(4)) return chunks(std::integral_constant<int, 2>());
+    if (each(3) == each(4)) return chunks(std::integral_constant<int, 3>());
+    return chunks(std::integral_constant<int, 4>());
 }
 
 hipError_t launch_blocks(const Shape& sh, const Fields& f, const Consts* cs, const double* psi, double* blocks,
