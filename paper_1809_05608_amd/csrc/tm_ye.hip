@@ -9,8 +9,9 @@
 // the absorption and emission opacities of the pair are linear in Y_e over the step, with their
 // derivatives given as inputs.
 //
-//   k_ye_couple       one block per ray, sixteen zones to a wavefront: completes the species residual (evaluated by the
-//                     single-species residual kernel with the opacities of Y_e^n) with the Y_e terms,
+//   k_ye_couple       one block per ray, of up to sixteen zones one wavefront; sixteen zones to a wavefront:
+//                     completes the species residual (evaluated by the single-species residual kernel
+//                     with the opacities of Y_e^n) with the Y_e terms,
 //                     evaluates the Y_e residual, max|G|, the rounding level, the lepton number and the
 //                     Newton/line-search decisions.
 //   k_ye_factor       one wavefront per ray: lane r owns row r of the coupled block.  Per zone the row is
@@ -25,6 +26,8 @@
 //   k_ye_temperature  sixteen zones to a wavefront: energy-weighted collision sources of every species, the
 //                     matter energy change and the new temperature (k_ye_temperature_zone: one thread per zone, for
 //                     very many zones of up to five groups).
+#include <type_traits>
+
 #include "tm_kernels.hpp"
 #include "tm_nes.hpp"
 
@@ -33,6 +36,11 @@ namespace tmk {
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
     return v;
 }
 
@@ -114,18 +122,23 @@ __device__ __forceinline__ void load_groups(const double* row, int a, int N, dou
     for (int t = 0; t < T; ++t) v[t] = row[t + 1 < T ? 4 * t + a : min(4 * t + a, N - 1)];
 }
 
-// PAIR compiles the pair sources in; the launch takes it when pair inputs are given.
-template <int T, bool PAIR>
-__global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs,
-                                                      const double* __restrict__ psi, const double* __restrict__ ye,
-                                                      double* __restrict__ G, double* __restrict__ GY,
-                                                      const double* __restrict__ level_sp, YeOut out) {
+// PAIR compiles the pair sources in; the launch takes it when pair inputs are given.  RAYS, 1 or 4, is a block's number
+// of rays: one for its four wavefronts, or one each.  With pairs, up to two tiles are held to three wavefronts a SIMD: two
+// tiles took 176 registers, eight more than allow it (step of 65536 rays of 24 zones x 8 groups 34.6 -> 32.9 ms).
+template <int T, bool PAIR, int RAYS>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PAIR && T <= 2 ? 3 : 1)))
+void k_ye_couple(Shape sh, Fields f, YeFields y, const Consts* __restrict__ cs, const double* __restrict__ psi,
+                 const double* __restrict__ ye, double* __restrict__ G, double* __restrict__ GY,
+                 const double* __restrict__ level_sp, YeOut out) {
     __shared__ double red[kBlock / 64];
     __shared__ PairLds<PAIR ? T : 1> sp;
-    const long long ray = blockIdx.x;
-    if (out.mode == kResTrial && out.pending[ray] == 0) return;          // no trial to evaluate
+    constexpr int W = kBlock / 64 / RAYS;                 // wavefronts a ray
     const int R = sh.R, I = sh.I, N = sh.N;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a = lane >> 4, j = lane & 15;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), a = lane >> 4, j = lane & 15;
+    const int ray = RAYS * blockIdx.x + wave / W;
+    // nothing to do for a wavefront past the last ray, or without a trial to evaluate; the block's others meet at a barrier
+    const bool idle = (RAYS > 1 && ray >= R) || (out.mode == kResTrial && out.pending[ray] == 0);
+    if (RAYS == 1 && idle) return;
     const double c = sh.c_dt;
     const bool emabs = sh.terms & kEmAbs;
     const double* re = f.r_edge + (size_t)ray * (I + 1);
@@ -134,13 +147,14 @@ __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFiel
         sp.fill(y, f, *cs, N);
         __syncthreads();
     }
-    double W[T];
+    if (idle) return;
+    double Wt[T];
 #pragma unroll
-    for (int t = 0; t < T; ++t) W[t] = 4 * t + a < N ? cs->W[4 * t + a] : 0.0;
+    for (int t = 0; t < T; ++t) Wt[t] = 4 * t + a < N ? cs->W[4 * t + a] : 0.0;
 
     double gmax = 0.0, mag_max = 0.0, lep = 0.0;
     int bad = 0;
-    for (int z0 = 16 * wave; z0 < I; z0 += 16 * (kBlock / 64)) {
+    for (int z0 = 16 * (wave % W); z0 < I; z0 += 16 * W) {
         const int i = z0 + j, ic = min(i, I - 1);
         const bool in_zone = i < I;
         const double Y = ye[zb + ic], Yn = y.ye_n[zb + ic], rho = y.rho[zb + ic];
@@ -185,12 +199,12 @@ __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFiel
                     const double slope = det * h - dka * p;
                     g -= c * dy * slope;                                 // opacities at Y_e instead of Y_e^n
                     const double em = (v_et[t] + dy * det) * h, ab = (v_ka[t] + dy * dka) * p;
-                    const double sw = sgn * W[t];
+                    const double sw = sgn * Wt[t];
                     sY = fma(sw, em - ab, sY);
-                    sAbs = fma(W[t], fabs(em) + fabs(ab), sAbs);
+                    sAbs = fma(Wt[t], fabs(em) + fabs(ab), sAbs);
                     sD = fma(sw, slope, sD);
                 }
-                sL = fma(sgn * W[t], p, sL);
+                sL = fma(sgn * Wt[t], p, sL);
                 if (real) {
                     G[cz + k] = g;
                     bad |= !isfinite(g);
@@ -221,11 +235,19 @@ __global__ __launch_bounds__(kBlock) void k_ye_couple(Shape sh, Fields f, YeFiel
             lep += shell_volume(re[i], re[i + 1]) * (rho * Y / kBaryonMassG + kFourPiOverHc3 * ai3 * sL);
         }
     }
-    const double res = block_max(gmax, red);
-    const double mag = block_max(mag_max, red);
-    bad = block_or(bad, red);
-    if (out.lepton) lep = block_sum(lep, red);
-    if (threadIdx.x == 0) {
+    double res, mag;
+    if constexpr (RAYS == 1) {
+        res = block_max(gmax, red);
+        mag = block_max(mag_max, red);
+        bad = block_or(bad, red);
+        if (out.lepton) lep = block_sum(lep, red);
+    } else {
+        res = wave_max(gmax);
+        mag = wave_max(mag_max);
+        bad = __any(bad);
+        if (out.lepton) lep = wave_sum(lep);
+    }
+    if (RAYS == 1 ? threadIdx.x == 0 : lane == 0) {
         const double rr = bad ? __builtin_nan("") : res;
         out.res[ray] = rr;
         const double floor_g = fmax(fmax(level_sp[ray], level_sp[R + ray]), 32.0 * 2.220446049250313e-16 * mag);
@@ -912,15 +934,21 @@ __global__ __launch_bounds__(kBlock) void k_ye_temperature_zone(Shape sh, Fields
 hipError_t launch_ye_couple(const Shape& sh, const Fields& f, const YeFields& y, const Consts* cs, const double* psi,
                             const double* ye, double* G, double* GY, const double* level_sp, const YeOut& out,
                             hipStream_t st) {
-    if (y.pair_amp)
+    // Rays of at most sixteen zones leave three of four wavefronts without any, and the pair constants are staged for one
+    // wavefront's work, so there each wavefront takes a ray.  Step of 65536 rays with pairs: of 1 zone x 20 groups 9.7 ->
+    // 6.3 ms, of 4 x 8 12.8 -> 8.9, of 4 x 4 9.4 -> 6.6.
+    auto launch = [&](auto pair, auto rays) -> hipError_t {
+        constexpr bool PAIR = decltype(pair)::value;
+        constexpr int RAYS = decltype(rays)::value;
         TM_YE_DISPATCH(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_ye_couple<NT / 4, true>), dim3((unsigned)sh.R), dim3(kBlock), 0, st, sh, f, y, cs,
-                                          psi, ye, G, GY, level_sp, out))
-    else
-        TM_YE_DISPATCH(padded_groups(sh.N),
-                       hipLaunchKernelGGL((k_ye_couple<NT / 4, false>), dim3((unsigned)sh.R), dim3(kBlock), 0, st, sh, f, y,
-                                          cs, psi, ye, G, GY, level_sp, out))
-    return hipGetLastError();
+                       hipLaunchKernelGGL((k_ye_couple<NT / 4, PAIR, RAYS>), dim3((unsigned)((sh.R + RAYS - 1) / RAYS)),
+                                          dim3(kBlock), 0, st, sh, f, y, cs, psi, ye, G, GY, level_sp, out))
+        return hipGetLastError();
+    };
+    using One = std::integral_constant<int, 1>;
+    using Four = std::integral_constant<int, 4>;
+    if (y.pair_amp) return sh.I <= 16 ? launch(std::true_type(), Four()) : launch(std::true_type(), One());
+    return sh.I <= 16 ? launch(std::false_type(), Four()) : launch(std::false_type(), One());
 }
 
 hipError_t launch_ye_factor(const YeFactorArgs& a, hipStream_t st) {
