@@ -23,9 +23,23 @@ size_t factor_ws_bytes_per_system(int I, int N, bool fp32) {
 constexpr long long kWaveSystems = 768;
 
 // Up to four groups a block is one tile, and the tile kernel's wavefront carries two systems where lanes by rows
-// carry four: above this many systems, where all SIMDs are busy, the lanes are the faster.  Tiles against lanes, 300 zones x 4 groups: 8192 systems 0.75 against 1.25 ms, 16384: 1.33 against 1.36,
-// 32768: 2.40 against 1.91; one group, 32768 systems: 2.06 against 1.50.
+// carry four: above this many systems, where all SIMDs are busy, the lanes are the faster.  Tiles against lanes, 300
+// zones x 4 groups: 8192 systems 0.75 against 1.25 ms, 16384: 1.33 against 1.36, 32768: 2.40 against 1.91; one group,
+// 32768 systems: 2.06 against 1.50.
 constexpr long long kLaneSystems = 16384;
+
+// As many of five to eight groups take the lanes on rays of few zones, where what the tile kernel does once per system
+// is not spread over a chain: tiles against lanes, 8 groups: 32768 systems of 2 zones 0.175 against 0.146 ms, 300000 of 4
+// 1.70 against 1.49, of 8 2.11 against 1.95, of 16 2.99 against 2.90 and transposed 3.09 against 3.18.  The forward
+// solve up to twice the zones with the lapse and four times with the geometric options, which cost the lanes less:
+// 300000 of 16 with the lapse 3.75 against 3.37, of 24 geometric 4.5 against 4.0, of 32 5.5 against 5.0; but 32768 of
+// 24 with the lapse 0.61 against 0.62, 78125 of 48 geometric 2.07 against 2.03.
+static bool takes_lanes(const FactorArgs& a, bool transpose) {
+    if (a.list || a.total <= kLaneSystems || a.sh.N > 8) return false;
+    if (a.sh.N <= 4) return true;
+    const bool geo = a.sh.limiter == 2 || a.sh.outer_bc == 2;
+    return a.sh.I <= (transpose ? 8 : geo ? 32 : a.f.lapse ? 16 : 8);
+}
 
 // Up to this many systems a float32 launch leaves the chip waiting for one wavefront's chain of zones, 16 systems
 // from one end: the FP64 kernels with two or half a system per wavefront from both ends are faster up to about
@@ -63,13 +77,12 @@ hipError_t launch_factor(const FactorArgs& a, bool fp32, bool transpose, bool pi
         launch_factor_quad(a, st, kernel))
         return hipGetLastError();
     // FP64 with diagonal pivots: on the matrix cores, both ends of a ray at once, for every option and, but for very
-    // many systems of up to four groups, every group count (one row per lane: 8.2 ms against 2.1 at 720 systems of 540
-    // zones x 20 groups, 122 against 58 at 65536; five groups of 100 zones, 65536 systems: 2.92 against 2.63).  The tile
-    // kernel addresses the cells of two systems with 32-bit byte offsets.
+    // many systems of few groups (takes_lanes), every group count (one row per lane: 8.2 ms against 2.1 at 720 systems of
+    // 540 zones x 20 groups, 122 against 58 at 65536; five groups of 100 zones, 65536 systems: 2.92 against 2.63).  The
+    // tile kernel addresses the cells of two systems with 32-bit byte offsets.
     if (!fp32 && !pivot) {
         const bool few = a.total <= kWaveSystems, far = (long long)a.sh.I * a.sh.N >= (1ll << 27);
-        const bool lanes = a.sh.N <= 4 && a.total > kLaneSystems && !a.list;
-        if (!lanes) return few || far ? launch_factor_wave(a, transpose, st) : launch_factor_tile(a, transpose, st);
+        if (!takes_lanes(a, transpose)) return few || far ? launch_factor_wave(a, transpose, st) : launch_factor_tile(a, transpose, st);
     }
     if (a.sh.limiter == 2 || a.sh.outer_bc == 2) return launch_factor_geo(a, fp32, transpose, pivot, st);
     return launch_lane<false>(a, fp32, transpose, pivot, st);

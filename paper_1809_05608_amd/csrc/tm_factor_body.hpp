@@ -2,8 +2,8 @@
 // step (eq. a62ae), one (species, ray) system per SL-lane group of a wavefront.
 //
 // These lane kernels serve the partial-pivoting re-run (both precisions), the float32 solves that the quad kernel
-// does not take and FP64 solves of very many systems of up to four groups; the other FP64 solves with diagonal
-// pivots run on matrix-core tiles (tm_factor_t.hip, tm_factor_w.hip).
+// does not take and FP64 solves of very many systems of up to four groups, or eight on rays of few zones; the other
+// FP64 solves with diagonal pivots run on matrix-core tiles (tm_factor_t.hip, tm_factor_w.hip).
 //
 // Layout on the chip: lane k of a group owns row k of the current zone's dense N x N
 // block (N <= NT <= 32, SL = 16 or 32 lanes per system, 4 or 2 systems per wave64).
@@ -620,12 +620,12 @@ static hipError_t launch_tp(const FactorArgs& a, bool tr, bool pv, hipStream_t s
         else launch_t<T, NT, false, true, GEO>(a, st);
         return hipGetLastError();
     }
-    if constexpr (std::is_same<T, float>::value || NT == 4) {
+    if constexpr (std::is_same<T, float>::value || NT <= 8) {
         if (tr) launch_t<T, NT, true, false, GEO>(a, st);
         else launch_t<T, NT, false, false, GEO>(a, st);
         return hipGetLastError();
     }
-    return hipErrorInvalidValue;     // FP64 with diagonal pivots above four groups: the tile and wave kernels
+    return hipErrorInvalidValue;     // FP64 with diagonal pivots above eight groups: the tile and wave kernels
 }
 
 template <int NT, bool GEO>
