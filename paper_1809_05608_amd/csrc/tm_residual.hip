@@ -139,7 +139,7 @@ __device__ __forceinline__ double inv_mfp(const Fields& f, size_t c) {
 // zone below the edge; a chunk's last row serves as the upper neighbour only, and the flux below its first row
 // comes from the chunk before.
 // The sums over k' in Horner form, one cell per thread (the kernel by cells below), took 38 steps of three LDS reads (32 bytes a lane) and were
-// bound by LDS; now vector issue (63% of the cycles) and memory share the time: 32768 systems of 540 zones x 20
+// bound by LDS; now vector issue (61% of the cycles) and memory share the time: 32768 systems of 540 zones x 20
 // groups 7.3 -> 4.6 ms (48 bytes a cell once: 3.9 ms at the 4.4 TB/s of a copy), with the geometric options 9.6 ->
 // 5.0, 16384 systems of 300 x 32 4.5 -> 2.6, of 300 x 12 1.0 -> 0.9, 720 of 540 x 20 0.26 -> 0.14.  Loading in the
 // layout of the sums instead (32-byte pieces, no way through LDS) took 6.1 ms, most of it in the address units; a
