@@ -39,8 +39,9 @@ __device__ __forceinline__ double rcp_cubic(double x) {
 }
 
 // exp(x) for x <= 0: x = n ln 2 + r, |r| <= ln 2 / 2, with ln 2 in two parts whose first times n is exact (the argument
-// reduction of Cody and Waite), Taylor series of exp(r) to r^13 (remainder below 2^-60) and a scale by 2^n.  The coefficients come from memory through a pointer the compiler cannot see
-// through, so they are scalar operands at the point of use instead of vector registers held across a loop.
+// reduction of Cody and Waite), Taylor series of exp(r) to r^13 (remainder below 2^-60) and a scale by 2^n.  The
+// coefficients come from memory through a pointer the compiler cannot see through, so they are scalar operands at the
+// point of use instead of vector registers held across a loop.
 __constant__ const double kExpCoef[16] = {
     1.4426950408889634, -0x1.62e42fee00000p-1, -0x1.a39ef35793c76p-33,          // 1/ln 2, ln 2 to 32 bits, the rest of ln 2
     1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0,
